@@ -98,9 +98,10 @@ struct HostPlan {
   std::vector<uint8_t> adiag;
   std::vector<uint8_t> aflip;
   // device factorization: per-depth launch lists (deepest first) and pivot positions
-  std::vector<int32_t> fac_nodes;
-  std::vector<int2> fac_cn, fac_cw, fac_rb;
+  std::vector<FacNode> fac_nodes;
+  std::vector<int2> fac_rb;
   std::vector<int4> fac_tiles;
+  int64_t fin_elems = 0;
   std::vector<FacLevel> fac_lev;
   std::vector<int64_t> dpos;
   int64_t sq_elems = 0;
@@ -110,8 +111,8 @@ struct HostPlan {
     int64_t node_s, node_c, node_off, node_rowptr, node_sq, node_first, node_poff, kcol, kpos, posarr, items, item_ptr,
         nph, node_split, node_kchunk, node_yoff, node_goff, node_ldg, node_parent, order, lvl_items, lvl_recs, chunks, chunks_narrow, rblocks, small_nodes,
         sq_tiles, tiny, toff,
-        apos, adiag, aflip, bitems, pushrecs, y128recs, fac_nodes, fac_cn, fac_cw, fac_rb, fac_tiles, dpos, plan, plan2, linv, dinv, part, gbuf, ypart,
-        cnt, ctrl, fwd_end, adj_z, adj_l, adj_s, adj_t, adj_f, adj_d, ferr, fldet, end;
+        apos, adiag, aflip, bitems, pushrecs, y128recs, fac_nodes, fac_rb, fac_tiles, dpos, plan, plan2, linv, dinv, part, gbuf, ypart,
+        cnt, ctrl, fwd_end, adj_z, adj_l, adj_s, adj_t, adj_f, adj_d, ferr, fldet, finv, end;
   } off{};
   int64_t tables_bytes = 0;  // [0, tables_bytes) is uploaded once
 };
@@ -922,35 +923,66 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   H.aflip = S.aflip;
   // device factorization lists, deepest depth first
   H.fac_nodes.clear();
-  H.fac_cn.clear();
-  H.fac_cw.clear();
   H.fac_rb.clear();
   H.fac_tiles.clear();
   H.fac_lev.clear();
+  H.fin_elems = 0;
   {
     std::vector<std::vector<int64_t>> bydepth(S.depth);
     for (int64_t K = 0; K < ns; ++K) bydepth[S.sdepth[K]].push_back(K);
+    // one wavefront holds a node's 16 columns and up to eight 16-row strips in registers
+    auto is_small = [&](int64_t K, int64_t cmax) { return H.node_s[K] <= 16 && H.node_c[K] <= cmax; };
+    auto rec = [&](int64_t K, int32_t h) {
+      const int32_t s = H.node_s[K], c = H.node_c[K], ld = s + c, j0 = kFacCols * h;
+      const int32_t w = std::min(s - j0, kFacCols);
+      FacNode n{};
+      n.off = H.node_off[K] + (int64_t)j0 * (ld + 1);
+      n.rp = H.node_rowptr[K];
+      n.first = H.node_first[K] + j0;
+      n.ld = ld;
+      n.s = w;
+      n.c = ld - j0 - w;
+      n.rest = s - j0 - w;
+      return n;
+    };
     for (int64_t d = S.depth - 1; d >= 0; --d) {
       FacLevel lv{};
-      lv.nodes_b = (int32_t)H.fac_nodes.size();
-      lv.narrow_b = (int32_t)H.fac_cn.size();
-      lv.wide_b = (int32_t)H.fac_cw.size();
-      lv.rb_b = (int32_t)H.fac_rb.size();
+      lv.small4_b = (int32_t)H.fac_nodes.size();
+      for (int64_t K : bydepth[d])
+        if (is_small(K, 64)) H.fac_nodes.push_back(rec(K, 0));
+      lv.small8_b = (int32_t)H.fac_nodes.size();
+      lv.small4_n = lv.small8_b - lv.small4_b;
+      for (int64_t K : bydepth[d])
+        if (is_small(K, 128) && !is_small(K, 64)) H.fac_nodes.push_back(rec(K, 0));
+      lv.small8_n = (int32_t)H.fac_nodes.size() - lv.small8_b;
+      int64_t fin = 0;  // the scratch is used within one depth
+      for (int32_t h = 0; h < 2; ++h) {
+        lv.diag_b[h] = (int32_t)H.fac_nodes.size();
+        lv.rb_b[h] = (int32_t)H.fac_rb.size();
+        if (h == 0) lv.inner_b = (int32_t)H.fac_tiles.size();
+        for (int64_t K : bydepth[d]) {
+          if (is_small(K, 128) || H.node_s[K] <= kFacCols * h) continue;
+          FacNode n = rec(K, h);
+          n.fin = fin;
+          fin += (int64_t)kFacFin * ((n.s + 15) / 16);
+          const int32_t id = (int32_t)H.fac_nodes.size();
+          H.fac_nodes.push_back(n);
+          for (int32_t a = 0; a < (n.c + 63) / 64; ++a) H.fac_rb.push_back(int2{id, a});
+          for (int32_t b = 0; b < (n.rest + 63) / 64; ++b)
+            for (int32_t a = b; a < (n.c + 63) / 64; ++a) H.fac_tiles.push_back(int4{id, a, b, 0});
+        }
+        lv.diag_n[h] = (int32_t)H.fac_nodes.size() - lv.diag_b[h];
+        lv.rb_n[h] = (int32_t)H.fac_rb.size() - lv.rb_b[h];
+        if (h == 0) lv.inner_n = (int32_t)H.fac_tiles.size() - lv.inner_b;
+      }
+      H.fin_elems = std::max(H.fin_elems, fin);
       lv.tiles_b = (int32_t)H.fac_tiles.size();
       for (int64_t K : bydepth[d]) {
-        const int32_t s = H.node_s[K], c = H.node_c[K];
-        H.fac_nodes.push_back((int32_t)K);
-        for (int32_t q = 0; q < (s + 15) / 16; ++q) (s <= 64 ? H.fac_cn : H.fac_cw).push_back(int2{(int32_t)K, q});
-        const int32_t nr = (c + kTileM - 1) / kTileM;
-        for (int32_t a = 0; a < nr; ++a) {
-          H.fac_rb.push_back(int2{(int32_t)K, a});
+        if (is_small(K, 128)) continue;
+        const int32_t nr = (H.node_c[K] + kTileM - 1) / kTileM;
+        for (int32_t a = 0; a < nr; ++a)
           for (int32_t b = 0; b <= a; ++b) H.fac_tiles.push_back(int4{(int32_t)K, a, b, 0});
-        }
       }
-      lv.nodes_n = (int32_t)H.fac_nodes.size() - lv.nodes_b;
-      lv.narrow_n = (int32_t)H.fac_cn.size() - lv.narrow_b;
-      lv.wide_n = (int32_t)H.fac_cw.size() - lv.wide_b;
-      lv.rb_n = (int32_t)H.fac_rb.size() - lv.rb_b;
       lv.tiles_n = (int32_t)H.fac_tiles.size() - lv.tiles_b;
       H.fac_lev.push_back(lv);
     }
@@ -1004,9 +1036,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   o.bitems = take(16 * (int64_t)H.bitems.size());
   o.pushrecs = take((int64_t)sizeof(PushRec) * (int64_t)H.push.size());
   o.y128recs = take((int64_t)sizeof(Item) * (int64_t)H.y128.size());
-  o.fac_nodes = take(4 * (int64_t)H.fac_nodes.size());
-  o.fac_cn = take(8 * (int64_t)H.fac_cn.size());
-  o.fac_cw = take(8 * (int64_t)H.fac_cw.size());
+  o.fac_nodes = take((int64_t)sizeof(FacNode) * (int64_t)H.fac_nodes.size());
   o.fac_rb = take(8 * (int64_t)H.fac_rb.size());
   o.fac_tiles = take(16 * (int64_t)H.fac_tiles.size());
   o.dpos = take(8 * (int64_t)H.dpos.size());
@@ -1032,6 +1062,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   o.adj_d = take(sqb);
   o.ferr = take(8 * batch);
   o.fldet = take(16 * batch);
+  o.finv = take(H.lu ? 0 : scalar_bytes * batch * H.fin_elems);
   o.end = p;
 }
 
@@ -1187,6 +1218,8 @@ DevPlan make_devplan(const selinv_ctx *h, void *work) {
   d.dpos = (int64_t *)(b + o.dpos);
   d.ferr = (unsigned long long *)(b + o.ferr);
   d.fldet = (double *)(b + o.fldet);
+  d.finv = (void *)(b + o.finv);
+  d.fin_elems = H.fin_elems;
   d.ctrl = (int32_t *)(b + o.ctrl);
   d.trace = (int64_t *)h->trace;
   return d;
@@ -1291,9 +1324,7 @@ FactorAux make_fac_aux(const selinv_ctx *h, void *work) {
   const auto &H = h->H;
   unsigned char *b = static_cast<unsigned char *>(work);
   FactorAux a{};
-  a.nodes = (const int32_t *)(b + H.off.fac_nodes);
-  a.chunks_narrow = (const int2 *)(b + H.off.fac_cn);
-  a.chunks_wide = (const int2 *)(b + H.off.fac_cw);
+  a.nodes = (const FacNode *)(b + H.off.fac_nodes);
   a.rblocks = (const int2 *)(b + H.off.fac_rb);
   a.tiles = (const int4 *)(b + H.off.fac_tiles);
   a.lev = H.fac_lev.data();
@@ -1375,8 +1406,6 @@ void build_image(selinv_ctx *h) {
   put(img, o.pushrecs, H.push);
   put(img, o.y128recs, H.y128);
   put(img, o.fac_nodes, H.fac_nodes);
-  put(img, o.fac_cn, H.fac_cn);
-  put(img, o.fac_cw, H.fac_cw);
   put(img, o.fac_rb, H.fac_rb);
   put(img, o.fac_tiles, H.fac_tiles);
   put(img, o.dpos, H.dpos);

@@ -6,15 +6,17 @@
 // symmetrically and does no dynamic pivoting (Section 4); this is the
 // library's device producer of that input, in the panel layout the rest of
 // the path reads (strict lower L_KK, D_K on the diagonal, L_{C,K} below).
-// Right-looking supernodal form, one launch per etree depth and step, the
-// deepest depth first (every descendant of K is complete before K starts):
+// Right-looking supernodal form, etree depth by depth, the deepest first
+// (every descendant of K is complete before K starts):
 //
-//   diag   S_KK = L_KK D_K L_KK^T, unblocked in LDS on 32-column blocks with
-//          the trailing update of the rest of the block (one workgroup per
-//          node; zero or non-finite pivots are recorded, not fixed)
-//   inv    L_KK^{-1} and D_K^{-1} (the normalization's inverse kernel)
-//   lc     L_{C,K} = S_{C,K} L_KK^{-T} D_K^{-1}, one workgroup per 64-row block
-//          of C(K), column tiles right to left on FP64 MFMA (in place)
+//   small  a whole node with s <= 16 and c <= 128 in one wavefront (the lower
+//          depths hold little else)
+//   diag   S_KK = L_KK D_K L_KK^T of a block of at most kFacCols columns, its
+//          16 x 16 blocks in the registers of one workgroup
+//   lc     the rows below that block, by block forward substitution with the
+//          16 x 16 inverses the diag kernel left (one wavefront per 16 rows)
+//   inner  a node wider than kFacCols: the update of its remaining columns,
+//          then diag and lc again for those
 //   schur  S_{C,C} -= L_{C,K} D_K L_{C,K}^T on the lower block pairs of C(K),
 //          scattered into the ancestors' panels through the same index maps
 //          the selected inversion gathers through (Eq. (newset)), with FP64
@@ -35,8 +37,6 @@
 
 namespace selinv {
 
-hipError_t launch_linv(const DevPlan &pl, const DevPlan *dpl, bool cplx_, const void *src, const int2 *chunks,
-                       int32_t n, bool narrow, hipStream_t st);
 hipError_t launch_scatter(const DevPlan &pl, const DevPlan *dpl, bool cplx_, const void *vals, void *panel,
                           hipStream_t st);
 
@@ -47,187 +47,612 @@ __device__ __forceinline__ bool finite_nonzero(cplx d) {
   return (d.re != 0.0 || d.im != 0.0) && isfinite(d.re) && isfinite(d.im);
 }
 
-__device__ __forceinline__ void atomic_sub(double *p, double v) { unsafeAtomicAdd(p, -v); }
-__device__ __forceinline__ void atomic_sub(cplx *p, cplx v) {
+__device__ __forceinline__ void atomic_add_t(double *p, double v) { unsafeAtomicAdd(p, v); }
+__device__ __forceinline__ void atomic_add_t(cplx *p, cplx v) {
   double *q = reinterpret_cast<double *>(p);
-  unsafeAtomicAdd(q, -v.re);
-  unsafeAtomicAdd(q + 1, -v.im);
+  unsafeAtomicAdd(q, v.re);
+  unsafeAtomicAdd(q + 1, v.im);
 }
 
-// B(k, x) = D(k) M[k ld + x0 + x] with D(k) = Dg[k dld]: the transposed view
-// of LoadDenseBT with row k scaled by the pivot D_k (the row of a slot is
-// uniform in a wave, so the pivot is one scalar load per slot).
-template <typename T, int TK> struct LoadDenseBTScaled : LoadDenseBT<T, TK> {
-  const T *Dg;
-  int64_t dld;
-  __device__ __forceinline__ LoadDenseBTScaled(const T *M_, int ld_, int kend_, int x0, int xmax, const T *Dg_,
-                                               int64_t dld_)
-      : LoadDenseBT<T, TK>(M_, ld_, kend_, x0, xmax), Dg(Dg_), dld(dld_) {}
-  __device__ __forceinline__ void load(int k0, DVals<T, TK> &v) const {
+// ---------------------------------------------------------------------------
+// 16 x 16 blocks.  A block of S (rows i of one 16-row strip, columns j of
+// another) is held by one wavefront as register v of lane l = S(l % 16, 4 v +
+// l / 16): its transpose in the MFMA result layout, which is the A-operand
+// layout of the block and the B-operand layout of its transpose at the same
+// time.  Everything below works on transposed blocks, so that a product's
+// result is the next product's operand without any data movement:
+//   W^T = M S^T (M = L_kk^{-1}, W = L D),  L^T = D^{-1} W^T,
+//   S(i, j)^T -= L(j, k) W(i, k)^T          (M and L(j, k) conjugated if Hermitian)
+// ---------------------------------------------------------------------------
+template <typename T> struct Blk {
+  d4 p[Planes<T>::P];
+};
+
+__device__ __forceinline__ double blk_get(const Blk<double> &b, int v) { return b.p[0][v]; }
+__device__ __forceinline__ cplx blk_get(const Blk<cplx> &b, int v) { return cplx{b.p[0][v], b.p[1][v]}; }
+__device__ __forceinline__ void blk_set(Blk<double> &b, int v, double x) { b.p[0][v] = x; }
+__device__ __forceinline__ void blk_set(Blk<cplx> &b, int v, cplx x) {
+  b.p[0][v] = x.re;
+  b.p[1][v] = x.im;
+}
+template <typename T> __device__ __forceinline__ Blk<T> blk_zero() {
+  Blk<T> b;
 #pragma unroll
-    for (int m = 0; m < LoadDenseBT<T, TK>::E; ++m) {
+  for (int p = 0; p < Planes<T>::P; ++p) b.p[p] = d4{0.0, 0.0, 0.0, 0.0};
+  return b;
+}
+
+// acc += A B for 16 x 16 operands in the layout above, over the first 4 nv
+// contraction indices (complex: four real products)
+template <typename T>
+__device__ __forceinline__ void blk_mma(const Blk<T> &a, const Blk<T> &b, Blk<T> &acc, int nv = 4) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    if (v < nv) {
+      acc.p[0] = mfma16(a.p[0][v], b.p[0][v], acc.p[0]);
+      if constexpr (Planes<T>::P == 2) {
+        acc.p[1] = mfma16(a.p[0][v], b.p[1][v], acc.p[1]);
+        acc.p[0] = mfma16(-a.p[1][v], b.p[1][v], acc.p[0]);
+        acc.p[1] = mfma16(a.p[1][v], b.p[0][v], acc.p[1]);
+      }
+    }
+  }
+}
+
+// A block in LDS, plane p at q[p * stride]: element v * 64 + lane, so that
+// reads and writes of a register are contiguous.
+template <typename T> __device__ __forceinline__ Blk<T> blk_from_lds(const double *q, int stride) {
+  const int lane = threadIdx.x & 63;
+  Blk<T> b;
+#pragma unroll
+  for (int p = 0; p < Planes<T>::P; ++p)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) b.p[p][v] = q[p * stride + v * 64 + lane];
+  return b;
+}
+template <typename T> __device__ __forceinline__ void blk_to_lds(const Blk<T> &b, double *q, int stride) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int p = 0; p < Planes<T>::P; ++p)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) q[p * stride + v * 64 + lane] = b.p[p][v];
+}
+
+// Rows [0, rows) and columns [0, cols) of a 16 x 16 block at Q (leading
+// dimension ld); zeros outside (read from Q's first element).
+template <typename T>
+__device__ __forceinline__ Blk<T> blk_load(const T *Q, int64_t ld, int rows, int cols) {
+  const int r = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+  T v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    v[q] = gload(Q + (((4 * q + g) * ld + r) & opaque_mask(r < rows && 4 * q + g < cols)));
+  Blk<T> b;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) blk_set(b, q, masked(v[q], opaque_mask(r < rows && 4 * q + g < cols)));
+  return b;
+}
+template <typename T>
+__device__ __forceinline__ void blk_store(const Blk<T> &b, T *Q, int64_t ld, int rows, int cols) {
+  const int r = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (r < rows && 4 * q + g < cols) gstore(Q + (4 * q + g) * ld + r, blk_get(b, q));
+}
+
+// Rows 4 v + l / 16 of a transposed block times dl[4 v + l / 16] (plane p at dl[16 p]).
+template <typename T> __device__ __forceinline__ Blk<T> blk_scale_rows(const Blk<T> &b, const double *dl) {
+  const int g = (threadIdx.x & 63) >> 4;
+  Blk<T> o;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) blk_set(o, v, blk_get(b, v) * Planes<T>::from(dl + 4 * v + g, 16));
+  return o;
+}
+// The operand -L(j, k) (conjugated if Hermitian) of the updates.
+template <typename T> __device__ __forceinline__ Blk<T> blk_neg_cj(const Blk<T> &b, double cs) {
+  Blk<T> o;
+  o.p[0] = -b.p[0];
+  if constexpr (Planes<T>::P == 2) o.p[1] = -cs * b.p[1];
+  return o;
+}
+
+__device__ __forceinline__ double readlane_t(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int32_t)(uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ cplx readlane_t(cplx v, int lane) {
+  return cplx{readlane_t(v.re, lane), readlane_t(v.im, lane)};
+}
+
+// 1 / d.  The pivots' reciprocals are one serial chain per node, so the usual
+// range takes the hardware estimate and two Newton steps (r += r (1 - d r),
+// each doubling the correct bits) instead of a full division.
+__device__ __forceinline__ double pivot_recip(double d) {
+  const double m = fabs(d);
+  if (m > 0x1p-500 && m < 0x1p500) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return r;
+  }
+  return 1.0 / d;
+}
+__device__ __forceinline__ cplx pivot_recip(cplx d) {
+  const double m = fmax(fabs(d.re), fabs(d.im));
+  if (m > 0x1p-240 && m < 0x1p240) {
+    const double r = pivot_recip(fma(d.re, d.re, d.im * d.im));
+    return cplx{d.re * r, -d.im * r};
+  }
+  return cdiv(cplx{1.0, 0.0}, d);
+}
+
+// Component-wise select (a select of whole complex values goes through memory).
+__device__ __forceinline__ double pick(bool c, double a, double b) { return c ? a : b; }
+__device__ __forceinline__ cplx pick(bool c, cplx a, cplx b) { return cplx{c ? a.re : b.re, c ? a.im : b.im}; }
+
+// x[q] -= w_q y for the lanes of ldl16; ys carries the sign of conj(w_q) on the lanes of S.
+__device__ __forceinline__ void ldl_step(double &x, double w, double y, double) { x = fma(-w, y, x); }
+__device__ __forceinline__ void ldl_step(cplx &x, cplx w, cplx y, cplx ys) {
+  x.re = fma(w.im, ys.im, fma(-w.re, y.re, x.re));
+  x.im = fma(-w.im, ys.re, fma(-w.re, y.im, x.im));
+}
+__device__ __forceinline__ double scale_t(double s, double a) { return a; }
+__device__ __forceinline__ cplx scale_t(double s, cplx a) { return cplx{s * a.re, s * a.im}; }
+
+// Unpivoted LDL^T (LDL^H) of one 16 x 16 diagonal block and the inverse of
+// its L, by one wavefront: lane r < 16 holds row r of S (lower part) in x, lane
+// 16 + q column q of the identity.  Step j needs the same update on both:
+// row r:  S(r, q) -= L(r, j) W(q, j),  column q:  M(p, q) -= L(p, j) M(j, q),
+// i.e. x[q] -= w_q (x[j] / d_j) with w_q = S(q, j) read from lane q.  Only the
+// first w columns are eliminated.  On return row r holds L(r, 0 .. r - 1) and
+// D_r, column q holds M(:, q); 1 / D_j goes to dl[j] (1 beyond w).  A zero or
+// non-finite pivot is recorded (column first + j).
+// The whole step is latency of a serial chain (16 reciprocals, 120 dependent
+// broadcast-and-update steps); on the vector unit with lane broadcasts it runs
+// without LDS or barriers.
+template <typename T>
+__device__ __forceinline__ void ldl16(T (&x)[16], int w, double cs, double *dl, int64_t first,
+                                      unsigned long long *ferr) {
+  const int lane = threadIdx.x & 63;
+  const double sg = lane < 16 ? cs : 1.0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    T di = SOps<T>::one();
+    if (j < w) {
+      const T d = readlane_t(x[j], j);
+      if (!finite_nonzero(d) && lane == 0) atomicMin(ferr, (unsigned long long)(first + j));
+      di = pivot_recip(d);
+      const T y = x[j] * di, ys = scale_t(sg, y);
+#pragma unroll
+      for (int q = j + 1; q < 16; ++q) ldl_step(x[q], readlane_t(x[j], q), y, ys);
+      x[j] = pick(lane < 16 && lane > j, y, x[j]);
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int p = 0; p < Planes<T>::P; ++p) dl[16 * p + j] = Planes<T>::get(di, p);
+    }
+  }
+}
+
+// LDS ordering inside one wavefront.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// M from the lanes of ldl16 into LDS in the operand layout (element 16 q + p
+// = M(p, q)), the conjugate if Hermitian.
+template <typename T> __device__ __forceinline__ void ldl16_put_m(const T (&x)[16], double cs, double *ms, int stride) {
+  const int lane = threadIdx.x & 63;
+  if (lane >= 16 && lane < 32) {
+#pragma unroll
+    for (int p = 0; p < 16; ++p) {
+      const T v = cj(x[p], cs);
+#pragma unroll
+      for (int pl = 0; pl < Planes<T>::P; ++pl) ms[pl * stride + 16 * (lane - 16) + p] = Planes<T>::get(v, pl);
+    }
+  }
+}
+// L and D of the block into the panel (lower triangle only).
+template <typename T> __device__ __forceinline__ void ldl16_store(const T (&x)[16], T *Q, int64_t ld, int w) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int k = 0; k < 16; ++k)
+    if (lane < w && k <= lane) gstore(Q + k * ld + lane, x[k]);
+}
+
+// ---------------------------------------------------------------------------
+// Whole nodes with s <= 16 and c <= 16 NST in one wavefront: the diagonal
+// block, L_{C,K} one 16-row strip at a time, and every 16 x 16 block of the
+// update of S_{C,C} from registers.  These nodes are most of the tree and
+// have almost no arithmetic: what bounds them is the launches and the
+// dependent rounds of loads (record -> panel and row tables -> positions), so
+// one launch does everything and a CU holds many nodes at once (four launches
+// on 64 x 64 tiles before; 31 x 31 FP64 grid: 0.27 -> 0.09 ms for its ten depths;
+// 16 Hermitian 30^3 matrices, the lower 13 depths: 10.5 -> 3.0 ms).
+// ---------------------------------------------------------------------------
+template <typename T, int NST>
+__global__ void __launch_bounds__(64) k_fac_small(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs,
+                                                  int32_t count, unsigned long long *ferr) {
+  constexpr int P = Planes<T>::P;
+  const DevPlan &pl = *plp;
+  __shared__ double ms[P * 256], dl[P * 16];
+  __shared__ int64_t rcol[16 * NST], rpos[16 * NST];
+  const int64_t gidx = blockIdx.x;
+  const int64_t l = gidx / count;
+  const FacNode nd = recs[gidx - l * count];
+  const int s = uniform(nd.s), c = uniform(nd.c), ld = s + c;
+  T *Pl = Pall + l * pl.panel_elems;
+  T *Q = Pl + nd.off;
+  const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
+  const double cs = pl.csign;
+  T x[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) x[k] = gload(Q + (((int64_t)k * ld + lane) & opaque_mask(lane < s && k <= lane)));
+  Blk<T> sb[NST];
+#pragma unroll
+  for (int i = 0; i < NST; ++i)
+    if (16 * i < c) sb[i] = blk_load<T>(Q + s + 16 * i, ld, c - 16 * i, s);
+#pragma unroll
+  for (int u = 0; u < (16 * NST + 63) / 64; ++u) {
+    const int k = lane + 64 * u;
+    if (k < c) {
+      rcol[k] = gp(pl.kcol)[nd.rp + k];
+      rpos[k] = gp(pl.kpos)[nd.rp + k];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const T id = pick(lane - 16 == k, SOps<T>::one(), zero_of<T>());
+    x[k] = pick(lane < s && k <= lane, x[k], id);
+  }
+  ldl16<T>(x, s, cs, dl, nd.first, ferr + l);
+  ldl16_put_m<T>(x, cs, ms, 256);
+  ldl16_store<T>(x, Q, ld, s);
+  wave_lds_fence();
+  const int nv = (s + 3) / 4;
+  const Blk<T> m = blk_from_lds<T>(ms, 256);
+  Blk<T> wb[NST];
+#pragma unroll
+  for (int i = 0; i < NST; ++i) {
+    if (16 * i >= c) break;
+    wb[i] = blk_zero<T>();
+    blk_mma<T>(m, sb[i], wb[i], nv);
+    sb[i] = blk_scale_rows<T>(wb[i], dl);
+    blk_store<T>(sb[i], Q + s + 16 * i, ld, c - 16 * i, s);
+  }
+#pragma unroll
+  for (int j = 0; j < NST; ++j) {
+    if (16 * j >= c) break;
+    const Blk<T> lj = blk_neg_cj<T>(sb[j], cs);
+    int64_t col[4];
+    int32_t pos[NST][4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int kg = min(16 * j + 4 * v + g, c - 1);
+      col[v] = rcol[kg];
+      const int64_t rp = rpos[kg];
+#pragma unroll
+      for (int i = j; i < NST; ++i)
+        if (16 * i < c) {
+          const int ig = 16 * i + r;
+          pos[i][v] = gp(pl.posarr)[(rp + ig) & opaque_mask(ig < c && ig >= kg)];
+        }
+    }
+#pragma unroll
+    for (int i = j; i < NST; ++i) {
+      if (16 * i >= c) break;
+      Blk<T> u = blk_zero<T>();
+      blk_mma<T>(lj, wb[i], u, nv);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int ig = 16 * i + r, kg = 16 * j + 4 * v + g;
+        if (ig < c && kg <= ig) atomic_add_t(Pl + col[v] + pos[i][v], blk_get(u, v));
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Unpivoted LDL^T of a diagonal block of at most kFacCols = 128 columns (a
+// whole node's, or one column block of a wider node), one workgroup of eight
+// wavefronts.  The lower 16 x 16 blocks stay in registers: wavefront i owns
+// diagonal block i and up to four of the others.  Step k: the owner of
+// block (k, k) factors and inverts it (ldl16); the blocks below become W^T =
+// M S^T and L^T = D^{-1} W^T and go to LDS; every block right of the panel
+// takes its rank-16 update.  The next diagonal block is updated and factored
+// before its owner's other blocks.  What bounds it is the serial chain of the
+// ldl16 steps: 34 us a launch on average on the 40^3 FP64 Laplacian (19.9 ms of
+// diagonal blocks a factorization -> 1.35 ms) and 75 us on 16 Hermitian 30^3
+// matrices (15.9 -> 1.7 ms); the form before updated the block in global memory, one
+// thread an element, 1.3 ms (FP64) and 1.7 ms (complex) for 256 columns.
+// The inverses M_k (operand layout) and 1 / D go to `fin` for k_fac_lc.
+// ---------------------------------------------------------------------------
+constexpr int kFacWaves = kFacCols / 16;  // wavefronts, and 16-column blocks, of k_fac_diag
+constexpr int kFacOff = kFacWaves * (kFacWaves - 1) / 2;
+constexpr int kFacSlots = (kFacOff + kFacWaves - 1) / kFacWaves;
+
+template <typename T>
+__global__ void __launch_bounds__(64 * kFacWaves, 2)
+    k_fac_diag(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs, int32_t count, unsigned long long *ferr) {
+  constexpr int P = Planes<T>::P, NB = kFacWaves, LP = NB * 256;  // LP: doubles of one plane of a panel
+  const DevPlan &pl = *plp;
+  __shared__ double lp[P * LP], wp[P * LP];  // -L(i, k) (conjugated if Hermitian) and W(i, k), block i at 256 i
+  __shared__ double ms[P * 256], tr[P * 16 * 17], dl[P * 16];
+  const int64_t gidx = blockIdx.x;
+  const int64_t l = gidx / count;
+  const FacNode nd = recs[gidx - l * count];
+  const int s = uniform(nd.s), ld = uniform(nd.ld), nb = (s + 15) / 16;
+  T *Q = Pall + l * pl.panel_elems + nd.off;
+  T *F = reinterpret_cast<T *>(pl.finv) + l * pl.fin_elems + nd.fin;
+  const int wv = uniform((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const double cs = pl.csign;
+  int bi[kFacSlots], bj[kFacSlots];  // the wavefront's other blocks, listed column by column
+#pragma unroll
+  for (int q = 0; q < kFacSlots; ++q) {
+    int e = wv + NB * q, j = 0;
+    while (j < NB - 1 && e >= NB - 1 - j) e -= NB - 1 - j, ++j;
+    const bool in = j < NB - 1 && j + 1 + e < nb;
+    bi[q] = uniform(in ? j + 1 + e : -1);
+    bj[q] = uniform(in ? j : -1);
+  }
+  Blk<T> dg = blk_zero<T>(), ob[kFacSlots];
+  if (wv < nb) dg = blk_load<T>(Q + (int64_t)(16 * wv) * ld + 16 * wv, ld, s - 16 * wv, s - 16 * wv);
+#pragma unroll
+  for (int q = 0; q < kFacSlots; ++q)
+    if (bi[q] >= 0) ob[q] = blk_load<T>(Q + (int64_t)(16 * bj[q]) * ld + 16 * bi[q], ld, s - 16 * bi[q], 16);
+  for (int k = 0; k < nb; ++k) {
+    if (k > 0) {  // panel k - 1
+      lds_barrier();
+      const int kk = k - 1;
+#pragma unroll
+      for (int q = 0; q < kFacSlots; ++q)
+        if (bj[q] == kk) {
+          Blk<T> w = blk_zero<T>();
+          blk_mma<T>(blk_from_lds<T>(ms, 256), ob[q], w);
+          const Blk<T> lo = blk_scale_rows<T>(w, dl);
+          blk_to_lds<T>(w, wp + 256 * bi[q], LP);
+          blk_to_lds<T>(blk_neg_cj<T>(lo, cs), lp + 256 * bi[q], LP);
+          blk_store<T>(lo, Q + (int64_t)(16 * kk) * ld + 16 * bi[q], ld, s - 16 * bi[q], 16);
+        }
+      lds_barrier();
+      if (wv >= k && wv < nb)
+        blk_mma<T>(blk_from_lds<T>(lp + 256 * wv, LP), blk_from_lds<T>(wp + 256 * wv, LP), dg);
+    }
+    if (wv == k) {
+      const int w = min(16, s - 16 * k);
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tr[p * 272 + r * 17 + 4 * v + g] = dg.p[p][v];
+      wave_lds_fence();
+      T x[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        const T id = pick(lane - 16 == c, SOps<T>::one(), zero_of<T>());
+        x[c] = pick(lane < w && c <= lane, Planes<T>::from(&tr[r * 17 + c], 272), id);
+      }
+      ldl16<T>(x, w, cs, dl, nd.first + 16 * k, ferr + l);
+      ldl16_put_m<T>(x, cs, ms, 256);
+      ldl16_store<T>(x, Q + (int64_t)(16 * k) * ld + 16 * k, ld, w);
+      wave_lds_fence();
+      T *Fk = F + kFacFin * k;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) gstore(Fk + 64 * v + lane, Planes<T>::from(&ms[64 * v + lane], 256));
+      if (lane < 16) gstore(Fk + 256 + lane, Planes<T>::from(&dl[lane], 16));
+    }
+    if (k > 0) {
+#pragma unroll
+      for (int q = 0; q < kFacSlots; ++q)
+        if (bj[q] >= k) blk_mma<T>(blk_from_lds<T>(lp + 256 * bj[q], LP), blk_from_lds<T>(wp + 256 * bi[q], LP), ob[q]);
+    }
+  }
+}
+
+// The rows below a diagonal block of at most kFacCols columns, in place: L =
+// S L_KK^{-T} D^{-1} (L_KK^{-H} if Hermitian) by block forward substitution,
+// one wavefront per 16 rows with its up to eight 16 x 16 blocks in registers:
+//   W(:, k)^T = M_k S(:, k)^T, L(:, k)^T = D_k^{-1} W(:, k)^T,
+//   S(:, j)^T -= L(j, k) W(:, k)^T for j > k.
+// The four wavefronts of a workgroup share the step's operands (M_k and L(j,
+// k)) through LDS, two buffers deep: the loads of step k + 2 are in flight
+// while step k is multiplied.  No inverse of the whole L_KK is formed, and no
+// column waits for another workgroup.  Bound by the chain of eight steps where
+// few rows are left, else by MFMA: 40^3 FP64, inverse and product 2.4 ms a
+// factorization before, 0.6 ms now; 16 Hermitian 30^3 matrices 8.0 -> 1.6 ms.
+template <typename T>
+__global__ void __launch_bounds__(NT, 2)
+    k_fac_lc(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs, const int2 *rblocks, int32_t nrb) {
+  constexpr int P = Planes<T>::P, NB = kFacWaves, LP = NB * 256;
+  const DevPlan &pl = *plp;
+  __shared__ double buf[2][P * LP];  // M_k at 256 k, -L(j, k) at 256 j, j > k
+  __shared__ double dl[NB][P * 16];
+  const int64_t gidx = blockIdx.x;
+  const int64_t l = gidx / nrb;
+  const int2 rb = rblocks[gidx - l * nrb];
+  const FacNode nd = recs[uniform(rb.x)];
+  const int s = uniform(nd.s), c = uniform(nd.c), ld = uniform(nd.ld), nb = (s + 15) / 16;
+  T *Q = Pall + l * pl.panel_elems + nd.off;
+  const T *F = reinterpret_cast<const T *>(pl.finv) + l * pl.fin_elems + nd.fin;
+  const int wv = uniform((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const double cs = pl.csign;
+  const int i0 = uniform(rb.y) * 64 + 16 * wv;
+  T *R = Q + s + (i0 < c ? i0 : 0);  // the wavefront's 16 rows
+  const int rows = i0 < c ? c - i0 : 0;
+  Blk<T> sb[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k)
+    if (k < nb) sb[k] = blk_load<T>(R + (int64_t)(16 * k) * ld, ld, rows, s - 16 * k);
+  if (threadIdx.x < 16 * NB) {
+    const int k = threadIdx.x / 16;
+    const T d = gload(F + (k < nb ? kFacFin * k + 256 + r : 256));
+#pragma unroll
+    for (int p = 0; p < P; ++p) dl[k][16 * p + r] = Planes<T>::get(d, p);
+  }
+  // thread t of the workgroup: element t of every 256-element block of a step
+  T st[NB];
+  auto load = [&](int k) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (j == k) st[j] = gload(F + kFacFin * k + (int)threadIdx.x);
+      if (j > k && j < nb)
+        st[j] = gload(Q + (((int64_t)(16 * k + 4 * wv + g) * ld + 16 * j + r) & opaque_mask(16 * j + r < s)));
+    }
+  };
+  auto put = [&](int k) {
+    double *b = buf[k & 1];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (j < k || j >= nb) continue;
+      T v = st[j];
+      if (j > k) {
+        v = masked(v, opaque_mask(16 * j + r < s));
+        v = cj(SOps<T>::scale(-1.0, v), cs);
+      }
+#pragma unroll
+      for (int p = 0; p < P; ++p) b[p * LP + 256 * j + (int)threadIdx.x] = Planes<T>::get(v, p);
+    }
+  };
+  load(0);
+  put(0);
+  if (nb > 1) load(1);
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    if (k >= nb) break;
+    lds_barrier();
+    const double *b = buf[k & 1];
+    Blk<T> w = blk_zero<T>();
+    blk_mma<T>(blk_from_lds<T>(b + 256 * k, LP), sb[k], w);
+    if (k + 1 < nb) put(k + 1);
+    if (k + 2 < nb) load(k + 2);
+    blk_store<T>(blk_scale_rows<T>(w, dl[k]), R + (int64_t)(16 * k) * ld, ld, rows, s - 16 * k);
+#pragma unroll
+    for (int j = k + 1; j < NB; ++j)
+      if (j < nb) blk_mma<T>(blk_from_lds<T>(b + 256 * j, LP), w, sb[j]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Updates L D L^T on 64 x 64 tiles.
+// ---------------------------------------------------------------------------
+
+// A(i, k) = M[k ld + i0 + i] for i0 + i < rows, k < kend, with the branch-free
+// load and store forms of gemm_dense_il.
+template <typename T, int TK> struct FacLoadA : LoadDenseA<T, TK> {
+  using LoadDenseA<T, TK>::LoadDenseA;
+  static constexpr int E = LoadDenseA<T, TK>::E;
+  __device__ __forceinline__ void load_bf(int k0, DVals<T, TK> &v) const { this->load(k0, v); }
+  __device__ __forceinline__ void store_bf(double *stg, int plane_off, int k0, const DVals<T, TK> &v) const {
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      const T x = masked(v.v[m], this->mask(k0, m));
+#pragma unroll
+      for (int p = 0; p < Planes<T>::P; ++p) stg[(plane_off + p) * TK * PITCH + this->slot(k0, m)] = Planes<T>::get(x, p);
+    }
+  }
+};
+// B(k, x) = D_k M[k ld + i0 + x] (M conjugated if Hermitian): the pivots come
+// from LDS and multiply the loaded values where these go to LDS, so that the
+// loads stay in flight (a product at the load site waits for each of them).
+template <typename T, int TK> struct FacLoadB : FacLoadA<T, TK> {
+  const T *D;  // LDS
+  double cs;
+  __device__ __forceinline__ FacLoadB(const T *M, int ld, int rows, int kend, int x0, const T *D_, double cs_)
+      : FacLoadA<T, TK>(M, ld, rows, kend, x0), D(D_), cs(cs_) {}
+  __device__ __forceinline__ void store_bf(double *stg, int plane_off, int k0, const DVals<T, TK> &v) const {
+#pragma unroll
+    for (int m = 0; m < this->E; ++m) {
       const int k = min(k0 + this->kq + (NT / 64) * m, this->kend - 1);
-      v.v[m] = ld_off(this->M + (int64_t)k * this->ld, this->vcol) * gload(Dg + (int64_t)k * dld);
+      const T x = masked(cj(v.v[m], cs) * D[k], this->mask(k0, m));
+#pragma unroll
+      for (int p = 0; p < Planes<T>::P; ++p) stg[(plane_off + p) * TK * PITCH + this->slot(k0, m)] = Planes<T>::get(x, p);
     }
   }
 };
 
-constexpr int kFacBW = 32;             // column block of the diagonal factorization
-constexpr int kFacRows = 256 - kFacBW; // rows below a block inside a diagonal block (s <= 256)
-
-// Unpivoted LDL^T of the diagonal block S_KK of one node (one workgroup).
-// For each block of BW columns: the block's own LDL^T in LDS (column by
-// column, each step a rank-one update of the rest of the block), then the
-// rows of S_KK below the block by forward substitution (one row per
-// thread), then the trailing update of S_KK below the block.  Only the lower
-// triangle is read and written.
-template <typename T>
-__global__ void __launch_bounds__(NT) k_fac_diag(const DevPlan *__restrict__ plp, T *Pall, const int32_t *nodes,
-                                                 int32_t count, unsigned long long *ferr) {
-  constexpr int BW = kFacBW, BP = BW + 1;
-  const DevPlan &pl = *plp;
-  __shared__ T ajj[BW * BP];
-  __shared__ T lb[kFacRows * BW];
-  __shared__ T dv[BW];
-  const int64_t g = blockIdx.x;
-  const int64_t l = g / count;
-  const int K = uniform(nodes[g - l * count]);
-  const int s = uniform(gp(pl.node_s)[K]), c = uniform(gp(pl.node_c)[K]), ld = s + c;
-  T *P = Pall + l * pl.panel_elems + gp(pl.node_off)[K];
-  const int64_t first = gp(pl.node_first)[K];
-  const int t = threadIdx.x;
-  const double cs = pl.csign;  // LDL^H in a Hermitian plan: the right factor conjugated
-  for (int jb = 0; jb < s; jb += BW) {
-    const int w = min(BW, s - jb);
-    for (int e = t; e < BW * BW; e += NT) {
-      const int i = e % BW, k = e / BW;
-      if (i < w && k <= i) ajj[i * BP + k] = P[(int64_t)(jb + k) * ld + jb + i];
-    }
-    __syncthreads();
-    for (int j = 0; j < w; ++j) {
-      const T d = ajj[j * BP + j];
-      if (t == 0 && !finite_nonzero(d)) atomicMin(ferr + l, (unsigned long long)(first + jb + j));
-      if (t > j && t < w) ajj[t * BP + j] = SOps<T>::div(ajj[t * BP + j], d);
-      __syncthreads();
-      for (int e = t; e < BW * BW; e += NT) {
-        const int i = e % BW, k = e / BW;
-        if (k > j && k <= i && i < w) ajj[i * BP + k] -= ajj[i * BP + j] * d * cj(ajj[k * BP + j], cs);
-      }
-      __syncthreads();
-    }
-    for (int e = t; e < BW * BW; e += NT) {
-      const int i = e % BW, k = e / BW;
-      if (i < w && k <= i) P[(int64_t)(jb + k) * ld + jb + i] = ajj[i * BP + k];
-    }
-    if (t < w) dv[t] = ajj[t * BP + t];
-    __syncthreads();
-    // rows r = jb + w + rr of S_KK: L(r, jb + j) = (S(r, jb + j) - sum_{k<j} L(r, jb + k) D_k L(jb + j, jb + k)) / D_j
-    const int m = s - jb - w;
-    for (int rr = t; rr < m; rr += NT) {
-      const int r = jb + w + rr;
-      T a[BW];
-#pragma unroll
-      for (int j = 0; j < BW; ++j) a[j] = j < w ? P[(int64_t)(jb + j) * ld + r] : zero_of<T>();
-#pragma unroll
-      for (int j = 0; j < BW; ++j) {
-        if (j < w) {
-          T v = a[j];
-#pragma unroll
-          for (int k = 0; k < j; ++k) v -= a[k] * dv[k] * cj(ajj[j * BP + k], cs);
-          a[j] = SOps<T>::div(v, dv[j]);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < BW; ++j)
-        if (j < w) {
-          P[(int64_t)(jb + j) * ld + r] = a[j];
-          lb[rr * BW + j] = a[j];
-        }
-    }
-    __syncthreads();
-    // trailing update: S(r, q) -= sum_j L(r, j) D_j L(q, j), jb + w <= q <= r < s
-    const int npair = m * (m + 1) / 2;
-    for (int e = t; e < npair; e += NT) {
-      int rr = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
-      while (rr * (rr + 1) / 2 > e) --rr;
-      while ((rr + 1) * (rr + 2) / 2 <= e) ++rr;
-      const int qq = e - rr * (rr + 1) / 2;
-      T acc = zero_of<T>();
-      for (int j = 0; j < w; ++j) acc += lb[rr * BW + j] * dv[j] * cj(lb[qq * BW + j], cs);
-      P[(int64_t)(jb + w + qq) * ld + jb + w + rr] -= acc;
-    }
-    __syncthreads();
-  }
-}
-
-// L_{C,K} = S_{C,K} L_KK^{-T} D_K^{-1} (L_KK^{-H} if Hermitian) for one 64-row
-// block of C(K), in place.
-// Column tile x of the result needs columns k <= x of S_{C,K} only (L_KK^{-1}
-// is lower triangular), so tiles run right to left and each is stored after
-// its own product has read everything it needs.
-template <typename T>
-__global__ void __launch_bounds__(NT, Planes<T>::P == 1 ? 2 : 1)
-    k_fac_lc(const DevPlan *__restrict__ plp, T *Pall, const int2 *rblocks, int32_t nrb) {
+// Tile (a, b), a >= b, of the update L D L^T of the rows below a column block,
+// subtracted from
+//   INNER:  the node's own columns behind a column block of kFacCols (the rows
+//           and columns of the tile count from the block's end; columns
+//           >= kFacCols / no atomics, the tiles of a launch are disjoint);
+//   else:   the ancestors' entries of S_{C,C} (lower part: C-local rows i >= k)
+//           over all columns of the node, with atomic adds.
+// MFMA-bound on wide nodes, by the atomics on narrow ones.  Branch-free
+// interleaved stages and the 3M form at two workgroups a CU; 16 Hermitian 30^3
+// matrices: 12.7 ms of updates (nodes beyond the single-wavefront ones) -> 7.3 ms.
+template <typename T, bool INNER>
+__global__ void __launch_bounds__(NT, 2)
+    k_fac_update(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs, const int4 *tiles, int32_t ntiles) {
   const DevPlan &pl = *plp;
   constexpr int TK = DenseTK<T>::TK;
   constexpr int kStages = 2 * dense_stage_doubles<T, TK>();
   __shared__ double smem[kStages > tile_doubles<T>() ? kStages : tile_doubles<T>()];
-  const int64_t g = blockIdx.x;
-  const int64_t l = g / nrb;
-  const int2 rb = rblocks[g - l * nrb];
-  const int K = uniform(rb.x), i0 = uniform(rb.y) * 64;
-  const int s = uniform(gp(pl.node_s)[K]), c = uniform(gp(pl.node_c)[K]), ld = s + c;
-  T *P = Pall + l * pl.panel_elems + gp(pl.node_off)[K];
-  const T *Linv = reinterpret_cast<const T *>(pl.linv) + l * pl.sq_elems + gp(pl.node_sq)[K];
-  const T *dinv = reinterpret_cast<const T *>(pl.dinv) + l * pl.n + gp(pl.node_first)[K];
-  for (int x0 = uniform(((s - 1) / 64) * 64); x0 >= 0; x0 -= 64) {
-    const int kend = min(s, x0 + 64);
-    LoadDenseA<T, TK> la{P + s, ld, c, kend, i0};     // S_{C,K}(i, k)
-    LoadDenseBT<T, TK> lb{Linv, s, kend, x0, s};       // L_KK^{-1}(x, k), conjugated if Hermitian
-    lb.cs = pl.csign;
-    Acc<T> acc;
-    gemm_dense<T>(0, kend, la, lb, smem, acc);
-    acc_to_lds<T>(acc, smem);
-    lds_barrier();
-    for (int e = threadIdx.x; e < 64 * 64; e += NT) {
-      const int i = e & 63, x = e >> 6;
-      if (i0 + i < c && x0 + x < s)
-        P[(int64_t)(x0 + x) * ld + s + i0 + i] = lds_get<T>(smem, i, x) * gload(dinv + x0 + x);
-    }
-    __syncthreads();  // the next tile reads columns this one did not write; LDS reuse
-  }
-}
-
-// Block (a, b), a >= b, of the update L_{C,K} D_K L_{C,K}^T (^H if Hermitian), subtracted from
-// the ancestors' entries of S_{C,C} (lower part: C-local rows i >= k).
-template <typename T>
-__global__ void __launch_bounds__(NT, Planes<T>::P == 1 ? 2 : 1)
-    k_fac_schur(const DevPlan *__restrict__ plp, T *Pall, const int4 *tiles, int32_t ntiles) {
-  const DevPlan &pl = *plp;
-  constexpr int TK = DenseTK<T>::TK;
-  constexpr int kStages = 2 * dense_stage_doubles<T, TK>();
-  __shared__ double smem[kStages > tile_doubles<T>() ? kStages : tile_doubles<T>()];
-  const int64_t g = blockIdx.x;
-  const int64_t l = g / ntiles;
-  const int4 tl = tiles[g - l * ntiles];
-  const int K = uniform(tl.x), i0 = uniform(tl.y) * 64, k0 = uniform(tl.z) * 64;
-  const int s = uniform(gp(pl.node_s)[K]), c = uniform(gp(pl.node_c)[K]), ld = s + c;
+  __shared__ T dls[INNER ? kFacCols : 256];
+  const int64_t gidx = blockIdx.x;
+  const int64_t l = gidx / ntiles;
+  const int4 tl = tiles[gidx - l * ntiles];
+  const int i0 = uniform(tl.y) * 64, k0 = uniform(tl.z) * 64;
+  int s, c, ld, nc;  // contraction length, rows, leading dimension, columns of the target
   T *Pl = Pall + l * pl.panel_elems;
-  const int64_t off = gp(pl.node_off)[K], rp = gp(pl.node_rowptr)[K];
-  const T *P = Pl + off;
-  LoadDenseA<T, TK> la{P + s, ld, c, s, i0};                           // L_C(i, j)
-  LoadDenseBTScaled<T, TK> lb{P + s, ld, s, k0, c, P, (int64_t)ld + 1};  // D_j L_C(k, j) (conjugated if Hermitian)
-  lb.cs = pl.csign;
+  T *Q;
+  int64_t rp = 0;
+  if constexpr (INNER) {
+    const FacNode nd = recs[uniform(tl.x)];
+    s = uniform(nd.s);
+    c = uniform(nd.c);
+    ld = uniform(nd.ld);
+    nc = uniform(nd.rest);
+    Q = Pl + nd.off;
+  } else {
+    const int K = uniform(tl.x);
+    s = uniform(gp(pl.node_s)[K]);
+    c = uniform(gp(pl.node_c)[K]);
+    ld = s + c;
+    nc = c;
+    Q = Pl + gp(pl.node_off)[K];
+    rp = gp(pl.node_rowptr)[K];
+  }
+  for (int k = threadIdx.x; k < s; k += NT) dls[k] = gload(Q + (int64_t)k * (ld + 1));
+  lds_barrier();
+  FacLoadA<T, TK> la(Q + s, ld, c, s, i0);
+  FacLoadB<T, TK> lb(Q + s, ld, nc, s, k0, dls, pl.csign);
   Acc<T> acc;
-  gemm_dense<T>(0, s, la, lb, smem, acc);
+  gemm_dense_il<T, true>(0, s, la, lb, smem, acc);
   acc_to_lds<T>(acc, smem);
   lds_barrier();
-  for (int e = threadIdx.x; e < 64 * 64; e += NT) {
-    const int i = e & 63, k = e >> 6;
-    const int ig = i0 + i, kg = k0 + k;
-    if (ig < c && kg < c && ig >= kg) {
-      const int64_t addr = gp(pl.kcol)[rp + kg] + gp(pl.posarr)[gp(pl.kpos)[rp + kg] + ig];
-      atomic_sub(Pl + addr, lds_get<T>(smem, i, k));
+  const int i = threadIdx.x & 63, w = uniform((int)(threadIdx.x >> 6)), ig = i0 + i;
+  constexpr int QN = 64 * 64 / NT;
+  if constexpr (INNER) {
+    T *R = Q + (int64_t)s * (ld + 1);
+    T v[QN];
+#pragma unroll
+    for (int q = 0; q < QN; ++q) {
+      const int kg = k0 + w + 4 * q;
+      v[q] = gload(R + (((int64_t)kg * ld + ig) & opaque_mask(ig < c && kg < nc && ig >= kg)));
+    }
+#pragma unroll
+    for (int q = 0; q < QN; ++q) {
+      const int kg = k0 + w + 4 * q;
+      if (ig < c && kg < nc && ig >= kg) gstore(R + (int64_t)kg * ld + ig, v[q] - lds_get<T>(smem, i, w + 4 * q));
+    }
+  } else {
+    // the positions of all of a thread's elements first, then the adds
+    int32_t pos[QN];
+    int64_t col[QN];
+#pragma unroll
+    for (int q = 0; q < QN; ++q) {
+      const int kg = k0 + w + 4 * q, kc = min(kg, c - 1);
+      col[q] = uniform64(gp(pl.kcol)[rp + kc]);
+      pos[q] = gp(pl.posarr)[(gp(pl.kpos)[rp + kc] + ig) & opaque_mask(ig < c && kg < c && ig >= kg)];
+    }
+#pragma unroll
+    for (int q = 0; q < QN; ++q) {
+      const int kg = k0 + w + 4 * q;
+      if (ig < c && kg < c && ig >= kg)
+        atomic_add_t(Pl + col[q] + pos[q], SOps<T>::scale(-1.0, lds_get<T>(smem, i, w + 4 * q)));
     }
   }
 }
@@ -283,22 +708,26 @@ hipError_t factor_impl(const DevPlan &pl, const DevPlan *dpl, const FactorAux &f
   const unsigned B = (unsigned)pl.batch;
   for (int q = 0; q < fa.nlev; ++q) {
     const FacLevel &lv = fa.lev[q];
-    if (lv.nodes_n > 0)
-      hipLaunchKernelGGL(k_fac_diag<T>, dim3(lv.nodes_n * B), dim3(NT), 0, st, dpl, P, fa.nodes + lv.nodes_b,
-                         lv.nodes_n, pl.ferr);
-    if (lv.narrow_n > 0) {
-      e = launch_linv(pl, dpl, sizeof(T) == 16, panels, fa.chunks_narrow + lv.narrow_b, lv.narrow_n, true, st);
-      if (e != hipSuccess) return e;
+    if (lv.small4_n > 0)
+      hipLaunchKernelGGL((k_fac_small<T, 4>), dim3(lv.small4_n * B), dim3(64), 0, st, dpl, P, fa.nodes + lv.small4_b,
+                         lv.small4_n, pl.ferr);
+    if (lv.small8_n > 0)
+      hipLaunchKernelGGL((k_fac_small<T, 8>), dim3(lv.small8_n * B), dim3(64), 0, st, dpl, P, fa.nodes + lv.small8_b,
+                         lv.small8_n, pl.ferr);
+    for (int h = 0; h < 2; ++h) {  // column block h of the nodes
+      if (lv.diag_n[h] > 0)
+        hipLaunchKernelGGL(k_fac_diag<T>, dim3(lv.diag_n[h] * B), dim3(64 * kFacWaves), 0, st, dpl, P,
+                           fa.nodes + lv.diag_b[h], lv.diag_n[h], pl.ferr);
+      if (lv.rb_n[h] > 0)
+        hipLaunchKernelGGL(k_fac_lc<T>, dim3(lv.rb_n[h] * B), dim3(NT), 0, st, dpl, P, fa.nodes,
+                           fa.rblocks + lv.rb_b[h], lv.rb_n[h]);
+      if (h == 0 && lv.inner_n > 0)
+        hipLaunchKernelGGL((k_fac_update<T, true>), dim3(lv.inner_n * B), dim3(NT), 0, st, dpl, P, fa.nodes,
+                           fa.tiles + lv.inner_b, lv.inner_n);
     }
-    if (lv.wide_n > 0) {
-      e = launch_linv(pl, dpl, sizeof(T) == 16, panels, fa.chunks_wide + lv.wide_b, lv.wide_n, false, st);
-      if (e != hipSuccess) return e;
-    }
-    if (lv.rb_n > 0)
-      hipLaunchKernelGGL(k_fac_lc<T>, dim3(lv.rb_n * B), dim3(NT), 0, st, dpl, P, fa.rblocks + lv.rb_b, lv.rb_n);
     if (lv.tiles_n > 0)
-      hipLaunchKernelGGL(k_fac_schur<T>, dim3(lv.tiles_n * B), dim3(NT), 0, st, dpl, P, fa.tiles + lv.tiles_b,
-                         lv.tiles_n);
+      hipLaunchKernelGGL((k_fac_update<T, false>), dim3(lv.tiles_n * B), dim3(NT), 0, st, dpl, P, fa.nodes,
+                         fa.tiles + lv.tiles_b, lv.tiles_n);
   }
   hipLaunchKernelGGL(k_fac_logdet<T>, dim3(B), dim3(NT), 0, st, dpl, P, pl.fldet);
   return hipGetLastError();

@@ -957,28 +957,6 @@ static hipError_t normalize_impl(const DevPlan &pl, const DevPlan *dpl, const La
   return hipGetLastError();
 }
 
-// L_KK^{-1} and D_K^{-1} of the nodes of a chunk list (the device factorization).
-hipError_t launch_linv(const DevPlan &pl, const DevPlan *dpl, bool cplx_, const void *src, const int2 *chunks,
-                       int32_t n, bool narrow, hipStream_t st) {
-  const dim3 grid((unsigned)(n * pl.batch));
-  if (cplx_) {
-    if (narrow)
-      hipLaunchKernelGGL((k_normalize_inv<cplx, 64>), grid, dim3(NT), 0, st, dpl, reinterpret_cast<const cplx *>(src),
-                         chunks, n, 1);
-    else
-      hipLaunchKernelGGL((k_normalize_inv<cplx, 256>), grid, dim3(NT), 0, st, dpl, reinterpret_cast<const cplx *>(src),
-                         chunks, n, 1);
-  } else {
-    if (narrow)
-      hipLaunchKernelGGL((k_normalize_inv<double, 64>), grid, dim3(NT), 0, st, dpl,
-                         reinterpret_cast<const double *>(src), chunks, n, 1);
-    else
-      hipLaunchKernelGGL((k_normalize_inv<double, 256>), grid, dim3(NT), 0, st, dpl,
-                         reinterpret_cast<const double *>(src), chunks, n, 1);
-  }
-  return hipGetLastError();
-}
-
 hipError_t launch_normalize(const DevPlan &pl, const DevPlan *dpl, const LaunchAux &aux, bool cplx_, const void *src,
                             void *panels, void *dt, hipStream_t st, int part, int steps) {
   return cplx_ ? normalize_impl<cplx>(pl, dpl, aux, src, panels, dt, st, part, steps)

@@ -165,6 +165,8 @@ struct DevPlan {
   int64_t *dpos;       // [n] panel element of each pivot D_jj (one matrix)
   unsigned long long *ferr;  // [batch] device factorization: first column with a bad pivot (~0: none)
   double *fldet;       // [batch][2] device factorization: log det (re, im)
+  void *finv;          // [batch][fin_elems] device factorization: inverses of one depth's 16 x 16 diagonal blocks
+  int64_t fin_elems;
   int32_t *ctrl;       // CTRL_WORDS
   int64_t *trace;      // optional: per ticket {item id, workgroup, t_ticket, t_start, t_end, 0, 0, 0}
 };
@@ -224,19 +226,33 @@ struct LaunchAux {
   const int32_t *lvl_cut, *norm_cut;
 };
 
+// A column block of the device factorization (see factor.hip): a whole node,
+// or columns [128 h, 128 h + s) of a wider one.
+constexpr int kFacCols = 128;  // widest column block
+constexpr int kFacFin = 272;   // scratch scalars per 16 columns: the 16 x 16 inverse of L_kk, then 1 / D
+struct alignas(16) FacNode {
+  int64_t off;    // panel offset of the block's first diagonal element
+  int64_t rp;     // first row of C(K) in the row tables
+  int64_t fin;    // first scratch scalar (see kFacFin)
+  int64_t first;  // column of B
+  int32_t ld, s, c, rest;  // leading dimension, columns, rows below them (all of the node's), of which
+                           // the first `rest` are columns of the node too
+};
+
 // Launches of the device factorization, one entry per etree depth (deepest
 // first): ranges of the lists in FactorAux.
 struct FacLevel {
-  int32_t nodes_b, nodes_n;    // nodes of the depth (diagonal-block factorization)
-  int32_t narrow_b, narrow_n;  // 16-column blocks of L_KK^{-1}, s <= 64
-  int32_t wide_b, wide_n;      // the same, s > 64
-  int32_t rb_b, rb_n;          // 64-row blocks of C(K) (L_{C,K})
-  int32_t tiles_b, tiles_n;    // lower 64 x 64 block pairs of C(K) x C(K) (Schur update)
+  int32_t small4_b, small4_n;      // nodes with s <= 16 and c <= 64, one wavefront each
+  int32_t small8_b, small8_n;      // the same with 64 < c <= 128
+  int32_t diag_b[2], diag_n[2];    // column block h of the other nodes (diagonal block)
+  int32_t rb_b[2], rb_n[2];        // 64-row blocks below it
+  int32_t inner_b, inner_n;        // tiles of the second column blocks updated by the first
+  int32_t tiles_b, tiles_n;        // lower 64 x 64 block pairs of C(K) x C(K) (Schur update)
 };
 struct FactorAux {
-  const int32_t *nodes;        // device lists
-  const int2 *chunks_narrow, *chunks_wide, *rblocks;
-  const int4 *tiles;
+  const FacNode *nodes;        // device lists
+  const int2 *rblocks;         // {FacNode, 64-row block}
+  const int4 *tiles;           // {node K, a, b, 0}; inner tiles {FacNode, a, b, 0}
   const FacLevel *lev;         // host array
   int32_t nlev;
 };
