@@ -930,7 +930,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   {
     std::vector<std::vector<int64_t>> bydepth(S.depth);
     for (int64_t K = 0; K < ns; ++K) bydepth[S.sdepth[K]].push_back(K);
-    // one wavefront holds a node's 16 columns and up to eight 16-row strips in registers
+    // whole-node kernels: one block of columns, and strips that fit the registers (one wavefront) or LDS (four)
     auto is_small = [&](int64_t K, int64_t cmax) { return H.node_s[K] <= 16 && H.node_c[K] <= cmax; };
     auto rec = [&](int64_t K, int32_t h) {
       const int32_t s = H.node_s[K], c = H.node_c[K], ld = s + c, j0 = kFacCols * h;
@@ -947,21 +947,21 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
     };
     for (int64_t d = S.depth - 1; d >= 0; --d) {
       FacLevel lv{};
-      lv.small4_b = (int32_t)H.fac_nodes.size();
+      lv.small_b = (int32_t)H.fac_nodes.size();
       for (int64_t K : bydepth[d])
-        if (is_small(K, 64)) H.fac_nodes.push_back(rec(K, 0));
-      lv.small8_b = (int32_t)H.fac_nodes.size();
-      lv.small4_n = lv.small8_b - lv.small4_b;
+        if (is_small(K, kFacSmallC)) H.fac_nodes.push_back(rec(K, 0));
+      lv.mid_b = (int32_t)H.fac_nodes.size();
+      lv.small_n = lv.mid_b - lv.small_b;
       for (int64_t K : bydepth[d])
-        if (is_small(K, 128) && !is_small(K, 64)) H.fac_nodes.push_back(rec(K, 0));
-      lv.small8_n = (int32_t)H.fac_nodes.size() - lv.small8_b;
+        if (is_small(K, kFacMidC) && !is_small(K, kFacSmallC)) H.fac_nodes.push_back(rec(K, 0));
+      lv.mid_n = (int32_t)H.fac_nodes.size() - lv.mid_b;
       int64_t fin = 0;  // the scratch is used within one depth
       for (int32_t h = 0; h < 2; ++h) {
         lv.diag_b[h] = (int32_t)H.fac_nodes.size();
         lv.rb_b[h] = (int32_t)H.fac_rb.size();
         if (h == 0) lv.inner_b = (int32_t)H.fac_tiles.size();
         for (int64_t K : bydepth[d]) {
-          if (is_small(K, 128) || H.node_s[K] <= kFacCols * h) continue;
+          if (is_small(K, kFacMidC) || H.node_s[K] <= kFacCols * h) continue;
           FacNode n = rec(K, h);
           n.fin = fin;
           fin += (int64_t)kFacFin * ((n.s + 15) / 16);
@@ -978,7 +978,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
       H.fin_elems = std::max(H.fin_elems, fin);
       lv.tiles_b = (int32_t)H.fac_tiles.size();
       for (int64_t K : bydepth[d]) {
-        if (is_small(K, 128)) continue;
+        if (is_small(K, kFacMidC)) continue;
         const int32_t nr = (H.node_c[K] + kTileM - 1) / kTileM;
         for (int32_t a = 0; a < nr; ++a)
           for (int32_t b = 0; b <= a; ++b) H.fac_tiles.push_back(int4{(int32_t)K, a, b, 0});
@@ -1061,7 +1061,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   o.adj_f = take(sqb);
   o.adj_d = take(sqb);
   o.ferr = take(8 * batch);
-  o.fldet = take(16 * batch);
+  o.fldet = take(16 * batch * ldet_parts(S.n));
   o.finv = take(H.lu ? 0 : scalar_bytes * batch * H.fin_elems);
   o.end = p;
 }
@@ -2226,14 +2226,24 @@ selinv_status selinv_sync(selinv_ctx *h, void *stream) {
   if (h->devfac_work) {  // pivots and log det of the last device factorization
     const int64_t B = h->opts.batch;
     const unsigned char *b = static_cast<const unsigned char *>(h->devfac_work);
-    std::vector<unsigned long long> ferr((size_t)B);
-    std::vector<double> ld((size_t)(2 * B));
+    std::vector<unsigned long long> ferr;
+    const int64_t parts = ldet_parts(h->S.n);
+    std::vector<double> part, ld;
+    try {
+      ferr.resize((size_t)B);
+      part.resize((size_t)(2 * B * parts));
+      ld.resize((size_t)(2 * B), 0.0);
+    } catch (const std::bad_alloc &) {
+      return set_err(h, SELINV_ENOMEM, "host allocation failed in sync");
+    }
     e = hipMemcpy(ferr.data(), b + h->H.off.ferr, sizeof(unsigned long long) * B, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(ld.data(), b + h->H.off.fldet, sizeof(double) * 2 * B, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(part.data(), b + h->H.off.fldet, sizeof(double) * part.size(), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_err(h, e, "factor status readback");
     h->devfac_work = nullptr;
     for (int64_t l = 0; l < B; ++l)
       if (ferr[l] != ~0ull) return set_err(h, SELINV_ESINGULAR, "zero or non-finite pivot", (int64_t)ferr[l], l);
+    for (int64_t q = 0; q < B * parts; ++q)  // a fixed order
+      for (int p = 0; p < 2; ++p) ld[2 * (q / parts) + p] += part[2 * q + p];
     h->logdet = ld;
     h->have_logdet = true;
   }

@@ -9,8 +9,8 @@
 // Right-looking supernodal form, etree depth by depth, the deepest first
 // (every descendant of K is complete before K starts):
 //
-//   small  a whole node with s <= 16 and c <= 128 in one wavefront (the lower
-//          depths hold little else)
+//   small  a whole node with s <= 16 and c <= 64 in one wavefront, or c <= 128 in
+//          four (the lower depths hold little else)
 //   diag   S_KK = L_KK D_K L_KK^T of a block of at most kFacCols columns, its
 //          16 x 16 blocks in the registers of one workgroup
 //   lc     the rows below that block, by block forward substitution with the
@@ -29,6 +29,8 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
+#include <utility>
 
 #include "items.hpp"
 #include "plan.hpp"
@@ -118,34 +120,49 @@ template <typename T> __device__ __forceinline__ void blk_to_lds(const Blk<T> &b
     for (int v = 0; v < 4; ++v) q[p * stride + v * 64 + lane] = b.p[p][v];
 }
 
-// Rows [0, rows) and columns [0, cols) of a 16 x 16 block at Q (leading
-// dimension ld); zeros outside (read from Q's first element).
+__device__ __forceinline__ void st_off(double *base, uint32_t b, double v) {
+  *reinterpret_cast<SELINV_GAS double *>(reinterpret_cast<SELINV_GAS char *>(gw(base)) + b) = v;
+}
+__device__ __forceinline__ void st_off(cplx *base, uint32_t b, cplx v) {
+  SELINV_GAS char *q = reinterpret_cast<SELINV_GAS char *>(gw(base)) + b;
+  *reinterpret_cast<SELINV_GAS double *>(q) = v.re;
+  *reinterpret_cast<SELINV_GAS double *>(q + 8) = v.im;
+}
+// This lane's row of a block, opaque: the addresses below are cheap to form
+// and cost registers when kept from a block's load to its store.
+__device__ __forceinline__ int blk_row() {
+  int r = threadIdx.x & 15;
+  asm("" : "+v"(r));
+  return r;
+}
+// Rows [0, rows) and columns [0, cols) of a 16 x 16 block at Q (wave-uniform,
+// leading dimension ld); zeros outside (read from Q's first element).
 template <typename T>
-__device__ __forceinline__ Blk<T> blk_load(const T *Q, int64_t ld, int rows, int cols) {
-  const int r = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+__device__ __forceinline__ Blk<T> blk_load(const T *Q, int ld, int rows, int cols) {
+  const int r = blk_row(), g = (threadIdx.x & 63) >> 4;
   T v[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
-    v[q] = gload(Q + (((4 * q + g) * ld + r) & opaque_mask(r < rows && 4 * q + g < cols)));
+    v[q] = ld_off(Q, ((uint32_t)((4 * q + g) * ld + r) & opaque_mask32(r < rows && 4 * q + g < cols)) * (uint32_t)sizeof(T));
   Blk<T> b;
 #pragma unroll
   for (int q = 0; q < 4; ++q) blk_set(b, q, masked(v[q], opaque_mask(r < rows && 4 * q + g < cols)));
   return b;
 }
 template <typename T>
-__device__ __forceinline__ void blk_store(const Blk<T> &b, T *Q, int64_t ld, int rows, int cols) {
-  const int r = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+__device__ __forceinline__ void blk_store(const Blk<T> &b, T *Q, int ld, int rows, int cols) {
+  const int r = blk_row(), g = (threadIdx.x & 63) >> 4;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
-    if (r < rows && 4 * q + g < cols) gstore(Q + (4 * q + g) * ld + r, blk_get(b, q));
+    if (r < rows && 4 * q + g < cols) st_off(Q, (uint32_t)((4 * q + g) * ld + r) * (uint32_t)sizeof(T), blk_get(b, q));
 }
 
-// Rows 4 v + l / 16 of a transposed block times dl[4 v + l / 16] (plane p at dl[16 p]).
-template <typename T> __device__ __forceinline__ Blk<T> blk_scale_rows(const Blk<T> &b, const double *dl) {
+// Rows 4 v + l / 16 of a transposed block times dl[4 v + l / 16] (planes `stride` apart).
+template <typename T> __device__ __forceinline__ Blk<T> blk_scale_rows(const Blk<T> &b, const double *dl, int stride) {
   const int g = (threadIdx.x & 63) >> 4;
   Blk<T> o;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) blk_set(o, v, blk_get(b, v) * Planes<T>::from(dl + 4 * v + g, 16));
+  for (int v = 0; v < 4; ++v) blk_set(o, v, blk_get(b, v) * Planes<T>::from(dl + 4 * v + g, stride));
   return o;
 }
 // The operand -L(j, k) (conjugated if Hermitian) of the updates.
@@ -156,85 +173,75 @@ template <typename T> __device__ __forceinline__ Blk<T> blk_neg_cj(const Blk<T> 
   return o;
 }
 
-__device__ __forceinline__ double readlane_t(double v, int lane) {
+template <class F, int... I> __device__ __forceinline__ void static_for(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+// Lane broadcasts inside a row of 16 lanes (row_newbcast, the one DPP form of
+// 64-bit operations): acc += w[lane L of the row] y in one instruction.  The
+// compiler does not look into these for hazards: a DPP read needs two wait
+// states after its source was written, which bcast16 supplies and fmac16
+// gets by following a bcast16 of the same source.
+template <int L> __device__ __forceinline__ double bcast16(double w) {
+  double r;
+  asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(w), "n"(L));
+  return r;
+}
+template <int L> __device__ __forceinline__ cplx bcast16(cplx w) { return cplx{bcast16<L>(w.re), bcast16<L>(w.im)}; }
+template <int L> __device__ __forceinline__ void fmac16(double &acc, double w, double y) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(w), "v"(y), "n"(L));
+}
+
+// Lanes 0 .. 15 of v on lanes 0 .. 15 and 16 .. 31 (and 32 .. 47 on the rest).
+__device__ __forceinline__ double even_row(double v) {
+  asm("s_nop 1" : "+v"(v));  // v may come from an fmac16
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane((int32_t)(uint32_t)u, lane);
-  const uint32_t hi = __builtin_amdgcn_readlane((int32_t)(u >> 32), lane);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return __builtin_bit_cast(double, ((uint64_t)b[0] << 32) | a[0]);
 }
-__device__ __forceinline__ cplx readlane_t(cplx v, int lane) {
-  return cplx{readlane_t(v.re, lane), readlane_t(v.im, lane)};
-}
+__device__ __forceinline__ cplx even_row(cplx v) { return cplx{even_row(v.re), even_row(v.im)}; }
 
 // 1 / d.  The pivots' reciprocals are one serial chain per node, so the usual
 // range takes the hardware estimate and two Newton steps (r += r (1 - d r),
-// each doubling the correct bits) instead of a full division.
-__device__ __forceinline__ double pivot_recip(double d) {
-  const double m = fabs(d);
-  if (m > 0x1p-500 && m < 0x1p500) {
-    double r = __builtin_amdgcn_rcp(d);
-    r = fma(fma(-d, r, 1.0), r, r);
-    r = fma(fma(-d, r, 1.0), r, r);
-    return r;
-  }
-  return 1.0 / d;
+// each doubling the correct bits) instead of a full division.  recip_ok says
+// afterwards whether that held: out of range, zero and non-finite pivots all
+// leave a result whose exponent is beyond the limits.
+__device__ __forceinline__ double fast_recip(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return fma(fma(-d, r, 1.0), r, r);
 }
-__device__ __forceinline__ cplx pivot_recip(cplx d) {
-  const double m = fmax(fabs(d.re), fabs(d.im));
-  if (m > 0x1p-240 && m < 0x1p240) {
-    const double r = pivot_recip(fma(d.re, d.re, d.im * d.im));
-    return cplx{d.re * r, -d.im * r};
-  }
-  return cdiv(cplx{1.0, 0.0}, d);
+__device__ __forceinline__ cplx fast_recip(cplx d) {
+  const double r = fast_recip(fma(d.re, d.re, d.im * d.im));
+  return cplx{d.re * r, -d.im * r};
+}
+__device__ __forceinline__ uint32_t exponent_of(double v) {
+  return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 52) & 0x7ffu;
+}
+__device__ __forceinline__ bool recip_ok(double di) { return exponent_of(di) - 523u < 1000u; }
+__device__ __forceinline__ bool recip_ok(cplx di) {
+  return max(exponent_of(di.re), exponent_of(di.im)) - 783u < 480u;  // the squared modulus is in range too
 }
 
 // Component-wise select (a select of whole complex values goes through memory).
 __device__ __forceinline__ double pick(bool c, double a, double b) { return c ? a : b; }
 __device__ __forceinline__ cplx pick(bool c, cplx a, cplx b) { return cplx{c ? a.re : b.re, c ? a.im : b.im}; }
 
-// x[q] -= w_q y for the lanes of ldl16; ys carries the sign of conj(w_q) on the lanes of S.
-__device__ __forceinline__ void ldl_step(double &x, double w, double y, double) { x = fma(-w, y, x); }
-__device__ __forceinline__ void ldl_step(cplx &x, cplx w, cplx y, cplx ys) {
-  x.re = fma(w.im, ys.im, fma(-w.re, y.re, x.re));
-  x.im = fma(-w.im, ys.re, fma(-w.re, y.im, x.im));
+// x -= w[lane Q of the row] y; sg: the sign of the imaginary part of w (conj(w_q) on the lanes of S if Hermitian)
+template <int Q> __device__ __forceinline__ void ldl_step(double &x, double w, double ny) { fmac16<Q>(x, w, ny); }
+struct NegY {
+  cplx ny, sy;  // -y and sg y
+};
+template <int Q> __device__ __forceinline__ void ldl_step(cplx &x, cplx w, const NegY &y) {
+  fmac16<Q>(x.re, w.re, y.ny.re);
+  fmac16<Q>(x.im, w.re, y.ny.im);
+  fmac16<Q>(x.re, w.im, y.sy.im);
+  fmac16<Q>(x.im, w.im, -y.sy.re);
 }
-__device__ __forceinline__ double scale_t(double s, double a) { return a; }
-__device__ __forceinline__ cplx scale_t(double s, cplx a) { return cplx{s * a.re, s * a.im}; }
-
-// Unpivoted LDL^T (LDL^H) of one 16 x 16 diagonal block and the inverse of
-// its L, by one wavefront: lane r < 16 holds row r of S (lower part) in x, lane
-// 16 + q column q of the identity.  Step j needs the same update on both:
-// row r:  S(r, q) -= L(r, j) W(q, j),  column q:  M(p, q) -= L(p, j) M(j, q),
-// i.e. x[q] -= w_q (x[j] / d_j) with w_q = S(q, j) read from lane q.  Only the
-// first w columns are eliminated.  On return row r holds L(r, 0 .. r - 1) and
-// D_r, column q holds M(:, q); 1 / D_j goes to dl[j] (1 beyond w).  A zero or
-// non-finite pivot is recorded (column first + j).
-// The whole step is latency of a serial chain (16 reciprocals, 120 dependent
-// broadcast-and-update steps); on the vector unit with lane broadcasts it runs
-// without LDS or barriers.
-template <typename T>
-__device__ __forceinline__ void ldl16(T (&x)[16], int w, double cs, double *dl, int64_t first,
-                                      unsigned long long *ferr) {
-  const int lane = threadIdx.x & 63;
-  const double sg = lane < 16 ? cs : 1.0;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    T di = SOps<T>::one();
-    if (j < w) {
-      const T d = readlane_t(x[j], j);
-      if (!finite_nonzero(d) && lane == 0) atomicMin(ferr, (unsigned long long)(first + j));
-      di = pivot_recip(d);
-      const T y = x[j] * di, ys = scale_t(sg, y);
-#pragma unroll
-      for (int q = j + 1; q < 16; ++q) ldl_step(x[q], readlane_t(x[j], q), y, ys);
-      x[j] = pick(lane < 16 && lane > j, y, x[j]);
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int p = 0; p < Planes<T>::P; ++p) dl[16 * p + j] = Planes<T>::get(di, p);
-    }
-  }
-}
+__device__ __forceinline__ double neg_y(double y, double) { return -y; }
+__device__ __forceinline__ NegY neg_y(cplx y, double sg) { return NegY{cplx{-y.re, -y.im}, cplx{sg * y.re, sg * y.im}}; }
 
 // LDS ordering inside one wavefront.
 __device__ __forceinline__ void wave_lds_fence() {
@@ -243,43 +250,161 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
-// M from the lanes of ldl16 into LDS in the operand layout (element 16 q + p
-// = M(p, q)), the conjugate if Hermitian.
-template <typename T> __device__ __forceinline__ void ldl16_put_m(const T (&x)[16], double cs, double *ms, int stride) {
+// The lanes of ldl16 in LDS: row r of L and D at [17 r + k], M(p, q) at
+// [17 (16 + q) + p], 1 / D_j at [kLdlD + j]; planes kLdlLds apart.
+constexpr int kLdlD = 32 * 17;
+constexpr int kLdlLds = kLdlD + 16;
+template <typename T> __device__ __forceinline__ void lds_set(double *q, T v) {
+#pragma unroll
+  for (int p = 0; p < Planes<T>::P; ++p) q[p * kLdlLds] = Planes<T>::get(v, p);
+}
+template <typename T> __device__ __forceinline__ T lds_at(const double *q) { return Planes<T>::from(q, kLdlLds); }
+template <typename T> __device__ __forceinline__ void ldl16_put(const T (&x)[16], T dinv, double *ls) {
   const int lane = threadIdx.x & 63;
-  if (lane >= 16 && lane < 32) {
+  if (lane < 32) {
 #pragma unroll
-    for (int p = 0; p < 16; ++p) {
-      const T v = cj(x[p], cs);
-#pragma unroll
-      for (int pl = 0; pl < Planes<T>::P; ++pl) ms[pl * stride + 16 * (lane - 16) + p] = Planes<T>::get(v, pl);
+    for (int k = 0; k < 16; ++k) lds_set<T>(ls + 17 * lane + k, x[k]);
+  }
+  if (lane < 16) lds_set<T>(ls + kLdlD + lane, dinv);
+}
+
+// Unpivoted LDL^T (LDL^H) of one 16 x 16 diagonal block and the inverse of
+// its L, by one wavefront: lane r < 16 holds row r of S (lower part) in x, lane
+// 16 + q column q of the identity (lanes 32 .. 63 are not used).  Step j needs
+// the same update on both:
+// row r:  S(r, q) -= L(r, j) W(q, j),  column q:  M(p, q) -= L(p, j) M(j, q),
+// i.e. x[q] -= w_q (x[j] / d_j) with w_q = S(q, j) of lane q.  A block of w < 16
+// columns is padded with the identity (its columns are skipped in fours).
+// Row r becomes L(r, 0 .. r - 1) and D_r, column q M(:, q), and lane j < 16
+// gets 1 / D_j.  False when a pivot is outside the range of the fast
+// reciprocal (x is then undefined).
+// One wavefront issues at most an instruction every four cycles, so what
+// counts in this serial chain is their number: a column of S is copied to the
+// lanes of M once, a broadcast and its multiply-add are one instruction, and
+// there is no branch per column (with scalar lane reads and branches a block
+// took 4.7 us of the 128-column kernel's 39 us, FP64).
+template <typename T>
+__device__ __forceinline__ bool ldl16(T (&x)[16], int w, double cs, T &dinv) {
+  const int lane = threadIdx.x & 63;
+  const double sg = lane < 16 ? cs : 1.0;
+  dinv = SOps<T>::one();
+  static_for(
+      [&](auto bc) {
+        constexpr int b = decltype(bc)::value;
+        if (b == 0 || 4 * b < w)
+          static_for(
+              [&](auto jc) {
+                constexpr int j = 4 * b + decltype(jc)::value;
+                const T ww = even_row(x[j]);
+                const T di = fast_recip(bcast16<j>(ww));
+                const T y = x[j] * di;
+                const auto ny = neg_y(y, sg);
+                static_for(
+                    [&](auto qc) {
+                      constexpr int q = decltype(qc)::value + j + 1;
+                      ldl_step<q>(x[q], ww, ny);
+                    },
+                    std::make_integer_sequence<int, 15 - j>{});
+                int ln = lane;
+                asm("" : "+v"(ln));  // the lane masks are made here: kept from step to step they spill
+                x[j] = pick((unsigned)(ln - j - 1) < (unsigned)(15 - j), y, x[j]);
+                dinv = pick(ln == j, di, dinv);
+              },
+              std::make_integer_sequence<int, 4>{});
+      },
+      std::make_integer_sequence<int, 4>{});
+  return __ballot(lane < 16 && !recip_ok(dinv)) == 0;
+}
+
+// The same from LDS, with full divisions, for the blocks ldl16 turns down:
+// lanes 0 .. 31 have put their x at [17 lane].  A zero or non-finite pivot is
+// recorded (column first + j).
+template <typename T>
+__device__ __forceinline__ void ldl16_wide_range(double *ls, int w, double cs, int64_t first, unsigned long long *ferr) {
+  const int lane = threadIdx.x & 63, row = lane & 31;
+  const double sg = row < 16 ? cs : 1.0;
+  if (lane < 16) lds_set<T>(ls + kLdlD + lane, SOps<T>::one());
+#pragma unroll 1
+  for (int j = 0; j < w; ++j) {
+    wave_lds_fence();
+    const T d = lds_at<T>(ls + 18 * j);
+    if (!finite_nonzero(d) && lane == 0) atomicMin(ferr, (unsigned long long)(first + j));
+    const T di = SOps<T>::div(SOps<T>::one(), d);
+    const T y = SOps<T>::div(lds_at<T>(ls + 17 * row + j), d);
+#pragma unroll 1
+    for (int q = j + 1; q < 16; ++q) {
+      const T v = lds_at<T>(ls + 17 * row + q) - cj(lds_at<T>(ls + 17 * q + j), sg) * y;
+      if (lane < 32) lds_set<T>(ls + 17 * row + q, v);
     }
+    wave_lds_fence();
+    if (lane > j && lane < 16) lds_set<T>(ls + 17 * lane + j, y);
+    if (lane == 0) lds_set<T>(ls + kLdlD + j, di);
   }
 }
-// L and D of the block into the panel (lower triangle only).
-template <typename T> __device__ __forceinline__ void ldl16_store(const T (&x)[16], T *Q, int64_t ld, int w) {
-  const int lane = threadIdx.x & 63;
+
+// Both of them; load(x) gives each lane its x again.
+template <typename T, class F>
+__device__ __forceinline__ void ldl16_block(T (&x)[16], F load, int w, double cs, double *ls, int64_t first,
+                                            unsigned long long *ferr) {
+  T dinv;
+  const bool ok = ldl16<T>(x, w, cs, dinv);
+  if (!ok) load(x);
+  ldl16_put<T>(x, dinv, ls);
+  wave_lds_fence();
+  if (!ok) {
+    ldl16_wide_range<T>(ls, w, cs, first, ferr);
+    wave_lds_fence();
+  }
+}
+
+// M as the A operand of W^T = M S^T (conjugated if Hermitian).
+template <typename T> __device__ __forceinline__ Blk<T> ldl16_m(const double *q, double cs) {
+  const int r = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+  Blk<T> m;
 #pragma unroll
-  for (int k = 0; k < 16; ++k)
-    if (lane < w && k <= lane) gstore(Q + k * ld + lane, x[k]);
+  for (int v = 0; v < 4; ++v) blk_set(m, v, cj(Planes<T>::from(q + 17 * (16 + 4 * v + g) + r, kLdlLds), cs));
+  return m;
+}
+// L and D into the panel (lower triangle only).
+template <typename T> __device__ __forceinline__ void ldl16_store(const double *ls, T *Q, int ld, int w) {
+  const int r = blk_row(), g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+    if (r < w && 4 * v + g <= r)
+      st_off(Q, (uint32_t)((4 * v + g) * ld + r) * (uint32_t)sizeof(T), lds_at<T>(ls + 17 * r + 4 * v + g));
 }
 
 // ---------------------------------------------------------------------------
-// Whole nodes with s <= 16 and c <= 16 NST in one wavefront: the diagonal
+// Whole nodes with s <= 16 and c <= kFacSmallC in one wavefront: the diagonal
 // block, L_{C,K} one 16-row strip at a time, and every 16 x 16 block of the
 // update of S_{C,C} from registers.  These nodes are most of the tree and
 // have almost no arithmetic: what bounds them is the launches and the
 // dependent rounds of loads (record -> panel and row tables -> positions), so
 // one launch does everything and a CU holds many nodes at once (four launches
-// on 64 x 64 tiles before; 31 x 31 FP64 grid: 0.27 -> 0.09 ms for its ten depths;
-// 16 Hermitian 30^3 matrices, the lower 13 depths: 10.5 -> 3.0 ms).
+// on 64 x 64 tiles before; 31 x 31 FP64 grid: 0.27 -> 0.08 ms for its ten depths;
+// 16 Hermitian 30^3 matrices, the lower 13 depths: 10.5 -> 2.9 ms, where the
+// atomics of nodes with c near 64 bound it).
 // ---------------------------------------------------------------------------
-template <typename T, int NST>
-__global__ void __launch_bounds__(64) k_fac_small(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs,
+// x of ldl16 from the panel.
+template <typename T>
+__device__ __forceinline__ void small_load(const T *Q, int ld, int s, T (&x)[16]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int k = 0; k < 16; ++k)
+    x[k] = ld_off(Q, ((uint32_t)(k * ld + lane) & opaque_mask32(lane < s && k <= lane)) * (uint32_t)sizeof(T));
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const T id = pick(lane - 16 == k || (lane == k && k >= s), SOps<T>::one(), zero_of<T>());
+    x[k] = pick(lane < s && k <= lane, x[k], id);
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs,
                                                   int32_t count, unsigned long long *ferr) {
-  constexpr int P = Planes<T>::P;
+  constexpr int P = Planes<T>::P, NST = kFacSmallC / 16;
   const DevPlan &pl = *plp;
-  __shared__ double ms[P * 256], dl[P * 16];
+  __shared__ double ls[P * kLdlLds];
   __shared__ int64_t rcol[16 * NST], rpos[16 * NST];
   const int64_t gidx = blockIdx.x;
   const int64_t l = gidx / count;
@@ -289,59 +414,53 @@ __global__ void __launch_bounds__(64) k_fac_small(const DevPlan *__restrict__ pl
   T *Q = Pl + nd.off;
   const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
   const double cs = pl.csign;
+  const int kq = min(lane, c - 1);
+  const int64_t kc = c > 0 ? gp(pl.kcol)[nd.rp + kq] : 0, kp = c > 0 ? gp(pl.kpos)[nd.rp + kq] : 0;
   T x[16];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) x[k] = gload(Q + (((int64_t)k * ld + lane) & opaque_mask(lane < s && k <= lane)));
-  Blk<T> sb[NST];
+  small_load<T>(Q, ld, s, x);
+  Blk<T> wb[NST];
 #pragma unroll
   for (int i = 0; i < NST; ++i)
-    if (16 * i < c) sb[i] = blk_load<T>(Q + s + 16 * i, ld, c - 16 * i, s);
-#pragma unroll
-  for (int u = 0; u < (16 * NST + 63) / 64; ++u) {
-    const int k = lane + 64 * u;
-    if (k < c) {
-      rcol[k] = gp(pl.kcol)[nd.rp + k];
-      rpos[k] = gp(pl.kpos)[nd.rp + k];
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const T id = pick(lane - 16 == k, SOps<T>::one(), zero_of<T>());
-    x[k] = pick(lane < s && k <= lane, x[k], id);
-  }
-  ldl16<T>(x, s, cs, dl, nd.first, ferr + l);
-  ldl16_put_m<T>(x, cs, ms, 256);
-  ldl16_store<T>(x, Q, ld, s);
+    if (16 * i < c) wb[i] = blk_load<T>(Q + s + 16 * i, ld, c - 16 * i, s);
+  rcol[lane] = kc;
+  rpos[lane] = kp;
   wave_lds_fence();
+  // positions of the update's elements in strip j's columns, loaded one strip
+  // ahead (the first while the diagonal block is factored)
+  int32_t pos[2][NST][4];
+  auto load_pos = [&](int j) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int kg = 16 * j + 4 * v + g;
+      const int64_t rp = rpos[kg];
+#pragma unroll
+      for (int i = 0; i < NST; ++i) {
+        const int ig = 16 * i + r;
+        if (i >= j && 16 * i < c) pos[j & 1][i][v] = gp(pl.posarr)[(rp + ig) & opaque_mask(ig < c && ig >= kg)];
+      }
+    }
+  };
+  load_pos(0);
+  ldl16_block<T>(x, [&](T(&y)[16]) { small_load<T>(Q, ld, s, y); }, s, cs, ls, nd.first, ferr + l);
+  ldl16_store<T>(ls, Q, ld, s);
   const int nv = (s + 3) / 4;
-  const Blk<T> m = blk_from_lds<T>(ms, 256);
-  Blk<T> wb[NST];
+  const Blk<T> m = ldl16_m<T>(ls, cs);
 #pragma unroll
   for (int i = 0; i < NST; ++i) {
     if (16 * i >= c) break;
-    wb[i] = blk_zero<T>();
-    blk_mma<T>(m, sb[i], wb[i], nv);
-    sb[i] = blk_scale_rows<T>(wb[i], dl);
-    blk_store<T>(sb[i], Q + s + 16 * i, ld, c - 16 * i, s);
+    Blk<T> w = blk_zero<T>();
+    blk_mma<T>(m, wb[i], w, nv);
+    wb[i] = w;
+    blk_store<T>(blk_scale_rows<T>(w, ls + kLdlD, kLdlLds), Q + s + 16 * i, ld, c - 16 * i, s);
   }
 #pragma unroll
   for (int j = 0; j < NST; ++j) {
     if (16 * j >= c) break;
-    const Blk<T> lj = blk_neg_cj<T>(sb[j], cs);
+    if (j + 1 < NST && 16 * (j + 1) < c) load_pos(j + 1);
+    const Blk<T> lj = blk_neg_cj<T>(blk_scale_rows<T>(wb[j], ls + kLdlD, kLdlLds), cs);
     int64_t col[4];
-    int32_t pos[NST][4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int kg = min(16 * j + 4 * v + g, c - 1);
-      col[v] = rcol[kg];
-      const int64_t rp = rpos[kg];
-#pragma unroll
-      for (int i = j; i < NST; ++i)
-        if (16 * i < c) {
-          const int ig = 16 * i + r;
-          pos[i][v] = gp(pl.posarr)[(rp + ig) & opaque_mask(ig < c && ig >= kg)];
-        }
-    }
+    for (int v = 0; v < 4; ++v) col[v] = rcol[16 * j + 4 * v + g];
 #pragma unroll
     for (int i = j; i < NST; ++i) {
       if (16 * i >= c) break;
@@ -350,8 +469,91 @@ __global__ void __launch_bounds__(64) k_fac_small(const DevPlan *__restrict__ pl
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int ig = 16 * i + r, kg = 16 * j + 4 * v + g;
-        if (ig < c && kg <= ig) atomic_add_t(Pl + col[v] + pos[i][v], blk_get(u, v));
+        if (ig < c && kg <= ig) atomic_add_t(Pl + col[v] + pos[j & 1][i][v], blk_get(u, v));
       }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// The same for kFacSmallC < c <= kFacMidC by four wavefronts: one factors the
+// diagonal block, each forms every fourth strip of W and -L in LDS and takes
+// every fourth pair of strips of the update (one wavefront for all of it held
+// 360 registers and waited for one strip's positions after another: 30 to 36
+// us a launch on the 40^3 FP64 Laplacian, now 10 to 22).
+template <typename T>
+__global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs,
+                                                int32_t count, unsigned long long *ferr) {
+  constexpr int P = Planes<T>::P, NST = kFacMidC / 16, W = NT / 64, NP = NST * (NST + 1) / 2, LP = NST * 256;
+  const DevPlan &pl = *plp;
+  __shared__ double ls[P * kLdlLds], wp[P * LP], lp[P * LP];
+  __shared__ int64_t rcol[kFacMidC], rpos[kFacMidC];
+  const int64_t gidx = blockIdx.x;
+  const int64_t l = gidx / count;
+  const FacNode nd = recs[gidx - l * count];
+  const int s = uniform(nd.s), c = uniform(nd.c), ld = s + c;
+  T *Pl = Pall + l * pl.panel_elems;
+  T *Q = Pl + nd.off;
+  const int wv = uniform((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const double cs = pl.csign;
+  if (threadIdx.x < kFacMidC) {
+    const int kq = min((int)threadIdx.x, c - 1);
+    rcol[threadIdx.x] = gp(pl.kcol)[nd.rp + kq];
+    rpos[threadIdx.x] = gp(pl.kpos)[nd.rp + kq];
+  }
+  T x[16];
+  if (wv == 0) small_load<T>(Q, ld, s, x);
+  Blk<T> sb[NST / W];
+#pragma unroll
+  for (int q = 0; q < NST / W; ++q) {
+    const int i = wv + W * q;
+    if (16 * i < c) sb[q] = blk_load<T>(Q + s + 16 * i, ld, c - 16 * i, s);
+  }
+  lds_barrier();
+  // pair e = wv + W q of strips (i, j), i >= j, row by row
+  int pi[(NP + W - 1) / W], pj[(NP + W - 1) / W];
+  int32_t pos[(NP + W - 1) / W][4];
+#pragma unroll
+  for (int q = 0; q < (NP + W - 1) / W; ++q) {
+    int j = wv + W * q, i = 0;
+    while (j > i) j -= ++i;
+    pi[q] = uniform(i);
+    pj[q] = uniform(j);
+    if (16 * pi[q] >= c) continue;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int ig = 16 * pi[q] + r, kg = 16 * pj[q] + 4 * v + g;
+      pos[q][v] = gp(pl.posarr)[(rpos[kg] + ig) & opaque_mask(ig < c && ig >= kg)];
+    }
+  }
+  if (wv == 0) {
+    ldl16_block<T>(x, [&](T(&y)[16]) { small_load<T>(Q, ld, s, y); }, s, cs, ls, nd.first, ferr + l);
+    ldl16_store<T>(ls, Q, ld, s);
+  }
+  lds_barrier();
+  const int nv = (s + 3) / 4;
+  const Blk<T> m = ldl16_m<T>(ls, cs);
+#pragma unroll
+  for (int q = 0; q < NST / W; ++q) {
+    const int i = wv + W * q;
+    if (16 * i >= c) break;
+    Blk<T> w = blk_zero<T>();
+    blk_mma<T>(m, sb[q], w, nv);
+    const Blk<T> lo = blk_scale_rows<T>(w, ls + kLdlD, kLdlLds);
+    blk_to_lds<T>(w, wp + 256 * i, LP);
+    blk_to_lds<T>(blk_neg_cj<T>(lo, cs), lp + 256 * i, LP);
+    blk_store<T>(lo, Q + s + 16 * i, ld, c - 16 * i, s);
+  }
+  lds_barrier();
+#pragma unroll
+  for (int q = 0; q < (NP + W - 1) / W; ++q) {
+    if (16 * pi[q] >= c) break;
+    Blk<T> u = blk_zero<T>();
+    blk_mma<T>(blk_from_lds<T>(lp + 256 * pj[q], LP), blk_from_lds<T>(wp + 256 * pi[q], LP), u, nv);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int ig = 16 * pi[q] + r, kg = 16 * pj[q] + 4 * v + g;
+      if (ig < c && kg <= ig) atomic_add_t(Pl + rcol[kg] + pos[q][v], blk_get(u, v));
     }
   }
 }
@@ -365,9 +567,9 @@ __global__ void __launch_bounds__(64) k_fac_small(const DevPlan *__restrict__ pl
 // M S^T and L^T = D^{-1} W^T and go to LDS; every block right of the panel
 // takes its rank-16 update.  The next diagonal block is updated and factored
 // before its owner's other blocks.  What bounds it is the serial chain of the
-// ldl16 steps: 34 us a launch on average on the 40^3 FP64 Laplacian (19.9 ms of
-// diagonal blocks a factorization -> 1.35 ms) and 75 us on 16 Hermitian 30^3
-// matrices (15.9 -> 1.7 ms); the form before updated the block in global memory, one
+// ldl16 steps: 25 us (FP64) and 55 us (complex) for 128 columns; 19.9 -> 0.84 ms
+// of diagonal blocks a factorization on the 40^3 FP64 Laplacian, 15.9 -> 1.2 ms
+// on 16 Hermitian 30^3 matrices; the form before updated the block in global memory, one
 // thread an element, 1.3 ms (FP64) and 1.7 ms (complex) for 256 columns.
 // The inverses M_k (operand layout) and 1 / D go to `fin` for k_fac_lc.
 // ---------------------------------------------------------------------------
@@ -381,7 +583,7 @@ __global__ void __launch_bounds__(64 * kFacWaves, 2)
   constexpr int P = Planes<T>::P, NB = kFacWaves, LP = NB * 256;  // LP: doubles of one plane of a panel
   const DevPlan &pl = *plp;
   __shared__ double lp[P * LP], wp[P * LP];  // -L(i, k) (conjugated if Hermitian) and W(i, k), block i at 256 i
-  __shared__ double ms[P * 256], tr[P * 16 * 17], dl[P * 16];
+  __shared__ double ls[P * kLdlLds];
   const int64_t gidx = blockIdx.x;
   const int64_t l = gidx / count;
   const FacNode nd = recs[gidx - l * count];
@@ -404,6 +606,15 @@ __global__ void __launch_bounds__(64 * kFacWaves, 2)
 #pragma unroll
   for (int q = 0; q < kFacSlots; ++q)
     if (bi[q] >= 0) ob[q] = blk_load<T>(Q + (int64_t)(16 * bj[q]) * ld + 16 * bi[q], ld, s - 16 * bi[q], 16);
+  // L, D, M and 1 / D of diagonal block kk, from LDS
+  auto store_diag = [&](int kk) {
+    ldl16_store<T>(ls, Q + (int64_t)(16 * kk) * ld + 16 * kk, ld, min(16, s - 16 * kk));
+    const Blk<T> m = ldl16_m<T>(ls, cs);
+    T *Fk = F + kFacFin * kk;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gstore(Fk + 64 * v + lane, blk_get(m, v));
+    if (lane < 16) gstore(Fk + 256 + lane, Planes<T>::from(&ls[kLdlD + lane], kLdlLds));
+  };
   for (int k = 0; k < nb; ++k) {
     if (k > 0) {  // panel k - 1
       lds_barrier();
@@ -412,37 +623,35 @@ __global__ void __launch_bounds__(64 * kFacWaves, 2)
       for (int q = 0; q < kFacSlots; ++q)
         if (bj[q] == kk) {
           Blk<T> w = blk_zero<T>();
-          blk_mma<T>(blk_from_lds<T>(ms, 256), ob[q], w);
-          const Blk<T> lo = blk_scale_rows<T>(w, dl);
+          blk_mma<T>(ldl16_m<T>(ls, cs), ob[q], w);
+          const Blk<T> lo = blk_scale_rows<T>(w, ls + kLdlD, kLdlLds);
           blk_to_lds<T>(w, wp + 256 * bi[q], LP);
           blk_to_lds<T>(blk_neg_cj<T>(lo, cs), lp + 256 * bi[q], LP);
           blk_store<T>(lo, Q + (int64_t)(16 * kk) * ld + 16 * bi[q], ld, s - 16 * bi[q], 16);
         }
+      if (wv == kk) store_diag(kk);
       lds_barrier();
       if (wv >= k && wv < nb)
         blk_mma<T>(blk_from_lds<T>(lp + 256 * wv, LP), blk_from_lds<T>(wp + 256 * wv, LP), dg);
     }
     if (wv == k) {
       const int w = min(16, s - 16 * k);
+      auto rows = [&](T(&y)[16]) {
 #pragma unroll
-      for (int p = 0; p < P; ++p)
+        for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) tr[p * 272 + r * 17 + 4 * v + g] = dg.p[p][v];
-      wave_lds_fence();
+          for (int v = 0; v < 4; ++v) ls[p * kLdlLds + r * 17 + 4 * v + g] = dg.p[p][v];
+        wave_lds_fence();
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          const T id = pick(lane - 16 == c || (lane == c && c >= w), SOps<T>::one(), zero_of<T>());
+          y[c] = pick(lane < w && c <= lane, lds_at<T>(ls + r * 17 + c), id);
+        }
+        wave_lds_fence();
+      };
       T x[16];
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const T id = pick(lane - 16 == c, SOps<T>::one(), zero_of<T>());
-        x[c] = pick(lane < w && c <= lane, Planes<T>::from(&tr[r * 17 + c], 272), id);
-      }
-      ldl16<T>(x, w, cs, dl, nd.first + 16 * k, ferr + l);
-      ldl16_put_m<T>(x, cs, ms, 256);
-      ldl16_store<T>(x, Q + (int64_t)(16 * k) * ld + 16 * k, ld, w);
-      wave_lds_fence();
-      T *Fk = F + kFacFin * k;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) gstore(Fk + 64 * v + lane, Planes<T>::from(&ms[64 * v + lane], 256));
-      if (lane < 16) gstore(Fk + 256 + lane, Planes<T>::from(&dl[lane], 16));
+      rows(x);
+      ldl16_block<T>(x, rows, w, cs, ls, nd.first + 16 * k, ferr + l);
     }
     if (k > 0) {
 #pragma unroll
@@ -450,6 +659,8 @@ __global__ void __launch_bounds__(64 * kFacWaves, 2)
         if (bj[q] >= k) blk_mma<T>(blk_from_lds<T>(lp + 256 * bj[q], LP), blk_from_lds<T>(wp + 256 * bi[q], LP), ob[q]);
     }
   }
+  wave_lds_fence();
+  if (wv == nb - 1) store_diag(nb - 1);  // its own wavefront wrote it
 }
 
 // The rows below a diagonal block of at most kFacCols columns, in place: L =
@@ -528,7 +739,7 @@ __global__ void __launch_bounds__(NT, 2)
     blk_mma<T>(blk_from_lds<T>(b + 256 * k, LP), sb[k], w);
     if (k + 1 < nb) put(k + 1);
     if (k + 2 < nb) load(k + 2);
-    blk_store<T>(blk_scale_rows<T>(w, dl[k]), R + (int64_t)(16 * k) * ld, ld, rows, s - 16 * k);
+    blk_store<T>(blk_scale_rows<T>(w, dl[k], 16), R + (int64_t)(16 * k) * ld, ld, rows, s - 16 * k);
 #pragma unroll
     for (int j = k + 1; j < NB; ++j)
       if (j < nb) blk_mma<T>(blk_from_lds<T>(b + 256 * j, LP), w, sb[j]);
@@ -664,22 +875,34 @@ __global__ void k_fac_init(unsigned long long *ferr, int64_t batch) {
 
 // log det B = sum_j log D_jj per matrix: the sum of the principal logarithms
 // of the pivots (real part log |d|, imaginary part arg d; pi per negative
-// pivot of a real matrix), reduced in a fixed order.
+// pivot of a real matrix).  Workgroup q of a matrix takes pivots [q, q + 1)
+// kLdetSpan and leaves its sum, reduced in a fixed order; the host adds the sums in
+// order when it reads them.  Bound by the logarithms' arithmetic: one
+// workgroup for a whole matrix took 215 us for 64,000 pivots.
 template <typename T>
-__global__ void __launch_bounds__(NT) k_fac_logdet(const DevPlan *__restrict__ plp, const T *Pall, double *out) {
+__global__ void __launch_bounds__(NT) k_fac_logdet(const DevPlan *__restrict__ plp, const T *Pall, double *out, int32_t nq) {
+  constexpr int U = 4;
+  static_assert(kLdetSpan % (NT * U) == 0, "whole rounds of loads");
   const DevPlan &pl = *plp;
   __shared__ double sr[NT], si[NT];
-  const int64_t l = blockIdx.x;
+  const int64_t l = blockIdx.x / nq, q = blockIdx.x - l * nq;
   const T *P = Pall + l * pl.panel_elems;
+  const int64_t jend = min((q + 1) * kLdetSpan, pl.n);
   double re = 0.0, im = 0.0;
-  for (int64_t j = threadIdx.x; j < pl.n; j += NT) {
-    const T d = P[gp(pl.dpos)[j]];
-    if constexpr (Planes<T>::P == 1) {
-      re += log(fabs(d));
-      if (d < 0) im += M_PI;
-    } else {
-      re += log(hypot(d.re, d.im));
-      im += atan2(d.im, d.re);
+  for (int64_t j0 = q * kLdetSpan + threadIdx.x; j0 < jend; j0 += NT * U) {
+    T d[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) d[u] = gload(P + gp(pl.dpos)[min(j0 + NT * u, jend - 1)]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (j0 + NT * u >= jend) break;
+      if constexpr (Planes<T>::P == 1) {
+        re += log(fabs(d[u]));
+        if (d[u] < 0) im += M_PI;
+      } else {
+        re += log(hypot(d[u].re, d[u].im));
+        im += atan2(d[u].im, d[u].re);
+      }
     }
   }
   sr[threadIdx.x] = re;
@@ -693,8 +916,8 @@ __global__ void __launch_bounds__(NT) k_fac_logdet(const DevPlan *__restrict__ p
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    out[2 * l] = sr[0];
-    out[2 * l + 1] = si[0];
+    out[2 * (int64_t)blockIdx.x] = sr[0];
+    out[2 * (int64_t)blockIdx.x + 1] = si[0];
   }
 }
 
@@ -708,12 +931,12 @@ hipError_t factor_impl(const DevPlan &pl, const DevPlan *dpl, const FactorAux &f
   const unsigned B = (unsigned)pl.batch;
   for (int q = 0; q < fa.nlev; ++q) {
     const FacLevel &lv = fa.lev[q];
-    if (lv.small4_n > 0)
-      hipLaunchKernelGGL((k_fac_small<T, 4>), dim3(lv.small4_n * B), dim3(64), 0, st, dpl, P, fa.nodes + lv.small4_b,
-                         lv.small4_n, pl.ferr);
-    if (lv.small8_n > 0)
-      hipLaunchKernelGGL((k_fac_small<T, 8>), dim3(lv.small8_n * B), dim3(64), 0, st, dpl, P, fa.nodes + lv.small8_b,
-                         lv.small8_n, pl.ferr);
+    if (lv.small_n > 0)
+      hipLaunchKernelGGL(k_fac_small<T>, dim3(lv.small_n * B), dim3(64), 0, st, dpl, P, fa.nodes + lv.small_b,
+                         lv.small_n, pl.ferr);
+    if (lv.mid_n > 0)
+      hipLaunchKernelGGL(k_fac_mid<T>, dim3(lv.mid_n * B), dim3(NT), 0, st, dpl, P, fa.nodes + lv.mid_b, lv.mid_n,
+                         pl.ferr);
     for (int h = 0; h < 2; ++h) {  // column block h of the nodes
       if (lv.diag_n[h] > 0)
         hipLaunchKernelGGL(k_fac_diag<T>, dim3(lv.diag_n[h] * B), dim3(64 * kFacWaves), 0, st, dpl, P,
@@ -729,7 +952,8 @@ hipError_t factor_impl(const DevPlan &pl, const DevPlan *dpl, const FactorAux &f
       hipLaunchKernelGGL((k_fac_update<T, false>), dim3(lv.tiles_n * B), dim3(NT), 0, st, dpl, P, fa.nodes,
                          fa.tiles + lv.tiles_b, lv.tiles_n);
   }
-  hipLaunchKernelGGL(k_fac_logdet<T>, dim3(B), dim3(NT), 0, st, dpl, P, pl.fldet);
+  const int32_t nq = (int32_t)ldet_parts(pl.n);
+  hipLaunchKernelGGL(k_fac_logdet<T>, dim3(B * nq), dim3(NT), 0, st, dpl, P, pl.fldet, nq);
   return hipGetLastError();
 }
 

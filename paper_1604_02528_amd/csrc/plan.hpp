@@ -121,6 +121,10 @@ struct alignas(16) TinyRec {
 // graph, so the smallest unfinished ticket can always run).
 enum Ctrl : int32_t { CTRL_ERR = 0, CTRL_TICKET = 32, CTRL_WORDS = 64 };
 
+// Pivots per partial sum of the device factorization's log det.
+constexpr int64_t kLdetSpan = 2048;
+__host__ __device__ constexpr int64_t ldet_parts(int64_t n) { return (n + kLdetSpan - 1) / kLdetSpan; }
+
 // Raw device pointers, valid for one (context, work buffer) pair.
 struct DevPlan {
   int64_t n, ns, nitems, batch, panel_elems, sq_elems, nnzA, total_rows, part_elems;
@@ -164,7 +168,7 @@ struct DevPlan {
   Item *bitems;        // adjoint work items
   int64_t *dpos;       // [n] panel element of each pivot D_jj (one matrix)
   unsigned long long *ferr;  // [batch] device factorization: first column with a bad pivot (~0: none)
-  double *fldet;       // [batch][2] device factorization: log det (re, im)
+  double *fldet;       // [batch][ldet_parts(n)][2] device factorization: partial sums of log det (re, im)
   void *finv;          // [batch][fin_elems] device factorization: inverses of one depth's 16 x 16 diagonal blocks
   int64_t fin_elems;
   int32_t *ctrl;       // CTRL_WORDS
@@ -229,6 +233,7 @@ struct LaunchAux {
 // A column block of the device factorization (see factor.hip): a whole node,
 // or columns [128 h, 128 h + s) of a wider one.
 constexpr int kFacCols = 128;  // widest column block
+constexpr int kFacSmallC = 64, kFacMidC = 128;
 constexpr int kFacFin = 272;   // scratch scalars per 16 columns: the 16 x 16 inverse of L_kk, then 1 / D
 struct alignas(16) FacNode {
   int64_t off;    // panel offset of the block's first diagonal element
@@ -242,8 +247,8 @@ struct alignas(16) FacNode {
 // Launches of the device factorization, one entry per etree depth (deepest
 // first): ranges of the lists in FactorAux.
 struct FacLevel {
-  int32_t small4_b, small4_n;      // nodes with s <= 16 and c <= 64, one wavefront each
-  int32_t small8_b, small8_n;      // the same with 64 < c <= 128
+  int32_t small_b, small_n;        // nodes with s <= 16 and c <= kFacSmallC, one wavefront each
+  int32_t mid_b, mid_n;            // the same with c <= kFacMidC, four wavefronts each
   int32_t diag_b[2], diag_n[2];    // column block h of the other nodes (diagonal block)
   int32_t rb_b[2], rb_n[2];        // 64-row blocks below it
   int32_t inner_b, inner_n;        // tiles of the second column blocks updated by the first
