@@ -667,16 +667,31 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
     for (int64_t d = 0; d < S.depth; ++d) {
       H.lvl_depth_first[d] = (int32_t)H.lvl_ptr.size() - 1;
       for (int ph = 0; ph < kPhases; ++ph) {
-        // phase 1: the GEMM-1 tiles of nodes with a dense buffer form a launch of their own
-        for (int pass = 0; pass < (ph == 1 && per_level ? 2 : 1); ++pass) {
+        // phase 1: gathered GEMM-1 tiles, the fused ones of nodes with a dense
+        // buffer, and k_ydense's tiles; phase 3: diagonal blocks and
+        // single-workgroup nodes: a launch each
+        static const int32_t kinds1[3] = {LVL_YGATHER, LVL_ITEMS, LVL_YDENSE};
+        // (a depth with single-workgroup nodes whose diagonal blocks do not fill
+        // the GPU keeps both in one launch: there the launch costs more than
+        // the general kernel's occupancy)
+        int64_t dn = 0, sn = 0;
+        if (ph == 3)
+          for (int64_t K : bydepth[d])
+            if (!is_tiny(K)) (H.items[phase_begin(H, K, 3)].type == ITEM_D ? dn : sn) += phase_count(H, K, 3);
+        const bool mixed = ph == 3 && sn > 0 && dn * batch < kSplitTarget;
+        const int npass = !per_level ? 1 : ph == 1 ? 3 : ph == 3 && !mixed ? 2 : 1;
+        for (int pass = 0; pass < npass; ++pass) {
           for (int64_t K : bydepth[d]) {
             if (ph == 3 && is_tiny(K)) continue;
-            if (ph == 1 && per_level && (H.node_ykern[K] != 0) != (pass == 1)) continue;
-            if (ph == 1 && H.node_y128[K]) continue;  // launched on 128 x 128 tiles below
             const int32_t b = phase_begin(H, K, ph), n = phase_count(H, K, ph);
+            if (n == 0) continue;
+            if (ph == 1 && per_level && (H.node_goff[K] < 0 ? 0 : H.node_ykern[K] ? 2 : 1) != pass) continue;
+            if (ph == 1 && H.node_y128[K]) continue;  // launched on 128 x 128 tiles below
+            if (ph == 3 && npass == 2 && (H.items[b].type == ITEM_D) != (pass == 0)) continue;
             for (int32_t q = 0; q < n; ++q) H.lvl_items.push_back(b + q);
           }
-          close(-1, pass == 1 ? LVL_YDENSE : ph == 0 ? LVL_GATHER : ph == 2 ? LVL_GEMM2 : LVL_ITEMS);
+          const int32_t kind3 = npass == 2 && pass == 0 ? LVL_DIAG : LVL_ITEMS;
+          close(-1, ph == 0 ? LVL_GATHER : ph == 1 ? (npass == 3 ? kinds1[pass] : LVL_ITEMS) : ph == 2 ? LVL_GEMM2 : kind3);
         }
         if (ph == 1) {
           // 128 x 128 GEMM-1 tiles of the depth's FP64 dense-buffer nodes the tune table marks
@@ -2154,7 +2169,9 @@ selinv_status selinv_items(const selinv_ctx *hc, int32_t which, const int32_t **
           type = it.type;
           depth = (int32_t)h->S.sdepth[it.K];
         }
-        h->lseq.push_back(Item{H.lvl_kind[q], cnt, type, depth});
+        // (the launches of one item type are work items to the caller, like the mixed ones)
+        const int32_t kind = H.lvl_kind[q] == LVL_DIAG || H.lvl_kind[q] == LVL_YGATHER ? LVL_ITEMS : H.lvl_kind[q];
+        h->lseq.push_back(Item{kind, cnt, type, depth});
       }
     }
     *items = reinterpret_cast<const int32_t *>(h->lseq.data());

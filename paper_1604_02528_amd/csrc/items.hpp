@@ -358,6 +358,53 @@ __device__ void do_ytile(const Ctx<T> &cx, const NodeInfo &nd, int a, int bp, do
   lds_barrier();
 }
 
+// The gathered GEMM-1 tile of the level schedule's k_ygather: do_ytile without
+// the dense-buffer form, and (up) do_yutile.
+template <typename T>
+__device__ __forceinline__ void do_ygather(const Ctx<T> &cx, const NodeInfo &nd, int a, int bp, bool up, double *smem,
+                                           int64_t *rt) {
+  const DevPlan &pl = *cx.pl;
+  const int s = nd.s, c = nd.c, ld = s + c;
+  const int64_t rp = nd.rp;
+  const int b = bp & 0xffff, part = bp >> 16;
+  const int kb = part * nd.kchunk, ke = min(c, kb + nd.kchunk);
+  const int i0 = a * 64, j0 = b * 64;
+  if (threadIdx.x < 64) {
+    const int ig = i0 + threadIdx.x;
+    rt[threadIdx.x] = gp(pl.kcol)[rp + (ig < c ? ig : 0)];
+    rt[64 + threadIdx.x] = gp(pl.kpos)[rp + (ig < c ? ig : 0)];
+  }
+  lds_barrier();
+  // LU plans: X_{C,C}'s upper part from the X^T panel set; the upper tiles
+  // exchange the two sets (X_{C,C} transposed) and read Uhat^T
+  const int64_t hs = up ? pl.half : 0;
+  LoadGather<T, false> la{cx.Xp + hs, pl.kcol + rp, pl.kpos + rp, pl.posarr, rt, rt + 64, c, ke, i0};
+  la.cs = pl.csign;
+  la.du = up ? -pl.half : pl.half;
+  LoadPanelK<T, false> lb{cx.Lp + hs, nd.off, ld, s, 0, ke, j0, s};
+  Acc<T> acc;
+  gemm_tile<T>(kb, ke, la, lb, smem, acc);
+  acc_to_lds<T>(acc, smem);
+  lds_barrier();
+  if (nd.yoff < 0) {  // Y = -acc into X_{C,K} (up: the second set)
+    T *X = cx.Xp + hs + nd.off + s;
+    for (int e = threadIdx.x; e < 64 * 64; e += NT) {
+      const int i = e & 63, j = e >> 6;
+      if (i0 + i < c && j0 + j < s) gstore(X + (int64_t)(j0 + j) * ld + i0 + i, SOps<T>::scale(-1.0, lds_get<T>(smem, i, j)));
+    }
+    if (!up && !nd.defer2) {
+      lds_barrier();
+      gemm2_partial<T, false, Planes<T>::P == 1>(cx, nd, a, b, acc, smem);
+    }
+  } else {  // partial tile Ypart[part] (column-major c x s)
+    T *Y = static_cast<T *>(cx.Yp) + nd.yoff + (int64_t)part * c * s;
+    for (int e = threadIdx.x; e < 64 * 64; e += NT) {
+      const int i = e & 63, j = e >> 6;
+      if (i0 + i < c && j0 + j < s) gstore(Y + (int64_t)(j0 + j) * c + i0 + i, lds_get<T>(smem, i, j));
+    }
+  }
+}
+
 // Sum of a split node's partial tiles (a, b) into X, then the row tile's share
 // of GEMM-2 (the step-3 and step-4 work that an unsplit tile does itself).
 // With br = b | r << 16 | rq << 24 and rq > 1, the tile's GEMM-2 share is cut
@@ -627,16 +674,17 @@ __device__ void dtile_core(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, d
   lds_barrier();
 }
 
-// Blocks (a, b) and (b, a), a >= b, of X_KK = sym(Dt^{-1} - sum_r P_r)
-// (Alg. 1 step 4 and the symmetrization of Section 2.3).
 // The same as dtile_core for the column slab [b0 + kDSlabW sl, b0 +
 // kDSlabW (sl + 1)) of block (a, b) only (and the matching row slab of block
-// (b, a)), for nodes with many row tiles: with a quarter of the elements per
-// thread, the loads of several row tiles' partials are in flight together.
-template <typename T, bool COH>
-__device__ void dtile_slab(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, int sl, double *smem, const T *Dti, int sld, T *Xkk,
+// (b, a)): with a quarter of the elements per thread, the loads of several row
+// tiles' partials are in flight together, and two LDS slabs are all it needs
+// (rows of the second one a pitch of kDSlabW + 1 apart: it is read by columns).
+constexpr int kDSlabP = kDSlabW + 1;
+template <typename T> __device__ __forceinline__ constexpr int dslab_elems() { return 64 * kDSlabW + 64 * kDSlabP; }
+template <typename T>
+__device__ void dtile_slab(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, int sl, T *smem, const T *Dti, int sld, T *Xkk,
                            int dld) {
-  constexpr int W = kDSlabW, QE = 64 * W / NT;
+  constexpr int W = kDSlabW, WP = kDSlabP, QE = 64 * W / NT;
   constexpr int R = Planes<T>::P == 1 ? 4 : 2;  // row tiles per round trip
   const DevPlan &pl = *cx.pl;
   const int s = nd.s, c = nd.c;
@@ -646,14 +694,14 @@ __device__ void dtile_slab(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, i
   const int a0 = a * 64, b0 = b * 64 + sl * W;
   // element q of a thread: (i, j) = (e % 64, e / 64) of the (a, b) slab, and
   // (j', i') = (e % W, e / W) of the (b, a) slab, e = threadIdx.x + NT q
-  int64_t oab[QE], oba[QE];
+  uint32_t oab[QE], oba[QE];  // byte offsets in an s x s block
   T sab[QE], sba[QE];
 #pragma unroll
   for (int q = 0; q < QE; ++q) {
     const int e = threadIdx.x + NT * q;
     const int ia = e % 64, ja = e / 64, jb = e % W, ib = e / W;
-    oab[q] = ((int64_t)(b0 + ja) * s + a0 + ia) & opaque_mask(a0 + ia < s && b0 + ja < s);
-    oba[q] = ((int64_t)(a0 + ib) * s + b0 + jb) & opaque_mask(b0 + jb < s && a0 + ib < s);
+    oab[q] = ((uint32_t)((b0 + ja) * s + a0 + ia) & opaque_mask32(a0 + ia < s && b0 + ja < s)) * (uint32_t)sizeof(T);
+    oba[q] = ((uint32_t)((a0 + ib) * s + b0 + jb) & opaque_mask32(b0 + jb < s && a0 + ib < s)) * (uint32_t)sizeof(T);
     sab[q] = zero_of<T>();
     sba[q] = zero_of<T>();
   }
@@ -664,44 +712,67 @@ __device__ void dtile_slab(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, i
       const T *pr = cx.Pp + pb + min(r + rr, nr - 1) * ss;
 #pragma unroll
       for (int q = 0; q < QE; ++q) {
-        la[rr][q] = Mem<COH>::ld(pr + oab[q]);
-        lb[rr][q] = Mem<COH>::ld(pr + oba[q]);
+        la[rr][q] = ld_off(pr, oab[q]);
+        lb[rr][q] = ld_off(pr, oba[q]);
       }
     }
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
-      const int64_t m = opaque_mask(r + rr < nr);
+      if (rr > 0 && r + rr >= nr) break;
 #pragma unroll
       for (int q = 0; q < QE; ++q) {
-        sab[q] += masked(la[rr][q], m);
-        sba[q] += masked(lb[rr][q], m);
+        sab[q] += la[rr][q];
+        sba[q] += lb[rr][q];
       }
     }
   }
-  T *Sab = reinterpret_cast<T *>(smem);  // [i + 64 j]
-  T *Sba = Sab + 64 * W;                  // [j' + W i']
-  T *Xs = Sba + 64 * W;                   // [i + 64 j]
+  T *Sab = smem;            // [i + 64 j]
+  T *Sba = Sab + 64 * W;    // [j' + WP i']
 #pragma unroll
   for (int q = 0; q < QE; ++q) {
     const int e = threadIdx.x + NT * q;
     const int ia = e % 64, ja = e / 64, jb = e % W, ib = e / W;
     const int64_t mab = opaque_mask(a0 + ia < s && b0 + ja < s), mba = opaque_mask(b0 + jb < s && a0 + ib < s);
-    const T dab = gload(Dti + (((int64_t)(b0 + ja) * sld + a0 + ia) & mab));
-    const T dba = gload(Dti + (((int64_t)(a0 + ib) * sld + b0 + jb) & mba));
-    Sab[e] = masked(dab - sab[q], mab);
-    Sba[e] = masked(dba - sba[q], mba);
+    const T dab = ld_off(Dti, ((uint32_t)((b0 + ja) * sld + a0 + ia) & (uint32_t)mab) * (uint32_t)sizeof(T));
+    const T dba = ld_off(Dti, ((uint32_t)((a0 + ib) * sld + b0 + jb) & (uint32_t)mba) * (uint32_t)sizeof(T));
+    sab[q] = masked(dab - sab[q], mab);
+    sba[q] = masked(dba - sba[q], mba);
+    Sab[e] = sab[q];
+    Sba[jb + WP * ib] = sba[q];
   }
   lds_barrier();
+  if (uniform(pl.half > 0 ? 1 : 0)) {
+    // LU plan: no symmetrization.  X_KK's slabs into the L half, their
+    // transposes into the U^T half (entry (r, q) = X(q, r)).
+    T *Xu = Xkk + pl.half;
+#pragma unroll
+    for (int q = 0; q < QE; ++q) {
+      const int e = threadIdx.x + NT * q;
+      const int ia = e % 64, ja = e / 64, jb = e % W, ib = e / W;
+      if (a0 + ia < s && b0 + ja < s) {
+        const int64_t o = (int64_t)(b0 + ja) * dld + a0 + ia;
+        gstore(Xkk + o, sab[q]);
+        gstore(Xu + o, Sba[ja + WP * ia]);
+      }
+      if (a != b && b0 + jb < s && a0 + ib < s) {
+        const int64_t o = (int64_t)(a0 + ib) * dld + b0 + jb;
+        gstore(Xkk + o, sba[q]);
+        gstore(Xu + o, Sab[ib + 64 * jb]);
+      }
+    }
+    lds_barrier();
+    return;
+  }
   // x(i, j) = (T[a0 + i, b0 + j] + T[b0 + j, a0 + i]) / 2 (the second term
-  // conjugated in a Hermitian plan)
+  // conjugated in a Hermitian plan), kept in Sab (each thread its own elements)
   const double cs = pl.csign;
 #pragma unroll
   for (int q = 0; q < QE; ++q) {
     const int e = threadIdx.x + NT * q;
     const int ia = e % 64, ja = e / 64;
-    const T x = SOps<T>::scale(0.5, Sab[e] + cj(Sba[ja + W * ia], cs));
-    Xs[e] = x;
-    if (a0 + ia < s && b0 + ja < s) Mem<COH>::st(Xkk + (int64_t)(b0 + ja) * dld + a0 + ia, x);
+    const T x = SOps<T>::scale(0.5, sab[q] + cj(Sba[ja + WP * ia], cs));
+    Sab[e] = x;
+    if (a0 + ia < s && b0 + ja < s) gstore(Xkk + (int64_t)(b0 + ja) * dld + a0 + ia, x);
   }
   lds_barrier();
   if (a != b) {
@@ -709,12 +780,14 @@ __device__ void dtile_slab(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, i
     for (int q = 0; q < QE; ++q) {
       const int e = threadIdx.x + NT * q;
       const int jb = e % W, ib = e / W;
-      if (b0 + jb < s && a0 + ib < s) Mem<COH>::st(Xkk + (int64_t)(a0 + ib) * dld + b0 + jb, cj(Xs[ib + 64 * jb], cs));
+      if (b0 + jb < s && a0 + ib < s) gstore(Xkk + (int64_t)(a0 + ib) * dld + b0 + jb, cj(Sab[ib + 64 * jb], cs));
     }
   }
   lds_barrier();
 }
 
+// Blocks (a, b) and (b, a), a >= b, of X_KK = sym(Dt^{-1} - sum_r P_r)
+// (Alg. 1 step 4 and the symmetrization of Section 2.3).
 template <typename T, bool COH>
 __device__ void do_dtile(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, double *smem) {
   const DevPlan &pl = *cx.pl;
@@ -723,7 +796,7 @@ __device__ void do_dtile(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, dou
   // top block of the normalized panel = Dt^{-1}; top block of the X panel.
   // b carries the slab number + 1 in its high half for slab items.
   if (b >> 16)
-    dtile_slab<T, COH>(cx, nd, a, b & 0xffff, (b >> 16) - 1, smem, cx.Lp + off, ld, cx.Xp + off, ld);
+    dtile_slab<T>(cx, nd, a, b & 0xffff, (b >> 16) - 1, reinterpret_cast<T *>(smem), cx.Lp + off, ld, cx.Xp + off, ld);
   else
     dtile_core<T, COH>(cx, nd, a, b, smem, cx.Lp + off, ld, cx.Xp + off, ld);
 }

@@ -132,6 +132,74 @@ __global__ void __launch_bounds__(NT, 2) k_gemm2_list(const DevPlan *__restrict_
   }
 }
 
+// Rows of the trace for a launch of the list kernels below.
+__device__ __forceinline__ void trace_item(const DevPlan &pl, const int32_t *list, int64_t l, int64_t q, int64_t g,
+                                           int32_t list_pos, int64_t t_start) {
+  if (!pl.trace) return;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t *tr = pl.trace + 8 * ((int64_t)list_pos * pl.batch + g);
+    tr[0] = l * pl.nitems + list[q];
+    tr[1] = blockIdx.x;
+    tr[2] = t_start;
+    tr[3] = t_start;
+    tr[4] = wall_clock64();
+  }
+}
+
+// Diagonal blocks of a depth (the D items, Alg. 1 step 4 and Section 2.3):
+// sums of the row tiles' GEMM-2 partials, no MFMA.  Bound by the partials'
+// traffic, so what counts is the number of loads in flight: slabs of 16
+// columns (an item that is not cut into slabs takes them in turn) need 33 KB
+// (FP64: 17 KB) of LDS and few registers, three (FP64: four) workgroups to a CU
+// (one in k_items_list for complex).  With k_ygather in the same step: 32 complex
+// 30^3 shifts, normalization and traversal, 37.9 -> 34.8 ms; 27-point 64^3, two
+// shifts, 134.6 -> 129.2 ms; LU form 30^3, four shifts, 7.23 -> 6.80 ms.
+template <typename T>
+__global__ void __launch_bounds__(NT, Planes<T>::P == 1 ? 4 : 3) k_diag_list(const DevPlan *__restrict__ plp, const T *Lp, T *Xp, T *Pp,
+                                                     const LRec *recs, const int32_t *list, int32_t count,
+                                                     int32_t list_pos) {
+  const DevPlan &pl = *plp;
+  __shared__ T smem[dslab_elems<T>()];
+  const int64_t g = blockIdx.x;
+  const int64_t l = g / count;
+  const int64_t q = g - l * count;
+  const int64_t t_start = pl.trace ? wall_clock64() : 0;
+  Ctx<T> cx{&pl, Lp + l * pl.panel_elems, Xp + l * pl.panel_elems, Pp + l * pl.part_elems, nullptr, nullptr};
+  const LRec rec = recs[q];
+  const Item it = uniform(rec.it);
+  const NodeInfo nd = uniform(rec.nd);
+  const int ld = nd.s + nd.c, b = it.b & 0xffff, cut = it.b >> 16;
+  const int s0 = cut ? cut - 1 : 0, s1 = cut ? cut : min(64 / kDSlabW, (nd.s - 64 * b + kDSlabW - 1) / kDSlabW);
+  for (int sl = s0; sl < s1; ++sl)
+    dtile_slab<T>(cx, nd, it.a, b, sl, smem, cx.Lp + nd.off, ld, cx.Xp + nd.off, ld);
+  trace_item(pl, list, l, q, g, list_pos, t_start);
+}
+
+// GEMM-1 tiles that gather X_{C,C} on the fly (and the LU form's upper
+// tiles), with the GEMM-2 share of unsplit nodes: bound by the gather's
+// dependent loads, so the kernel holds their stages alone and two workgroups
+// share a CU also for complex (one in k_items_list).
+template <typename T>
+__global__ void __launch_bounds__(NT, 2) k_ygather(const DevPlan *__restrict__ plp, const T *Lp, T *Xp, T *Pp,
+                                                   const LRec *recs, const int32_t *list, int32_t count,
+                                                   int32_t list_pos) {
+  const DevPlan &pl = *plp;
+  __shared__ double smem[tile_doubles<T>()];  // two operand stages fit in one tile
+  __shared__ int64_t rt[128];
+  const int64_t g = blockIdx.x;
+  const int64_t l = g / count;
+  const int64_t q = g - l * count;
+  const int64_t t_start = pl.trace ? wall_clock64() : 0;
+  Ctx<T> cx{&pl, Lp + l * pl.panel_elems, Xp + l * pl.panel_elems, Pp + l * pl.part_elems, nullptr,
+            static_cast<T *>(pl.ypart) + l * pl.y_elems};
+  const LRec rec = recs[q];
+  const Item it = uniform(rec.it);
+  const NodeInfo nd = uniform(rec.nd);
+  do_ygather<T>(cx, nd, it.a, it.b, it.type == ITEM_YU, smem, rt);
+  trace_item(pl, list, l, q, g, list_pos, t_start);
+}
+
 // GEMM-1 tiles of nodes with a dense X_{C,C} buffer (see do_ytile_dense),
 // each followed by its GEMM-2 share when unsplit: dense loaders only, so it
 // fits two workgroups per CU also for complex.
@@ -997,6 +1065,12 @@ static void launch_level(const DevPlan &pl, const DevPlan *dpl, const LaunchAux 
     hipLaunchKernelGGL((pl.half > 0 ? k_gather_list<T, true> : k_gather_list<T, false>),
                        dim3((unsigned)((e - b) * pl.batch)), dim3(NT), 0, st, dpl, Xp, aux.lvl_recs + b,
                        aux.lvl_items + b, e - b, b);
+  else if (aux.lvl_kind[q] == LVL_DIAG)
+    hipLaunchKernelGGL(k_diag_list<T>, dim3((unsigned)((e - b) * pl.batch)), dim3(NT), 0, st, dpl, Lp, Xp, Pp,
+                       aux.lvl_recs + b, aux.lvl_items + b, e - b, b);
+  else if (aux.lvl_kind[q] == LVL_YGATHER)
+    hipLaunchKernelGGL(k_ygather<T>, dim3((unsigned)((e - b) * pl.batch)), dim3(NT), 0, st, dpl, Lp, Xp, Pp,
+                       aux.lvl_recs + b, aux.lvl_items + b, e - b, b);
   else if (aux.lvl_kind[q] == LVL_GEMM2)
     hipLaunchKernelGGL(k_gemm2_list<T>, dim3((unsigned)((e - b) * pl.batch)), dim3(NT), 0, st, dpl, Lp, Xp, Pp,
                        aux.lvl_recs + b, aux.lvl_items + b, e - b, b);

@@ -177,7 +177,8 @@ struct DevPlan {
 
 // Kernels of the level launches.
 enum LevelKind : int32_t {
-  LVL_ITEMS = 0, LVL_TINY = 1, LVL_YDENSE = 2, LVL_PUSH = 3, LVL_Y128 = 4, LVL_GATHER = 5, LVL_GEMM2 = 6
+  LVL_ITEMS = 0, LVL_TINY = 1, LVL_YDENSE = 2, LVL_PUSH = 3, LVL_Y128 = 4, LVL_GATHER = 5, LVL_GEMM2 = 6,
+  LVL_DIAG = 7, LVL_YGATHER = 8
 };
 
 // A tile of the left-looking (push) form, Alg. 2: supernode K pushes into the
