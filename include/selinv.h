@@ -409,9 +409,11 @@ selinv_status selinv_trace(selinv_ctx *h, void *trace_dev);
  *     GEMM-1 item; for type 0, b holds the column tile in its low 16 bits and
  *     the contraction part above them).  Item id i of
  *     matrix l is l * n + i in traces.
- *   which = 1: the adjoint's items in launch order (R1 leaves to root, then
- *     R3 root to leaves); type 0..11 as the BackItemType of the device plan,
- *     12 / 13 = the whole R1 / R3 of a small node in one wavefront.
+ *   which = 1: the adjoint's items by etree depth (R1 leaves to root, then R3
+ *     root to leaves), each formula's items after those it needs; type 0..11
+ *     as the BackItemType of the device plan, 12 / 13 = the whole R1 / R3 of a
+ *     small node in one wavefront.  The launches follow this order but take
+ *     several formulas at once.
  *   which = 2: the forward traversal's launches under the level and push
  *     schedules, in order: {kind (0 work items, 1 single-wavefront nodes,
  *     2 dense-buffer GEMM-1 tiles with their GEMM-2 shares, 3 push tiles,

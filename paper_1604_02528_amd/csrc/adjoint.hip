@@ -19,11 +19,21 @@
 //    Lhatbar = -(X_{C,C} Zbar + Y Tbar)
 //    W[ancestors] += -(Zbar Lhat^T + Lhat Zbar^T) on the lower part of C(K) x C(K)
 //                    (halved on the diagonal), through the ancestor index maps
-//  R2: Dtbar0 = -E Tbar E
+//  R2, all nodes at once: Dtbar0 = -E Tbar E;  N0 = Lhatbar E
 //  R3, root -> leaves, Sbar the adjoint of the trailing Schur complements:
-//    M = Sbar_{C,C} Lhat,  Lb = Lhatbar - 2 M Dt,  N = Lb E
+//    M = Sbar_{C,C} Lhat,  N = (Lhatbar - 2 M Dt) E = N0 - 2 M
 //    Sbar_{C,K} = N / 2,  Sbar_KK = sym(Dtbar0 - Lhat^T (M + N))
 //  Output: Abar = Sbar on A's pattern, doubled off the diagonal.
+//
+// Launches per etree depth: R1 two ({Tbar, X_{C,C} gathers, Zbar}: Zbar takes
+// Tbar straight from W_KK; {Lhatbar, scatter}), R3 two or three ({Sbar_{C,C}
+// gathers}, {M with N, Sbar_{C,K} and the share of Lhat^T (M + N)}, {Sbar_KK}),
+// and one each for the small nodes.  What has no successor in the sweep (R2)
+// runs in two launches between the sweeps, and N needs no product with Dt.
+// With a launch for every formula of every depth (nine), in one kernel at one
+// workgroup a CU for complex, the 200 x 200 GMRF's reverse sweep took 1.47 ms (84
+// launches of 15 us, now 1.05 ms) and four complex 20^3 shifts' 5.11 ms (now 3.54).
+// Bound by the chain of depths: few tiles each, of 20 to 150 us.
 //
 // Every step is a 64 x 64 tile on the MFMA machinery of the forward sweep;
 // the scatter-add uses hardware FP64 atomics (one per real plane; summation
@@ -31,6 +41,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "items.hpp"
 #include "plan.hpp"
@@ -42,17 +53,9 @@ namespace {
 template <typename T> struct BCtx {
   Ctx<T> cx;        // Lp normalized panels, Xp the forward X, Pp partials, Gp dense buffers
   T *W;             // stored-value gradient on F, accumulated in place
-  T *Z, *L, *S;     // panel-layout scratch: Zbar then M; Lhatbar then Lb; Sbar
+  T *Z, *L, *S;     // panel-layout scratch: Zbar; Lhatbar; Sbar (its C rows hold N0 before R3)
   T *TB, *FB, *DB;  // s x s scratch: Tbar; F = Tbar E; Dtbar0
-  const T *DT;      // Dt = L_KK D_K L_KK^T
 };
-
-__device__ __forceinline__ void atomic_add_t(double *p, double v) { unsafeAtomicAdd(p, v); }
-__device__ __forceinline__ void atomic_add_t(cplx *p, cplx v) {
-  double *q = reinterpret_cast<double *>(p);
-  unsafeAtomicAdd(q, v.re);
-  unsafeAtomicAdd(q + 1, v.im);
-}
 
 struct Geo {
   int s, c, ld;
@@ -90,21 +93,51 @@ __device__ void store_tile(const Acc<T> &acc, double *smem, T *dst, int64_t ld, 
   lds_barrier();
 }
 
-template <typename T> using DA = LoadDenseA<T, DenseTK<T>::TK>;
+template <typename T> using DA = LoadDenseAIl<T, DenseTK<T>::TK>;
 template <typename T> using DB = LoadDenseB<T, DenseTK<T>::TK>;
-template <typename T> using DBT = LoadDenseBT<T, DenseTK<T>::TK>;
+
+// B(k, x) = Tbar(k, x) = sym(W_KK): the stored lower triangle of W_KK, halved off the diagonal.
+template <typename T, int TK> struct LoadSymHalf {
+  static constexpr int E = 64 * TK / NT;
+  const T *W;
+  int ld, s, kk, xq;
+  __device__ __forceinline__ LoadSymHalf(const T *W_, int ld_, int s_, int x0)
+      : W(W_), ld(ld_), s(s_), kk(threadIdx.x % TK), xq(x0 + threadIdx.x / TK) {}
+  __device__ __forceinline__ void load_bf(int k0, DVals<T, TK> &v) const {
+    const int k = min(k0 + kk, s - 1);
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      const int x = min(xq + (NT / TK) * m, s - 1);
+      v.v[m] = ld_off(W, (uint32_t)(min(k, x) * ld + max(k, x)) * (uint32_t)sizeof(T));
+    }
+  }
+  __device__ __forceinline__ void store_bf(double *stg, int plane_off, int k0, const DVals<T, TK> &v) const {
+    const int k = k0 + kk;
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      const int e = threadIdx.x + NT * m, x = xq + (NT / TK) * m;
+      const T y = SOps<T>::scale(k == x ? 1.0 : 0.5, masked(v.v[m], opaque_mask(k < s && x < s)));
+#pragma unroll
+      for (int p = 0; p < Planes<T>::P; ++p) stg[(plane_off + p) * TK * PITCH + (e & (TK - 1)) * PITCH + e / TK] = Planes<T>::get(y, p);
+    }
+  }
+};
+
+// acc (+)= A B over k < ke, complex products in the three-chain form
+template <typename T, class LA, class LB>
+__device__ __forceinline__ void gemm_il(int ke, const LA &la, const LB &lb, double *smem, Acc<T> &acc, bool accumulate = false) {
+  gemm_dense_il<T, true>(0, ke, la, lb, smem, acc, accumulate);
+}
 
 // acc = X_{C,C}[tile rows, :] B[:, tile cols] with X_{C,C} gathered from Src (panel
 // layout) or read from the node's dense buffer; B = the c x s bottom block of a
 // panel-layout array Bp.
 template <typename T>
-__device__ void gemm_cc(const BCtx<T> &bx, const Geo &g, const T *Src, const T *Bp, int i0, int j0, double *smem,
-                        int64_t *rt, Acc<T> &acc) {
+__device__ __forceinline__ void gemm_cc(const BCtx<T> &bx, const Geo &g, const T *Src, const T *Bp, int i0, int j0,
+                                        double *smem, int64_t *rt, Acc<T> &acc) {
   const DevPlan &pl = *bx.cx.pl;
   if (uniform(g.goff >= 0 ? 1 : 0)) {
-    DA<T> la{bx.cx.Gp + g.goff, g.ldg, g.c, g.c, i0};
-    DB<T> lb{Bp, g.off, g.ld, g.s, g.c, j0, g.s};
-    gemm_dense<T>(0, g.c, la, lb, smem, acc);
+    gemm_il<T>(g.c, DA<T>(bx.cx.Gp + g.goff, g.ldg, g.c, g.c, i0), DB<T>(Bp, g.off, g.ld, g.s, g.c, j0, g.s), smem, acc);
   } else {
     if (threadIdx.x < 64) {
       const int ig = i0 + threadIdx.x;
@@ -115,6 +148,7 @@ __device__ void gemm_cc(const BCtx<T> &bx, const Geo &g, const T *Src, const T *
     LoadGather<T, false> la{Src, pl.kcol + g.rp, pl.kpos + g.rp, pl.posarr, rt, rt + 64, g.c, g.c, i0};
     LoadPanelK<T, false> lb{Bp, g.off, g.ld, g.s, 0, g.c, j0, g.s};
     gemm_tile<T>(0, g.c, la, lb, smem, acc);
+    lds_barrier();  // the stages are reused
   }
 }
 
@@ -135,8 +169,8 @@ template <typename T>
 __device__ void bi_z(const BCtx<T> &bx, const Geo &g, int a, int b, double *smem) {
   const int i0 = a * 64, j0 = b * 64;
   Acc<T> acc;
-  gemm_dense<T>(0, g.s, DA<T>{bx.cx.Lp + g.off + g.s, g.ld, g.c, g.s, i0},
-                DB<T>{bx.TB + g.sq, 0, g.s, 0, g.s, j0, g.s}, smem, acc);
+  gemm_il<T>(g.s, DA<T>(bx.cx.Lp + g.off + g.s, g.ld, g.c, g.s, i0),
+             LoadSymHalf<T, DenseTK<T>::TK>(bx.W + g.off, g.ld, g.s, j0), smem, acc);
   const T *Wb = bx.W + g.off + g.s;
   store_tile<T>(acc, smem, bx.Z + g.off + g.s, g.ld, i0, j0, g.c, g.s, [&](int64_t q, T v) { return Wb[q] - v; });
 }
@@ -146,8 +180,8 @@ __device__ void bi_l(const BCtx<T> &bx, const Geo &g, int a, int b, double *smem
   const int i0 = a * 64, j0 = b * 64;
   Acc<T> acc;
   gemm_cc<T>(bx, g, bx.cx.Xp, bx.Z, i0, j0, smem, rt, acc);  // X_{C,C} Zbar
-  gemm_dense<T>(0, g.s, DA<T>{bx.cx.Xp + g.off + g.s, g.ld, g.c, g.s, i0},
-                DB<T>{bx.TB + g.sq, 0, g.s, 0, g.s, j0, g.s}, smem, acc, true);  // + Y Tbar
+  gemm_il<T>(g.s, DA<T>(bx.cx.Xp + g.off + g.s, g.ld, g.c, g.s, i0), DB<T>(bx.TB + g.sq, 0, g.s, 0, g.s, j0, g.s), smem,
+             acc, true);  // + Y Tbar
   store_tile<T>(acc, smem, bx.L + g.off + g.s, g.ld, i0, j0, g.c, g.s,
                 [](int64_t, T v) { return SOps<T>::scale(-1.0, v); });
 }
@@ -156,100 +190,95 @@ __device__ void bi_l(const BCtx<T> &bx, const Geo &g, int a, int b, double *smem
 // from the stored-value gradient of the ancestors' entries of X_{C,C}.
 template <typename T>
 __device__ void bi_sc(const BCtx<T> &bx, const Geo &g, int a, int a2, double *smem) {
-  const DevPlan &pl = *bx.cx.pl;
   const int i0 = a * 64, k0 = a2 * 64;
   const T *Zb = bx.Z + g.off + g.s, *Lh = bx.cx.Lp + g.off + g.s;
   Acc<T> acc;
-  gemm_dense<T>(0, g.s, DA<T>{Zb, g.ld, g.c, g.s, i0}, DBT<T>{Lh, g.ld, g.s, k0, g.c}, smem, acc);
-  gemm_dense<T>(0, g.s, DA<T>{Lh, g.ld, g.c, g.s, i0}, DBT<T>{Zb, g.ld, g.s, k0, g.c}, smem, acc, true);
+  gemm_il<T>(g.s, DA<T>(Zb, g.ld, g.c, g.s, i0), DA<T>(Lh, g.ld, g.c, g.s, k0), smem, acc);
+  gemm_il<T>(g.s, DA<T>(Lh, g.ld, g.c, g.s, i0), DA<T>(Zb, g.ld, g.c, g.s, k0), smem, acc, true);
   acc_to_lds<T>(acc, smem);
   lds_barrier();
-  for (int e = threadIdx.x; e < 64 * 64; e += NT) {
-    const int i = e & 63, k = e >> 6;
-    const int ig = i0 + i, kg = k0 + k;
-    if (ig < g.c && kg < g.c && ig >= kg) {
-      const T v = lds_get<T>(smem, i, k);
-      const int64_t addr = gp(pl.kcol)[g.rp + kg] + gp(pl.posarr)[gp(pl.kpos)[g.rp + kg] + ig];
-      atomic_add_t(bx.W + addr, SOps<T>::scale(ig == kg ? -0.5 : -1.0, v));
-    }
-  }
-  lds_barrier();
+  scatter_lower<T>(*bx.cx.pl, g.rp, g.c, i0, k0, smem, bx.W,
+                   [](T v, bool diag) { return SOps<T>::scale(diag ? -0.5 : -1.0, v); });
 }
 
+// F = Tbar E
 template <typename T>
 __device__ void bi_f(const BCtx<T> &bx, const Geo &g, int a, int b, double *smem) {
   const int i0 = a * 64, j0 = b * 64;
   Acc<T> acc;
-  gemm_dense<T>(0, g.s, DA<T>{bx.TB + g.sq, g.s, g.s, g.s, i0}, DB<T>{bx.cx.Lp, g.off, g.ld, 0, g.s, j0, g.s}, smem,
-                acc);
+  gemm_il<T>(g.s, DA<T>(bx.TB + g.sq, g.s, g.s, g.s, i0), DB<T>(bx.cx.Lp, g.off, g.ld, 0, g.s, j0, g.s), smem, acc);
   store_tile<T>(acc, smem, bx.FB + g.sq, g.s, i0, j0, g.s, g.s, [](int64_t, T v) { return v; });
 }
 
+// Dtbar0 = -E F
 template <typename T>
 __device__ void bi_d0(const BCtx<T> &bx, const Geo &g, int a, int b, double *smem) {
   const int i0 = a * 64, j0 = b * 64;
   Acc<T> acc;
-  gemm_dense<T>(0, g.s, DA<T>{bx.cx.Lp + g.off, g.ld, g.s, g.s, i0}, DB<T>{bx.FB + g.sq, 0, g.s, 0, g.s, j0, g.s},
-                smem, acc);
+  gemm_il<T>(g.s, DA<T>(bx.cx.Lp + g.off, g.ld, g.s, g.s, i0), DB<T>(bx.FB + g.sq, 0, g.s, 0, g.s, j0, g.s), smem, acc);
   store_tile<T>(acc, smem, bx.DB + g.sq, g.s, i0, j0, g.s, g.s, [](int64_t, T v) { return SOps<T>::scale(-1.0, v); });
 }
 
+// N0 = Lhatbar E, kept where Sbar_{C,K} will be
 template <typename T>
-__device__ void bi_m(const BCtx<T> &bx, const Geo &g, int a, int b, double *smem, int64_t *rt) {
+__device__ void bi_n0(const BCtx<T> &bx, const Geo &g, int a, int b, double *smem) {
   const int i0 = a * 64, j0 = b * 64;
   Acc<T> acc;
-  gemm_cc<T>(bx, g, bx.S, bx.cx.Lp, i0, j0, smem, rt, acc);  // Sbar_{C,C} Lhat
-  store_tile<T>(acc, smem, bx.Z + g.off + g.s, g.ld, i0, j0, g.c, g.s, [](int64_t, T v) { return v; });
+  gemm_il<T>(g.s, DA<T>(bx.L + g.off + g.s, g.ld, g.c, g.s, i0), DB<T>(bx.cx.Lp, g.off, g.ld, 0, g.s, j0, g.s), smem, acc);
+  store_tile<T>(acc, smem, bx.S + g.off + g.s, g.ld, i0, j0, g.c, g.s, [](int64_t, T v) { return v; });
 }
 
+// M = Sbar_{C,C} Lhat, N = N0 - 2 M, Sbar_{C,K} = N / 2, and the row tile's
+// share of Lhat^T (M + N) into the partial products
 template <typename T>
-__device__ void bi_lb(const BCtx<T> &bx, const Geo &g, int a, int b, double *smem) {
-  const int i0 = a * 64, j0 = b * 64;
-  Acc<T> acc;
-  gemm_dense<T>(0, g.s, DA<T>{bx.Z + g.off + g.s, g.ld, g.c, g.s, i0}, DB<T>{bx.DT + g.sq, 0, g.s, 0, g.s, j0, g.s},
-                smem, acc);
-  T *Lb = bx.L + g.off + g.s;
-  store_tile<T>(acc, smem, Lb, g.ld, i0, j0, g.c, g.s,
-                [&](int64_t q, T v) { return Lb[q] - SOps<T>::scale(2.0, v); });
-}
-
-template <typename T>
-__device__ void bi_n(const BCtx<T> &bx, const Geo &g, int K, int a, int b, double *smem) {
+__device__ void bi_m(const BCtx<T> &bx, const Geo &g, int K, int a, int b, double *smem, int64_t *rt) {
   constexpr int P = Planes<T>::P;
   const int i0 = a * 64, j0 = b * 64;
   Acc<T> acc;
-  gemm_dense<T>(0, g.s, DA<T>{bx.L + g.off + g.s, g.ld, g.c, g.s, i0}, DB<T>{bx.cx.Lp, g.off, g.ld, 0, g.s, j0, g.s},
-                smem, acc);  // N = Lb E
-  store_tile<T>(acc, smem, bx.S + g.off + g.s, g.ld, i0, j0, g.c, g.s,
-                [](int64_t, T v) { return SOps<T>::scale(0.5, v); });
-  // acc <- -(M + N) in the accumulator layout, then the row tile's share of
-  // Lhat^T (M + N) into the partial products
+  gemm_cc<T>(bx, g, bx.S, bx.cx.Lp, i0, j0, smem, rt, acc);
+  acc_to_lds<T>(acc, smem);
+  lds_barrier();
+  T *Sb = bx.S + g.off + g.s;
+#pragma unroll
+  for (int q = 0; q < 64 * 64 / NT; ++q) {
+    const int e = threadIdx.x + NT * q, i = e & 63, j = e >> 6;
+    T u = zero_of<T>();
+    if (i0 + i < g.c && j0 + j < g.s) {
+      T *p = Sb + (int64_t)(j0 + j) * g.ld + i0 + i;
+      const T n0 = gload(p), m = lds_get<T>(smem, i, j);
+      gstore(p, SOps<T>::scale(0.5, n0) - m);
+      u = m - n0;  // -(M + N)
+    }
+    lds_put<T>(smem, i, j, u);
+  }
+  lds_barrier();
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wi = w & 1, wj = w >> 1;
-  const T *M = bx.Z + g.off + g.s;
 #pragma unroll
-  for (int bi = 0; bi < 2; ++bi)
+  for (int p = 0; p < P; ++p)
 #pragma unroll
-    for (int bj = 0; bj < 2; ++bj)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = i0 + 32 * wi + 16 * bi + 4 * v + (lane >> 4);
-        const int j = j0 + 32 * wj + 16 * bj + (lane & 15);
-        const int64_t m = opaque_mask(i < g.c && j < g.s);
-        const T mv = masked(M[((int64_t)j * g.ld + i) & m], m);
+      for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-        for (int p = 0; p < P; ++p)
-          acc.v[p][bi][bj][v] = -(Planes<T>::get(mv, p) + masked(acc.v[p][bi][bj][v], m));
-      }
-  gemm2_partial<T, false>(bx.cx, node_info(*bx.cx.pl, K), a, b, acc, smem);
+        for (int v = 0; v < 4; ++v)
+          acc.v[p][bi][bj][v] = smem[p * 64 * PITCH + (32 * wj + 16 * bj + (lane & 15)) * PITCH + 32 * wi + 16 * bi + 4 * v + (lane >> 4)];
+  lds_barrier();
+  gemm2_partial<T, false, P == 1>(bx.cx, node_info(*bx.cx.pl, K), a, b, acc, smem);
 }
 
-template <typename T>
-__global__ void __launch_bounds__(NT, Planes<T>::P == 1 ? 2 : 1)
-    k_back_items(const DevPlan *__restrict__ plp, const T *panels, const T *x, const T *dt, T *xbar, int32_t first,
-                 int32_t count) {
+// The tile items of one step (a BackStep), each step in a kernel of its own:
+// all of them fit two workgroups a CU, for complex too (one, with all in one
+// kernel).
+template <typename T, int STEP>
+__global__ void __launch_bounds__(NT, STEP == BS_SKK && Planes<T>::P == 1 ? 4 : 2)
+    k_back_items(const DevPlan *__restrict__ plp, const T *panels, const T *x, T *xbar, int32_t first, int32_t count) {
   const DevPlan &pl = *plp;
-  __shared__ double smem[smem_doubles<T>()];
+  // two operand stages of a dense product or one 64 x 64 tile
+  constexpr int kStages = 2 * dense_stage_doubles<T, DenseTK<T>::TK>(), kTile = tile_doubles<T>();
+  __shared__ double smem[STEP == BS_SKK  ? Planes<T>::P * dslab_elems<T>()
+                         : STEP == BS_SG ? kTile
+                                         : kStages > kTile ? kStages : kTile];
   __shared__ int64_t rt[128];
   const int64_t g0 = blockIdx.x;
   const int64_t l = g0 / count;
@@ -265,24 +294,32 @@ __global__ void __launch_bounds__(NT, Planes<T>::P == 1 ? 2 : 1)
   bx.TB = static_cast<T *>(pl.adj_t) + l * sq;
   bx.FB = static_cast<T *>(pl.adj_f) + l * sq;
   bx.DB = static_cast<T *>(pl.adj_d) + l * sq;
-  bx.DT = dt + l * sq;
   const Geo g = geo(pl, it.K);
-  switch (it.type) {
-    case BI_T: bi_t<T>(bx, g, it.a, it.b); break;
-    case BI_G: do_gtile<T>(bx.cx, node_info(pl, it.K), it.a, it.b, smem, rt, bx.cx.Xp); break;
-    case BI_Z: bi_z<T>(bx, g, it.a, it.b, smem); break;
-    case BI_L: bi_l<T>(bx, g, it.a, it.b, smem, rt); break;
-    case BI_SC: bi_sc<T>(bx, g, it.a, it.b, smem); break;
-    case BI_F: bi_f<T>(bx, g, it.a, it.b, smem); break;
-    case BI_D0: bi_d0<T>(bx, g, it.a, it.b, smem); break;
-    case BI_SG: do_gtile<T>(bx.cx, node_info(pl, it.K), it.a, it.b, smem, rt, bx.S); break;
-    case BI_M: bi_m<T>(bx, g, it.a, it.b, smem, rt); break;
-    case BI_LB: bi_lb<T>(bx, g, it.a, it.b, smem); break;
-    case BI_N: bi_n<T>(bx, g, it.K, it.a, it.b, smem); break;
-    case BI_DF:
-      dtile_core<T, false>(bx.cx, node_info(pl, it.K), it.a, it.b, smem, bx.DB + g.sq, g.s, bx.S + g.off, g.ld);
-      break;
-    default: break;
+  if constexpr (STEP == BS_R1Z) {
+    switch (it.type) {
+      case BI_T: bi_t<T>(bx, g, it.a, it.b); break;
+      case BI_G: do_gtile<T, false>(bx.cx, node_info(pl, it.K), it.a, it.b, smem, rt, bx.cx.Xp); break;
+      default: bi_z<T>(bx, g, it.a, it.b, smem); break;
+    }
+  } else if constexpr (STEP == BS_R1L) {
+    if (it.type == BI_L)
+      bi_l<T>(bx, g, it.a, it.b, smem, rt);
+    else
+      bi_sc<T>(bx, g, it.a, it.b, smem);
+  } else if constexpr (STEP == BS_R2) {
+    switch (it.type) {
+      case BI_F: bi_f<T>(bx, g, it.a, it.b, smem); break;
+      case BI_N0: bi_n0<T>(bx, g, it.a, it.b, smem); break;
+      default: bi_d0<T>(bx, g, it.a, it.b, smem); break;
+    }
+  } else if constexpr (STEP == BS_SG) {
+    do_gtile<T, false>(bx.cx, node_info(pl, it.K), it.a, it.b, smem, rt, bx.S);
+  } else if constexpr (STEP == BS_M) {
+    bi_m<T>(bx, g, it.K, it.a, it.b, smem, rt);
+  } else {
+    for (int sl = 0; sl < min(64 / kDSlabW, (g.s - 64 * it.b + kDSlabW - 1) / kDSlabW); ++sl)
+      dtile_slab<T>(bx.cx, node_info(pl, it.K), it.a, it.b, sl, reinterpret_cast<T *>(smem), bx.DB + g.sq, g.s, bx.S + g.off,
+                    g.ld);
   }
 }
 
@@ -338,13 +375,12 @@ __device__ __forceinline__ void tiny_cc_any(const TinyRec &r, const uint32_t *to
 }
 
 template <int MODE, typename T>
-__global__ void __launch_bounds__(64) k_back_tiny(const DevPlan *__restrict__ plp, const T *panels, const T *x,
-                                                  const T *dt, T *xbar, const TinyRec *__restrict__ recs,
-                                                  int32_t count) {
+__global__ void __launch_bounds__(64) k_back_tiny(const DevPlan *__restrict__ plp, const T *panels, const T *x, T *xbar,
+                                                  const TinyRec *__restrict__ recs, int32_t count) {
   constexpr int TC = kTinyC, TS = kTinyS;
   const DevPlan &pl = *plp;
   __shared__ T lh[TS * TC], cb[TS * TC], yb[TS * TC];  // Lhat; Zbar (R1) / M + N (R3); Y Tbar (R1)
-  __shared__ T tb[64], eb[64], fb[64];                  // Tbar (R1) / Dt (R3); E = Dt^{-1}; F (R1) / Dtbar0 (R3)
+  __shared__ T tb[64], eb[64], fb[64];                  // Tbar (R1); E = Dt^{-1}; F (R1) / Dtbar0 (R3)
   const int64_t g0 = blockIdx.x;
   const int64_t l = g0 / count;
   const TinyRec r = recs[g0 - l * count];
@@ -354,7 +390,6 @@ __global__ void __launch_bounds__(64) k_back_tiny(const DevPlan *__restrict__ pl
   T *Lbar = static_cast<T *>(pl.adj_l) + l * pe;
   T *Sb = static_cast<T *>(pl.adj_s) + l * pe;
   T *DB = static_cast<T *>(pl.adj_d) + l * sqe;
-  const T *DT = dt + l * sqe;
   const T zero = zero_of<T>();
   const int s = r.s, c = r.c, lane = threadIdx.x;
   const int64_t ld = s + c, off = r.off, sq = gp(pl.node_sq)[r.K];
@@ -433,31 +468,19 @@ __global__ void __launch_bounds__(64) k_back_tiny(const DevPlan *__restrict__ pl
       DB[sq + (int64_t)y8 * s + x8] = SOps<T>::scale(-1.0, d);
     }
   } else {
-    // Dt, Dtbar0
-    tb[lane] = in_sq ? DT[sq + (int64_t)y8 * s + x8] : zero;
     fb[lane] = in_sq ? DB[sq + (int64_t)y8 * s + x8] : zero;
     __syncthreads();
-    // M = Sbar_{C,C} Lhat;  Lb = Lhatbar - 2 M Dt;  N = Lb E;  Sbar_{C,K} = N / 2
+    // M = Sbar_{C,C} Lhat;  N = Lhatbar E - 2 M;  Sbar_{C,K} = N / 2
     T m[TS];
     tiny_cc_any<T>(r, pl.toff, Sb, lh, m);
     if (lane < c && lane < (c <= 8 ? 8 : c <= 16 ? 16 : 32)) {
       T lb[TS];
 #pragma unroll
-      for (int j = 0; j < TS; ++j) {
-        T v = zero;
-        if (j < s) {
-          T md = zero;
-#pragma unroll
-          for (int k = 0; k < TS; ++k)
-            if (k < s) md += m[k] * tb[j * 8 + k];
-          v = Lbar[off + j * ld + s + lane] - SOps<T>::scale(2.0, md);
-        }
-        lb[j] = v;
-      }
+      for (int j = 0; j < TS; ++j) lb[j] = j < s ? Lbar[off + j * ld + s + lane] : zero;
 #pragma unroll
       for (int j = 0; j < TS; ++j) {
         if (j < s) {
-          T nv = zero;
+          T nv = SOps<T>::scale(-2.0, m[j]);
 #pragma unroll
           for (int k = 0; k < TS; ++k)
             if (k < s) nv += lb[k] * eb[j * 8 + k];
@@ -497,19 +520,30 @@ __global__ void k_abar(const DevPlan *__restrict__ plp, const T *x, const T *wlo
 
 template <typename T>
 hipError_t backward_impl(const DevPlan &pl, const DevPlan *dpl, const LaunchAux &aux, const void *panels,
-                         const void *x, const void *dt, void *xbar, const void *wlogdet, void *abar, hipStream_t st) {
-  const T *P = static_cast<const T *>(panels), *X = static_cast<const T *>(x), *D = static_cast<const T *>(dt);
+                         const void *x, void *xbar, const void *wlogdet, void *abar, hipStream_t st) {
+  const T *P = static_cast<const T *>(panels), *X = static_cast<const T *>(x);
   T *Wb = static_cast<T *>(xbar);
   for (int q = 0; q < aux.nblaunch; ++q) {
-    const int4 bl = aux.blaunch[q];  // {kind, first, count}: 0 items, 1 small-node R1, 2 small-node R3
+    const int4 bl = aux.blaunch[q];  // {BackStep, first, count}
     if (bl.z <= 0) continue;
     const dim3 grid((unsigned)(bl.z * pl.batch));
-    if (bl.x == 0)
-      hipLaunchKernelGGL(k_back_items<T>, grid, dim3(NT), 0, st, dpl, P, X, D, Wb, bl.y, bl.z);
-    else if (bl.x == 1)
-      hipLaunchKernelGGL((k_back_tiny<1, T>), grid, dim3(64), 0, st, dpl, P, X, D, Wb, aux.tiny + bl.y, bl.z);
-    else
-      hipLaunchKernelGGL((k_back_tiny<2, T>), grid, dim3(64), 0, st, dpl, P, X, D, Wb, aux.tiny + bl.y, bl.z);
+    auto items = [&](auto step) {
+      hipLaunchKernelGGL((k_back_items<T, decltype(step)::value>), grid, dim3(NT), 0, st, dpl, P, X, Wb, bl.y, bl.z);
+    };
+    switch (bl.x) {
+      case BS_TINY_R1:
+        hipLaunchKernelGGL((k_back_tiny<1, T>), grid, dim3(64), 0, st, dpl, P, X, Wb, aux.tiny + bl.y, bl.z);
+        break;
+      case BS_TINY_R3:
+        hipLaunchKernelGGL((k_back_tiny<2, T>), grid, dim3(64), 0, st, dpl, P, X, Wb, aux.tiny + bl.y, bl.z);
+        break;
+      case BS_R1Z: items(std::integral_constant<int, BS_R1Z>{}); break;
+      case BS_R1L: items(std::integral_constant<int, BS_R1L>{}); break;
+      case BS_R2: items(std::integral_constant<int, BS_R2>{}); break;
+      case BS_SG: items(std::integral_constant<int, BS_SG>{}); break;
+      case BS_M: items(std::integral_constant<int, BS_M>{}); break;
+      default: items(std::integral_constant<int, BS_SKK>{}); break;
+    }
   }
   const int64_t total = pl.batch * pl.nnzA;
   unsigned grid = (unsigned)((total + 255) / 256);
@@ -524,9 +558,10 @@ hipError_t backward_impl(const DevPlan &pl, const DevPlan *dpl, const LaunchAux 
 
 hipError_t launch_backward(const DevPlan &pl, const DevPlan *dpl, const LaunchAux &aux, bool cplx_, const void *panels,
                            const void *x, const void *dt, void *xbar, const void *wlogdet, void *abar, hipStream_t st) {
+  (void)dt;  // N = Lhatbar E - 2 M needs no product with Dt
   if (!pl.adj_s) return hipErrorNotSupported;
-  return cplx_ ? backward_impl<cplx>(pl, dpl, aux, panels, x, dt, xbar, wlogdet, abar, st)
-               : backward_impl<double>(pl, dpl, aux, panels, x, dt, xbar, wlogdet, abar, st);
+  return cplx_ ? backward_impl<cplx>(pl, dpl, aux, panels, x, xbar, wlogdet, abar, st)
+               : backward_impl<double>(pl, dpl, aux, panels, x, xbar, wlogdet, abar, st);
 }
 
 }  // namespace selinv

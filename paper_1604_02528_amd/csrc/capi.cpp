@@ -369,6 +369,27 @@ int64_t subtree_groups(const Symbolic &S, HostPlan &H) {
   return S.sdepth[front[0]];
 }
 
+// The adjoint's items of one type for node K (see BackItemType).
+void back_items(const HostPlan &H, int64_t K, int32_t type, std::vector<Item> &out) {
+  const int32_t s = H.node_s[K], c = H.node_c[K];
+  const int32_t nb = (s + kTileN - 1) / kTileN, nr = (c + kTileM - 1) / kTileM;
+  auto block = [&](int32_t na, bool lower, int32_t ncol) {
+    for (int32_t a = 0; a < na; ++a)
+      for (int32_t b = 0; b < (lower ? a + 1 : ncol); ++b) out.push_back(Item{(int32_t)K, type, a, b});
+  };
+  switch (type) {
+    case BI_T: case BI_F: case BI_D0: block(nb, false, nb); break;
+    case BI_DF: block(nb, true, 0); break;
+    case BI_G: case BI_SG:
+      if (H.node_goff[K] >= 0) block(nr, true, 0);
+      break;
+    case BI_SC: block(nr, true, 0); break;
+    default:  // c x s tiles
+      for (int32_t b = 0; b < nb; ++b)
+        for (int32_t a = 0; a < nr; ++a) out.push_back(Item{(int32_t)K, type, a, b});
+  }
+}
+
 void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t dense_min_c, int64_t dense_max_bytes,
                 int64_t split_min_k, int sched, const TuneTable *tt, bool adjoint, bool herm, bool lu, HostPlan &H) {
   const int64_t ns = S.nsuper();
@@ -796,70 +817,47 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
     n.yoff = H.node_yoff[K];
     H.lvl_recs[q] = LRec{it, n};
   }
-  // adjoint items: R1 leaves -> root (deepest level first), then R3 root -> leaves
+  // adjoint launches (see adjoint.hip): R1 leaves -> root (deepest level
+  // first), R2 for all nodes, then R3 root -> leaves
   H.bitems.clear();
   H.blaunch.clear();
   {
-    auto is_tiny = adj_tiny;
-    int32_t bstart = 0;
     std::vector<std::vector<int64_t>> bydepth(S.depth);
-    for (int64_t K = 0; K < ns; ++K) bydepth[S.sdepth[K]].push_back(K);
-    auto emit = [&](int64_t K, int32_t type) {
-      const int32_t s = H.node_s[K], c = H.node_c[K];
-      const int32_t nb = (s + kTileN - 1) / kTileN, nr = (c + kTileM - 1) / kTileM;
-      const bool dense = H.node_goff[K] >= 0;
-      switch (type) {
-        case BI_T: case BI_F: case BI_D0:
-          for (int32_t a = 0; a < nb; ++a)
-            for (int32_t b = 0; b < nb; ++b) H.bitems.push_back(Item{(int32_t)K, type, a, b});
-          break;
-        case BI_DF:
-          for (int32_t a = 0; a < nb; ++a)
-            for (int32_t b = 0; b <= a; ++b) H.bitems.push_back(Item{(int32_t)K, type, a, b});
-          break;
-        case BI_G: case BI_SG:
-          if (dense)
-            for (int32_t a = 0; a < nr; ++a)
-              for (int32_t b = 0; b <= a; ++b) H.bitems.push_back(Item{(int32_t)K, type, a, b});
-          break;
-        case BI_SC:
-          for (int32_t a = 0; a < nr; ++a)
-            for (int32_t b = 0; b <= a; ++b) H.bitems.push_back(Item{(int32_t)K, type, a, b});
-          break;
-        default:  // c x s tiles
-          for (int32_t b = 0; b < nb; ++b)
-            for (int32_t a = 0; a < nr; ++a) H.bitems.push_back(Item{(int32_t)K, type, a, b});
-      }
-    };
-    auto close = [&]() {
+    for (int64_t K = 0; K < ns; ++K)
+      if (!adj_tiny(K)) bydepth[S.sdepth[K]].push_back(K);
+    int32_t bstart = 0;
+    auto close = [&](int32_t step) {
       const int32_t n = (int32_t)H.bitems.size() - bstart;
-      if (n > 0) H.blaunch.push_back(int4{0, bstart, n, 0});
+      if (n > 0) H.blaunch.push_back(int4{step, bstart, n, 0});
       bstart = (int32_t)H.bitems.size();
     };
-    auto tiny_launch = [&](int64_t d, int32_t kind) {
-      const int32_t n = H.tiny_dadj[d] - H.tiny_dptr[d];
-      if (n > 0) H.blaunch.push_back(int4{kind, H.tiny_dptr[d], n, 0});
+    auto depth_step = [&](int64_t d, int32_t step, std::initializer_list<int32_t> types) {
+      for (int32_t t : types)
+        for (int64_t K : bydepth[d]) back_items(H, K, t, H.bitems);
+      close(step);
     };
-    static const int32_t r1[kBackR1Phases][3] = {{BI_T, BI_G, -1}, {BI_Z, -1, -1}, {BI_L, BI_SC, BI_F}, {BI_D0, -1, -1}};
-    static const int32_t r3[kBackR3Phases][3] = {{BI_SG, -1, -1}, {BI_M, -1, -1}, {BI_LB, -1, -1}, {BI_N, -1, -1},
-                                                 {BI_DF, -1, -1}};
+    auto tiny_launch = [&](int64_t d, int32_t step) {
+      const int32_t n = H.tiny_dadj[d] - H.tiny_dptr[d];
+      if (n > 0) H.blaunch.push_back(int4{step, H.tiny_dptr[d], n, 0});
+    };
     for (int64_t d = S.depth - 1; d >= 0; --d) {
-      for (int ph = 0; ph < kBackR1Phases; ++ph) {
-        for (int64_t K : bydepth[d])
-          if (!is_tiny(K))
-            for (int q = 0; q < 3 && r1[ph][q] >= 0; ++q) emit(K, r1[ph][q]);
-        close();
-      }
-      tiny_launch(d, 1);
+      depth_step(d, BS_R1Z, {BI_G, BI_Z, BI_T});
+      depth_step(d, BS_R1L, {BI_L, BI_SC});
+      tiny_launch(d, BS_TINY_R1);
+    }
+    for (int ph = 0; ph < 2; ++ph) {
+      for (int64_t d = 0; d < S.depth; ++d)
+        for (int64_t K : bydepth[d]) {
+          if (ph == 0) back_items(H, K, BI_N0, H.bitems);
+          back_items(H, K, ph == 0 ? BI_F : BI_D0, H.bitems);
+        }
+      close(BS_R2);
     }
     for (int64_t d = 0; d < S.depth; ++d) {
-      for (int ph = 0; ph < kBackR3Phases; ++ph) {
-        for (int64_t K : bydepth[d])
-          if (!is_tiny(K))
-            for (int q = 0; q < 3 && r3[ph][q] >= 0; ++q) emit(K, r3[ph][q]);
-        close();
-      }
-      tiny_launch(d, 2);
+      depth_step(d, BS_SG, {BI_SG});
+      depth_step(d, BS_M, {BI_M});
+      depth_step(d, BS_SKK, {BI_DF});
+      tiny_launch(d, BS_TINY_R3);
     }
   }
   // normalization work lists
@@ -2207,18 +2205,28 @@ selinv_status selinv_items(const selinv_ctx *hc, int32_t which, const int32_t **
     return set_err(h, SELINV_EINVAL,
                    "selinv_items: which must be 0 (forward), 1 (adjoint), 2 (level launches), 3 (normalization "
                    "chunks) or 4 (subtree group ranges)");
-  // the adjoint's launches in order, a small-node launch expanded into one
-  // row per node
+  // the adjoint's steps, depth by depth, one row per item of each formula
+  // (one per node for the small ones)
   if (h->bseq.empty()) {
     const HostPlan &H = h->H;
-    for (const int4 &bl : H.blaunch) {
-      if (bl.x == 0) {
-        for (int32_t q = bl.y; q < bl.y + bl.z; ++q) h->bseq.push_back(H.bitems[q]);
-      } else {
-        for (int32_t q = bl.y; q < bl.y + bl.z; ++q)
-          h->bseq.push_back(Item{H.tiny[q].K, bl.x == 1 ? BI_TINY_R1 : BI_TINY_R3, 0, 0});
-      }
-    }
+    const Symbolic &S = h->S;
+    static const int32_t r1[kBackR1Phases][3] = {{BI_T, BI_G, -1}, {BI_Z, -1, -1}, {BI_L, BI_SC, BI_F}, {BI_D0, -1, -1}};
+    static const int32_t r3[kBackR3Phases][3] = {{BI_SG, -1, -1}, {BI_M, -1, -1}, {BI_LB, -1, -1}, {BI_N, -1, -1},
+                                                 {BI_DF, -1, -1}};
+    std::vector<uint8_t> small(S.nsuper(), 0);
+    for (int64_t d = 0; d < S.depth; ++d)
+      for (int32_t q = H.tiny_dptr[d]; q < H.tiny_dadj[d]; ++q) small[H.tiny[q].K] = 1;
+    std::vector<std::vector<int64_t>> bydepth(S.depth);
+    for (int64_t K = 0; K < S.nsuper(); ++K)
+      if (!small[K]) bydepth[S.sdepth[K]].push_back(K);
+    auto depth_rows = [&](int64_t d, const int32_t(*types)[3], int phases, int32_t tiny) {
+      for (int ph = 0; ph < phases; ++ph)
+        for (int64_t K : bydepth[d])
+          for (int q = 0; q < 3 && types[ph][q] >= 0; ++q) back_items(H, K, types[ph][q], h->bseq);
+      for (int32_t q = H.tiny_dptr[d]; q < H.tiny_dadj[d]; ++q) h->bseq.push_back(Item{H.tiny[q].K, tiny, 0, 0});
+    };
+    for (int64_t d = S.depth - 1; d >= 0; --d) depth_rows(d, r1, kBackR1Phases, BI_TINY_R1);
+    for (int64_t d = 0; d < S.depth; ++d) depth_rows(d, r3, kBackR3Phases, BI_TINY_R3);
   }
   *items = reinterpret_cast<const int32_t *>(h->bseq.data());
   *n = (int64_t)h->bseq.size();

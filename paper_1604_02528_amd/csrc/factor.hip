@@ -49,13 +49,6 @@ __device__ __forceinline__ bool finite_nonzero(cplx d) {
   return (d.re != 0.0 || d.im != 0.0) && isfinite(d.re) && isfinite(d.im);
 }
 
-__device__ __forceinline__ void atomic_add_t(double *p, double v) { unsafeAtomicAdd(p, v); }
-__device__ __forceinline__ void atomic_add_t(cplx *p, cplx v) {
-  double *q = reinterpret_cast<double *>(p);
-  unsafeAtomicAdd(q, v.re);
-  unsafeAtomicAdd(q + 1, v.im);
-}
-
 // ---------------------------------------------------------------------------
 // 16 x 16 blocks.  A block of S (rows i of one 16-row strip, columns j of
 // another) is held by one wavefront as register v of lane l = S(l % 16, 4 v +
@@ -750,29 +743,14 @@ __global__ void __launch_bounds__(NT, 2)
 // Updates L D L^T on 64 x 64 tiles.
 // ---------------------------------------------------------------------------
 
-// A(i, k) = M[k ld + i0 + i] for i0 + i < rows, k < kend, with the branch-free
-// load and store forms of gemm_dense_il.
-template <typename T, int TK> struct FacLoadA : LoadDenseA<T, TK> {
-  using LoadDenseA<T, TK>::LoadDenseA;
-  static constexpr int E = LoadDenseA<T, TK>::E;
-  __device__ __forceinline__ void load_bf(int k0, DVals<T, TK> &v) const { this->load(k0, v); }
-  __device__ __forceinline__ void store_bf(double *stg, int plane_off, int k0, const DVals<T, TK> &v) const {
-#pragma unroll
-    for (int m = 0; m < E; ++m) {
-      const T x = masked(v.v[m], this->mask(k0, m));
-#pragma unroll
-      for (int p = 0; p < Planes<T>::P; ++p) stg[(plane_off + p) * TK * PITCH + this->slot(k0, m)] = Planes<T>::get(x, p);
-    }
-  }
-};
 // B(k, x) = D_k M[k ld + i0 + x] (M conjugated if Hermitian): the pivots come
 // from LDS and multiply the loaded values where these go to LDS, so that the
 // loads stay in flight (a product at the load site waits for each of them).
-template <typename T, int TK> struct FacLoadB : FacLoadA<T, TK> {
+template <typename T, int TK> struct FacLoadB : LoadDenseAIl<T, TK> {
   const T *D;  // LDS
   double cs;
   __device__ __forceinline__ FacLoadB(const T *M, int ld, int rows, int kend, int x0, const T *D_, double cs_)
-      : FacLoadA<T, TK>(M, ld, rows, kend, x0), D(D_), cs(cs_) {}
+      : LoadDenseAIl<T, TK>(M, ld, rows, kend, x0), D(D_), cs(cs_) {}
   __device__ __forceinline__ void store_bf(double *stg, int plane_off, int k0, const DVals<T, TK> &v) const {
 #pragma unroll
     for (int m = 0; m < this->E; ++m) {
@@ -828,7 +806,7 @@ __global__ void __launch_bounds__(NT, 2)
   }
   for (int k = threadIdx.x; k < s; k += NT) dls[k] = gload(Q + (int64_t)k * (ld + 1));
   lds_barrier();
-  FacLoadA<T, TK> la(Q + s, ld, c, s, i0);
+  LoadDenseAIl<T, TK> la(Q + s, ld, c, s, i0);
   FacLoadB<T, TK> lb(Q + s, ld, nc, s, k0, dls, pl.csign);
   Acc<T> acc;
   gemm_dense_il<T, true>(0, s, la, lb, smem, acc);
@@ -850,21 +828,7 @@ __global__ void __launch_bounds__(NT, 2)
       if (ig < c && kg < nc && ig >= kg) gstore(R + (int64_t)kg * ld + ig, v[q] - lds_get<T>(smem, i, w + 4 * q));
     }
   } else {
-    // the positions of all of a thread's elements first, then the adds
-    int32_t pos[QN];
-    int64_t col[QN];
-#pragma unroll
-    for (int q = 0; q < QN; ++q) {
-      const int kg = k0 + w + 4 * q, kc = min(kg, c - 1);
-      col[q] = uniform64(gp(pl.kcol)[rp + kc]);
-      pos[q] = gp(pl.posarr)[(gp(pl.kpos)[rp + kc] + ig) & opaque_mask(ig < c && kg < c && ig >= kg)];
-    }
-#pragma unroll
-    for (int q = 0; q < QN; ++q) {
-      const int kg = k0 + w + 4 * q;
-      if (ig < c && kg < c && ig >= kg)
-        atomic_add_t(Pl + col[q] + pos[q], SOps<T>::scale(-1.0, lds_get<T>(smem, i, w + 4 * q)));
-    }
+    scatter_lower<T>(pl, rp, c, i0, k0, smem, Pl, [](T v, bool) { return SOps<T>::scale(-1.0, v); });
   }
 }
 

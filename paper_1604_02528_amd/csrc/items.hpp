@@ -69,6 +69,37 @@ __device__ __forceinline__ NodeInfo node_info(const DevPlan &pl, int K) {
   return n;
 }
 
+__device__ __forceinline__ void atomic_add_t(double *p, double v) { unsafeAtomicAdd(p, v); }
+__device__ __forceinline__ void atomic_add_t(cplx *p, cplx v) {
+  double *q = reinterpret_cast<double *>(p);
+  unsafeAtomicAdd(q, v.re);
+  unsafeAtomicAdd(q + 1, v.im);
+}
+
+// The 64 x 64 tile in LDS (rows i0.., columns k0.. of C(K) x C(K), lower part)
+// added to the ancestors' entries of S_{C,C} in a panel-layout array, with
+// f(value, diagonal) applied: the positions of all of a thread's elements
+// first, then the adds.
+template <typename T, class F>
+__device__ __forceinline__ void scatter_lower(const DevPlan &pl, int64_t rp, int c, int i0, int k0, const double *smem,
+                                              T *base, F f) {
+  constexpr int Q = 64 * 64 / NT;
+  const int i = threadIdx.x & 63, w = uniform((int)(threadIdx.x >> 6)), ig = i0 + i;
+  int32_t pos[Q];
+  int64_t col[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int kg = k0 + w + 4 * q, kc = min(kg, c - 1);
+    col[q] = uniform64(gp(pl.kcol)[rp + kc]);
+    pos[q] = gp(pl.posarr)[(gp(pl.kpos)[rp + kc] + ig) & opaque_mask(ig < c && kg < c && ig >= kg)];
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int kg = k0 + w + 4 * q;
+    if (ig < c && kg < c && ig >= kg) atomic_add_t(base + col[q] + pos[q], f(lds_get<T>(smem, i, w + 4 * q), ig == kg));
+  }
+}
+
 // Block (a, b), a >= b, of X_{C,C} for a node with a dense buffer G (column
 // major, leading dimension ldg): element (i, k), i >= k, is the lower-part
 // entry Src[kcol[k] + posarr[kpos[k] + i]] of the ancestor owning column k

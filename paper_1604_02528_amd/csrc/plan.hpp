@@ -49,7 +49,9 @@ __host__ __device__ constexpr int item_phase(int type) {
 }
 
 // Work items of the adjoint (reverse) sweep; see adjoint.hip.  R1 runs
-// leaves -> root, R3 root -> leaves; each is listed by etree depth and phase.
+// leaves -> root, R3 root -> leaves.  selinv_items(which = 1) lists them by
+// formula (BI_LB and BI_N: the two halves of N = (Lhatbar - 2 M Dt) E); the
+// launches run BI_N0 for all nodes between the sweeps and the rest of N in BI_M.
 enum BackItemType : int32_t {
   BI_T = 0,   // R1 phase 0: Tbar = sym(Xbar_KK) from the stored lower triangle
   BI_G = 1,   // R1 phase 0: dense X_{C,C} gather block (nodes with a dense buffer)
@@ -59,15 +61,28 @@ enum BackItemType : int32_t {
   BI_F = 5,   // R1 phase 2: F = Tbar E   (E = Dt^{-1})
   BI_D0 = 6,  // R1 phase 3: Dtbar0 = -E F
   BI_SG = 7,  // R3 phase 0: dense Sbar_{C,C} gather block
-  BI_M = 8,   // R3 phase 1: M = Sbar_{C,C} Lhat
-  BI_LB = 9,  // R3 phase 2: Lb = Lhatbar - 2 M Dt
-  BI_N = 10,  // R3 phase 3: N = Lb E; Sbar_{C,K} = N / 2; GEMM-2 share of Lhat^T (M + N)
+  BI_M = 8,   // R3 phase 1: M = Sbar_{C,C} Lhat (launches: and N = N0 - 2 M, Sbar_{C,K} = N / 2, its share of Lhat^T (M + N))
+  BI_LB = 9,  // R3 phase 2: Lhatbar - 2 M Dt (listed only)
+  BI_N = 10,  // R3 phase 3: N, Sbar_{C,K} = N / 2, GEMM-2 share of Lhat^T (M + N) (listed only)
   BI_DF = 11, // R3 phase 4: Sbar_KK = sym(Dtbar0 - Lhat^T (M + N))
   BI_TINY_R1 = 12,  // (selinv_items only) all of R1 for a small node, one wavefront
-  BI_TINY_R3 = 13   // (selinv_items only) all of R3 for a small node, one wavefront
+  BI_TINY_R3 = 13,  // (selinv_items only) all of R3 for a small node, one wavefront
+  BI_N0 = 14        // (launches only) N0 = Lhatbar E
 };
 constexpr int kBackR1Phases = 4;
 constexpr int kBackR3Phases = 5;
+
+// Launches of the adjoint.
+enum BackStep : int32_t {
+  BS_R1Z = 0,      // T, G, Z of a depth
+  BS_TINY_R1 = 1,
+  BS_TINY_R3 = 2,
+  BS_R1L = 3,      // L, SC of a depth
+  BS_R2 = 4,       // F, N0 of all nodes; then D0 of all nodes
+  BS_SG = 5,       // SG of a depth
+  BS_M = 6,        // M of a depth
+  BS_SKK = 7       // DF of a depth
+};
 
 constexpr int kTileM = 64;   // GEMM-1 rows per item
 constexpr int kTileN = 64;   // columns per item (of s)
@@ -217,8 +232,8 @@ struct LaunchAux {
                             // start at lvl_tiny[q]): {K, ITEM_Y, row tile, column tile | part << 16}
   const TinyRec *tiny;      // single-wavefront node records, in launch order
   int32_t nlvl;
-  const int4 *blaunch;        // host array: adjoint launches {kind, first, count, 0} in order; kind 0 =
-                              // bitems [first, first + count), 1 / 2 = R1 / R3 of small-node records
+  const int4 *blaunch;        // host array: adjoint launches {BackStep, first, count, 0} in order: bitems
+                              // [first, first + count), or small-node records (BS_TINY_R1, BS_TINY_R3)
   int32_t nblaunch;
   // Top of the tree: the level launches of the depths whose tiles fill at
   // most a quarter of the GPU (0: none).

@@ -882,6 +882,22 @@ __device__ __forceinline__ void gemm_dense(int kb, int ke, const LA &la, const L
 }
 
 
+// LoadDenseA with the branch-free forms of gemm_dense_il.  The same loader
+// serves as B operand: B(k, x) = G[k ldg + i0 + x], a row-major view.
+template <typename T, int TK> struct LoadDenseAIl : LoadDenseA<T, TK> {
+  using LoadDenseA<T, TK>::LoadDenseA;
+  static constexpr int E = LoadDenseA<T, TK>::E;
+  __device__ __forceinline__ void load_bf(int k0, DVals<T, TK> &v) const { this->load(k0, v); }
+  __device__ __forceinline__ void store_bf(double *stg, int plane_off, int k0, const DVals<T, TK> &v) const {
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      const T x = masked(v.v[m], this->mask(k0, m));
+#pragma unroll
+      for (int p = 0; p < Planes<T>::P; ++p) stg[(plane_off + p) * TK * PITCH + this->slot(k0, m)] = Planes<T>::get(x, p);
+    }
+  }
+};
+
 // Issue order inside one step of gemm_dense_il: each of its NM MFMAs is
 // followed by one of the NW LDS stores of the next stage, then by one of the
 // NL global loads of the stage after it (the stage's own LDS reads are left
@@ -903,14 +919,15 @@ __device__ __forceinline__ void interleave_stage() {
 // stage (into the other buffer) and the global loads of the stage after
 // that, so the stores and loads can issue in the shadow of the MFMAs instead
 // of between them; one barrier per stage.  Same operands and results as
-// gemm_dense (accumulate = false).
+// gemm_dense.
 template <typename T, bool G3, class LA, class LB>
-__device__ __forceinline__ void gemm_dense_il(int kb, int ke, const LA &la, const LB &lb, double *smem, Acc<T> &acc) {
+__device__ __forceinline__ void gemm_dense_il(int kb, int ke, const LA &la, const LB &lb, double *smem, Acc<T> &acc,
+                                              bool accumulate = false) {
   constexpr int TK = DenseTK<T>::TK, P = Planes<T>::P;
   constexpr bool M3 = G3 && P == 2;
   constexpr int SD = dense_stage_doubles<T, TK>();
   using V = DVals<T, TK>;
-  acc_zero<T>(acc);
+  if (!accumulate) acc_zero<T>(acc);
   const int nk = (ke - kb + TK - 1) / TK;
   if (nk <= 0) return;
   Acc3M a3;
