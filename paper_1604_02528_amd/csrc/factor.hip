@@ -29,9 +29,9 @@
 
 #include <cmath>
 #include <cstdint>
-#include <type_traits>
 #include <utility>
 
+#include "blk16.hpp"
 #include "items.hpp"
 #include "plan.hpp"
 #include "scalar.hpp"
@@ -49,107 +49,6 @@ __device__ __forceinline__ bool finite_nonzero(cplx d) {
   return (d.re != 0.0 || d.im != 0.0) && isfinite(d.re) && isfinite(d.im);
 }
 
-// ---------------------------------------------------------------------------
-// 16 x 16 blocks.  A block of S (rows i of one 16-row strip, columns j of
-// another) is held by one wavefront as register v of lane l = S(l % 16, 4 v +
-// l / 16): its transpose in the MFMA result layout, which is the A-operand
-// layout of the block and the B-operand layout of its transpose at the same
-// time.  Everything below works on transposed blocks, so that a product's
-// result is the next product's operand without any data movement:
-//   W^T = M S^T (M = L_kk^{-1}, W = L D),  L^T = D^{-1} W^T,
-//   S(i, j)^T -= L(j, k) W(i, k)^T          (M and L(j, k) conjugated if Hermitian)
-// ---------------------------------------------------------------------------
-template <typename T> struct Blk {
-  d4 p[Planes<T>::P];
-};
-
-__device__ __forceinline__ double blk_get(const Blk<double> &b, int v) { return b.p[0][v]; }
-__device__ __forceinline__ cplx blk_get(const Blk<cplx> &b, int v) { return cplx{b.p[0][v], b.p[1][v]}; }
-__device__ __forceinline__ void blk_set(Blk<double> &b, int v, double x) { b.p[0][v] = x; }
-__device__ __forceinline__ void blk_set(Blk<cplx> &b, int v, cplx x) {
-  b.p[0][v] = x.re;
-  b.p[1][v] = x.im;
-}
-template <typename T> __device__ __forceinline__ Blk<T> blk_zero() {
-  Blk<T> b;
-#pragma unroll
-  for (int p = 0; p < Planes<T>::P; ++p) b.p[p] = d4{0.0, 0.0, 0.0, 0.0};
-  return b;
-}
-
-// acc += A B for 16 x 16 operands in the layout above, over the first 4 nv
-// contraction indices (complex: four real products)
-template <typename T>
-__device__ __forceinline__ void blk_mma(const Blk<T> &a, const Blk<T> &b, Blk<T> &acc, int nv = 4) {
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    if (v < nv) {
-      acc.p[0] = mfma16(a.p[0][v], b.p[0][v], acc.p[0]);
-      if constexpr (Planes<T>::P == 2) {
-        acc.p[1] = mfma16(a.p[0][v], b.p[1][v], acc.p[1]);
-        acc.p[0] = mfma16(-a.p[1][v], b.p[1][v], acc.p[0]);
-        acc.p[1] = mfma16(a.p[1][v], b.p[0][v], acc.p[1]);
-      }
-    }
-  }
-}
-
-// A block in LDS, plane p at q[p * stride]: element v * 64 + lane, so that
-// reads and writes of a register are contiguous.
-template <typename T> __device__ __forceinline__ Blk<T> blk_from_lds(const double *q, int stride) {
-  const int lane = threadIdx.x & 63;
-  Blk<T> b;
-#pragma unroll
-  for (int p = 0; p < Planes<T>::P; ++p)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) b.p[p][v] = q[p * stride + v * 64 + lane];
-  return b;
-}
-template <typename T> __device__ __forceinline__ void blk_to_lds(const Blk<T> &b, double *q, int stride) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int p = 0; p < Planes<T>::P; ++p)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) q[p * stride + v * 64 + lane] = b.p[p][v];
-}
-
-__device__ __forceinline__ void st_off(double *base, uint32_t b, double v) {
-  *reinterpret_cast<SELINV_GAS double *>(reinterpret_cast<SELINV_GAS char *>(gw(base)) + b) = v;
-}
-__device__ __forceinline__ void st_off(cplx *base, uint32_t b, cplx v) {
-  SELINV_GAS char *q = reinterpret_cast<SELINV_GAS char *>(gw(base)) + b;
-  *reinterpret_cast<SELINV_GAS double *>(q) = v.re;
-  *reinterpret_cast<SELINV_GAS double *>(q + 8) = v.im;
-}
-// This lane's row of a block, opaque: the addresses below are cheap to form
-// and cost registers when kept from a block's load to its store.
-__device__ __forceinline__ int blk_row() {
-  int r = threadIdx.x & 15;
-  asm("" : "+v"(r));
-  return r;
-}
-// Rows [0, rows) and columns [0, cols) of a 16 x 16 block at Q (wave-uniform,
-// leading dimension ld); zeros outside (read from Q's first element).
-template <typename T>
-__device__ __forceinline__ Blk<T> blk_load(const T *Q, int ld, int rows, int cols) {
-  const int r = blk_row(), g = (threadIdx.x & 63) >> 4;
-  T v[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    v[q] = ld_off(Q, ((uint32_t)((4 * q + g) * ld + r) & opaque_mask32(r < rows && 4 * q + g < cols)) * (uint32_t)sizeof(T));
-  Blk<T> b;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) blk_set(b, q, masked(v[q], opaque_mask(r < rows && 4 * q + g < cols)));
-  return b;
-}
-template <typename T>
-__device__ __forceinline__ void blk_store(const Blk<T> &b, T *Q, int ld, int rows, int cols) {
-  const int r = blk_row(), g = (threadIdx.x & 63) >> 4;
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (r < rows && 4 * q + g < cols) st_off(Q, (uint32_t)((4 * q + g) * ld + r) * (uint32_t)sizeof(T), blk_get(b, q));
-}
-
 // Rows 4 v + l / 16 of a transposed block times dl[4 v + l / 16] (planes `stride` apart).
 template <typename T> __device__ __forceinline__ Blk<T> blk_scale_rows(const Blk<T> &b, const double *dl, int stride) {
   const int g = (threadIdx.x & 63) >> 4;
@@ -164,25 +63,6 @@ template <typename T> __device__ __forceinline__ Blk<T> blk_neg_cj(const Blk<T> 
   o.p[0] = -b.p[0];
   if constexpr (Planes<T>::P == 2) o.p[1] = -cs * b.p[1];
   return o;
-}
-
-template <class F, int... I> __device__ __forceinline__ void static_for(F f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-
-// Lane broadcasts inside a row of 16 lanes (row_newbcast, the one DPP form of
-// 64-bit operations): acc += w[lane L of the row] y in one instruction.  The
-// compiler does not look into these for hazards: a DPP read needs two wait
-// states after its source was written, which bcast16 supplies and fmac16
-// gets by following a bcast16 of the same source.
-template <int L> __device__ __forceinline__ double bcast16(double w) {
-  double r;
-  asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(w), "n"(L));
-  return r;
-}
-template <int L> __device__ __forceinline__ cplx bcast16(cplx w) { return cplx{bcast16<L>(w.re), bcast16<L>(w.im)}; }
-template <int L> __device__ __forceinline__ void fmac16(double &acc, double w, double y) {
-  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(w), "v"(y), "n"(L));
 }
 
 // Lanes 0 .. 15 of v on lanes 0 .. 15 and 16 .. 31 (and 32 .. 47 on the rest).
@@ -218,10 +98,6 @@ __device__ __forceinline__ bool recip_ok(cplx di) {
   return max(exponent_of(di.re), exponent_of(di.im)) - 783u < 480u;  // the squared modulus is in range too
 }
 
-// Component-wise select (a select of whole complex values goes through memory).
-__device__ __forceinline__ double pick(bool c, double a, double b) { return c ? a : b; }
-__device__ __forceinline__ cplx pick(bool c, cplx a, cplx b) { return cplx{c ? a.re : b.re, c ? a.im : b.im}; }
-
 // x -= w[lane Q of the row] y; sg: the sign of the imaginary part of w (conj(w_q) on the lanes of S if Hermitian)
 template <int Q> __device__ __forceinline__ void ldl_step(double &x, double w, double ny) { fmac16<Q>(x, w, ny); }
 struct NegY {
@@ -235,13 +111,6 @@ template <int Q> __device__ __forceinline__ void ldl_step(cplx &x, cplx w, const
 }
 __device__ __forceinline__ double neg_y(double y, double) { return -y; }
 __device__ __forceinline__ NegY neg_y(cplx y, double sg) { return NegY{cplx{-y.re, -y.im}, cplx{sg * y.re, sg * y.im}}; }
-
-// LDS ordering inside one wavefront.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
 
 // The lanes of ldl16 in LDS: row r of L and D at [17 r + k], M(p, q) at
 // [17 (16 + q) + p], 1 / D_j at [kLdlD + j]; planes kLdlLds apart.

@@ -26,6 +26,7 @@
 
 #include <cstdint>
 
+#include "blk16.hpp"
 #include "plan.hpp"
 #include "scalar.hpp"
 #include "items.hpp"
@@ -563,132 +564,141 @@ __global__ void __launch_bounds__(NT, 1)
 
 // L_KK^{-1} and D_K^{-1} (Alg. 1 step 1, with the LDL^T factor of Section
 // 2.3: L_KK is unit lower triangular, its diagonal slot holds D).  The
-// columns of X = L_KK^{-1} are independent: one workgroup per 16-column block
-// [j0, j0 + 16) of one node solves L_KK X(:, J) = I(:, J) by forward
-// substitution down 16-row strips, with X(:, J) held in LDS.  Strip I:
-//   X(I, J) = I(I, J) - L(I, j0:I0) X(j0:I0, J)   (one 16 x 16 MFMA product:
-//   the four waves take interleaved 4-deep slices of the contraction and sum
-//   their partials through LDS; complex in the 3M form)
-// then the 16 x 16 unit triangular solve with L(I, I) (one thread per column).
-// The L strip of the next row block is loaded while the current one is used.
+// columns of X = L_KK^{-1} are independent: one workgroup of four wavefronts
+// per 16-column block J of one node goes down the 16-row strips I >= J by block
+// forward substitution,
+//   X(I, J) = M_I A_I,  A_I = [I = J] - sum_{J <= K < I} L(I, K) X(K, J),  M_I = L(I, I)^{-1},
+// wavefront w holding the A_I of every fourth strip in registers: once X(K, J)
+// is known (one product with M_K) it goes to LDS, and every wavefront updates
+// its strips with it.  The product's result layout is the layout of the next
+// one's B operand, so X needs no rearrangement; one barrier per strip; the
+// L(:, K + 1) are loaded while L(:, K) is used.  The M_I of a wavefront's strips
+// come first, all at once: one strip per row of 16 lanes, lane q computing
+// column q from row broadcasts.
+// Bound by the chain of strips (two 16 x 16 products, LDS and a barrier each).
+// 16 Hermitian 30^3 matrices, nodes wider than 64: 1.17 ms with a 16-row
+// triangular solve by 16 threads per strip, now 0.35; 32 complex 30^3 shifts,
+// normalization and traversal, 34.8 -> 32.2 ms.
 // MAXS bounds s for the nodes of the launch (256, or 64 for a launch of narrow
-// nodes with a quarter of the LDS, so that more workgroups share a CU).
+// nodes: one strip per wavefront, a quarter of the LDS and registers).
 // LU plans launch nsets = 2 grids' worth of workgroups: the second half
 // works on the second panel set, U^T, whose unit lower diagonal block gives
 // U_KK^{-T} (into the second half of the linv buffer); D_K^{-1} is written by
 // the first half only.
 template <typename T, int MAXS>
-__global__ void __launch_bounds__(NT) k_normalize_inv(const DevPlan *__restrict__ plp, const T *Src_all, const int2 *chunks,
-                                                      int32_t nchunks, int nsets) {
-  constexpr int P = Planes<T>::P, XP = 17, LPI = MAXS + 1, U = MAXS / 16;
+__global__ void __launch_bounds__(NT, MAXS == 64 || Planes<T>::P == 1 ? 3 : 2)
+    k_normalize_inv(const DevPlan *__restrict__ plp, const T *Src_all, const int2 *chunks, int32_t nchunks, int nsets) {
+  constexpr int P = Planes<T>::P, W = NT / 64, NS = MAXS / 16 / W, MP = 16 * 17;
   const DevPlan &pl = *plp;
-  __shared__ double xs[P][MAXS * XP];  // X(j0 + r, j0 + q) at [r * XP + q]
-  __shared__ double lsd[P][16 * LPI];  // L(I0 + i, j0 + k) at [i * LPI + k]
-  __shared__ double red[P][4 * 256];   // the waves' 16 x 16 partial products, [w * 256 + i * 16 + q]
+  __shared__ double ms[W][NS][P * MP];  // M(p, q) of the wavefronts' strips at [17 q + p]
+  __shared__ double xb[2][P * 256];     // X(K, J), register layout
   const int64_t per = (int64_t)nchunks * pl.batch;  // workgroups per panel set
   const int hs = nsets > 1 ? (int)(blockIdx.x / per) : 0;
-  const int64_t g = blockIdx.x - hs * per;
-  const int64_t l = g / nchunks;
-  const int2 ck = chunks[g - l * nchunks];
+  const int64_t g0 = blockIdx.x - hs * per;
+  const int64_t l = g0 / nchunks;
+  const int2 ck = chunks[g0 - l * nchunks];
   const int K = uniform(ck.x), j0 = uniform(ck.y) * 16;
-  const int s = uniform(gp(pl.node_s)[K]), c = gp(pl.node_c)[K], ld = s + c;
-  const T *Q = Src_all + l * pl.panel_elems + hs * pl.half + gp(pl.node_off)[K];  // LDL^T panel (read only)
-  T *Linv = reinterpret_cast<T *>(pl.linv) + (hs * pl.batch + l) * pl.sq_elems + gp(pl.node_sq)[K];
-  T *dinv = reinterpret_cast<T *>(pl.dinv) + l * pl.n + gp(pl.node_first)[K];
-  const int w = min(16, s - j0);
-  const int t = threadIdx.x;
-  if (t < w && hs == 0) gstore(dinv + j0 + t, SOps<T>::div(SOps<T>::one(), Q[(int64_t)(j0 + t) * ld + j0 + t]));
-  // strip element u of thread t: i = e & 15, k = e >> 4 with e = t + NT u (k < MAXS)
-  auto strip_ok = [&](int I0, int u) {
-    const int e = t + NT * u, i = e & 15, k = e >> 4;
-    return k < min(I0 + 16, s) - j0 && I0 + i < s;
-  };
-  T pre[U];
-  auto load_strip = [&](int I0) {
+  const int s = uniform(gp(pl.node_s)[K]), c = uniform(gp(pl.node_c)[K]), ld = s + c;
+  const T *Q = Src_all + l * pl.panel_elems + hs * pl.half + uniform64(gp(pl.node_off)[K]);  // LDL^T panel (read only)
+  T *Linv = reinterpret_cast<T *>(pl.linv) + (hs * pl.batch + l) * pl.sq_elems + uniform64(gp(pl.node_sq)[K]);
+  T *dinv = reinterpret_cast<T *>(pl.dinv) + l * pl.n + uniform64(gp(pl.node_first)[K]);
+  const int t = threadIdx.x, lane = t & 63, wv = uniform(t >> 6), r = lane & 15, g = lane >> 4;
+  const int w = min(16, s - j0), n = (s - j0 + 15) / 16;  // strips from J on
+  const T *Qj = Q + (int64_t)j0 * (ld + 1);               // L(j0.., j0..)
+  if (t < w && hs == 0) gstore(dinv + j0 + t, SOps<T>::div(SOps<T>::one(), gload(Qj + (int64_t)t * (ld + 1))));
+  // blocks L(I, k) of the wavefront's strips I = wv + W q > k
+  auto load_l = [&](int k, Blk<T>(&lb)[NS]) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = t + NT * u, i = e & 15, k = e >> 4;
-      pre[u] = gload(Q + (((int64_t)(j0 + k) * ld + I0 + i) & opaque_mask(strip_ok(I0, u))));
+    for (int q = 0; q < NS; ++q) {
+      const int I = wv + W * q;
+      if (I > k && I < n) lb[q] = blk_load<T>(Qj + (int64_t)(16 * k) * ld + 16 * I, ld, s - j0 - 16 * I, 16);
     }
   };
-  load_strip(j0);
-  const int ti = t & 15, tq = t >> 4;
-  for (int I0 = j0; I0 < s; I0 += 16) {
-    const int h = min(16, s - I0), r0 = I0 - j0;
-    lds_barrier();
+  Blk<T> lb[NS];
+  load_l(0, lb);
+  if (wv < n) {  // M of strip wv + W g' by the lanes of row g' (row 0 alone for the narrow nodes)
+    const int I = wv + W * g;
+    const int hI = NS > 1 || g == 0 ? s - j0 - 16 * I : 0;  // its rows (<= 0: none)
+    T x[16], m[16];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = t + NT * u, i = e & 15, k = e >> 4;
-      const T v = masked(pre[u], opaque_mask(strip_ok(I0, u)));
+    for (int j = 0; j < 15; ++j)
+      x[j] = gload(Qj + (((int64_t)(16 * I + j) * ld + 16 * I + r) & opaque_mask(r < hI && r > j)));
 #pragma unroll
-      for (int p = 0; p < P; ++p) lsd[p][i * LPI + k] = Planes<T>::get(v, p);
+    for (int j = 0; j < 15; ++j) x[j] = masked(x[j], opaque_mask(r < hI && r > j));
+#pragma unroll
+    for (int p = 0; p < 16; ++p) m[p] = pick(p == r, SOps<T>::one(), zero_of<T>());
+    // m[p] -= L(p, j) m[j], L(p, j) from lane p of the row
+    static_for(
+        [&](auto jc) {
+          constexpr int j = decltype(jc)::value;
+          const T nm = -m[j];
+          dpp_source(x[j]);
+          static_for(
+              [&](auto pc) {
+                constexpr int p = decltype(pc)::value + j + 1;
+                fmac16_t<p>(m[p], x[j], nm);
+              },
+              std::make_integer_sequence<int, 15 - j>{});
+        },
+        std::make_integer_sequence<int, 15>{});
+    if (g < NS) {
+#pragma unroll
+      for (int p = 0; p < 16; ++p)
+#pragma unroll
+        for (int pp = 0; pp < P; ++pp) ms[wv][g][pp * MP + 17 * r + p] = Planes<T>::get(m[p], pp);
     }
-    if (I0 + 16 < s) load_strip(I0 + 16);
-    lds_barrier();
-    // X(I0 + ti, j0 + tq) before the diagonal block: identity minus the
-    // earlier strips, L(I, j0:I0) X(j0:I0, J) on MFMA (lane l of a wave
-    // holds A(l % 16, l / 16), B(l / 16, l % 16) and the result rows
-    // 4 v + l / 16 of column l % 16)
-    {
-      constexpr int C = P == 1 ? 1 : 3;  // product chains (3M for complex)
-      const int lane = t & 63, wv = t >> 6, m = lane & 15;
-      d4 pc[C];
+    wave_lds_fence();
+  }
+  auto m_of = [&](int q) {
+    Blk<T> b;
 #pragma unroll
-      for (int q = 0; q < C; ++q) pc[q] = d4{0.0, 0.0, 0.0, 0.0};
-      for (int k0 = 4 * wv; k0 < r0; k0 += 16) {
-        const int ka = k0 + (lane >> 4);
-        if constexpr (P == 1) {
-          pc[0] = mfma16(lsd[0][m * LPI + ka], xs[0][ka * XP + m], pc[0]);
-        } else {
-          const double a0 = lsd[0][m * LPI + ka], a1 = lsd[1][m * LPI + ka];
-          const double b0 = xs[0][ka * XP + m], b1 = xs[1][ka * XP + m];
-          pc[0] = mfma16(a0, b0, pc[0]);
-          pc[1] = mfma16(a1, b1, pc[1]);
-          pc[2] = mfma16(a0 + a1, b0 + b1, pc[2]);
-        }
+    for (int pp = 0; pp < P; ++pp)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) b.p[pp][v] = ms[wv][q][pp * MP + 17 * (4 * v + g) + r];
+    return b;
+  };
+  Blk<T> acc[NS];
+#pragma unroll
+  for (int q = 0; q < NS; ++q) acc[q] = blk_zero<T>();
+  // strip 0: X(0, J) = M_0
+  if (wv == 0) {
+    Blk<T> x0;
+#pragma unroll
+    for (int pp = 0; pp < P; ++pp)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x0.p[pp][v] = ms[0][0][pp * MP + 17 * r + 4 * v + g];  // M(4 v + g, r)
+    blk_to_lds<T>(x0, xb[0], 256);
+  }
+  for (int k = 0; k < n; ++k) {
+    lds_barrier();
+    const double *xk = xb[k & 1];
+    const Blk<T> x = blk_from_lds<T>(xk, 256);
+    Blk<T> nx;  // -X(k, J)
+#pragma unroll
+    for (int pp = 0; pp < P; ++pp) nx.p[pp] = -x.p[pp];
+    // the next strip first: its X is what everyone waits for
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+      if (wv + W * q == k + 1 && k + 1 < n) {
+        blk_mma<T>(lb[q], nx, acc[q]);
+        Blk<T> xn = blk_zero<T>();
+        blk_mma<T>(m_of(q), acc[q], xn);
+        blk_to_lds<T>(xn, xb[(k + 1) & 1], 256);
       }
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int o = wv * 256 + (4 * v + (lane >> 4)) * 16 + m;
-        if constexpr (P == 1) {
-          red[0][o] = pc[0][v];
-        } else {
-          red[0][o] = pc[0][v] - pc[1][v];
-          red[1][o] = pc[2][v] - pc[0][v] - pc[1][v];
-        }
-      }
-    }
-    lds_barrier();
-    if (ti < h) {
-      T acc = (I0 + ti == j0 + tq) ? SOps<T>::one() : zero_of<T>();
-#pragma unroll
-      for (int wq = 0; wq < 4; ++wq) acc -= Planes<T>::from(&red[0][wq * 256 + ti * 16 + tq], 4 * 256);
-#pragma unroll
-      for (int p = 0; p < P; ++p) xs[p][(r0 + ti) * XP + tq] = Planes<T>::get(acc, p);
-    }
-    lds_barrier();
-    // unit lower triangular solve with L(I, I), one thread per column
-    if (t < 16) {
-      T xv[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        if (i < h) {
-          T v = Planes<T>::from(&xs[0][(r0 + i) * XP + t], MAXS * XP);
-#pragma unroll
-          for (int k = 0; k < i; ++k) v -= Planes<T>::from(&lsd[0][i * LPI + r0 + k], 16 * LPI) * xv[k];
-          xv[i] = v;
-#pragma unroll
-          for (int p = 0; p < P; ++p) xs[p][(r0 + i) * XP + t] = Planes<T>::get(v, p);
-        }
-      }
+    for (int q = 0; q < NS; ++q)
+      if (wv + W * q > k + 1 && wv + W * q < n) blk_mma<T>(lb[q], nx, acc[q]);
+    if (k + 1 < n) load_l(k + 1, lb);
+    // rows of strip k of columns J: wavefront w takes columns 4 w + g, lanes along the rows
+    const int col = 4 * wv + g, row = 16 * k + r;
+    if (col < w && j0 + row < s) {
+      const T v = Planes<T>::from(xk + (r >> 2) * 64 + (r & 3) * 16 + col, 256);
+      gstore(Linv + (int64_t)(j0 + col) * s + j0 + row, v);
     }
   }
-  lds_barrier();
-  // whole columns j0 .. j0 + w - 1 of L_KK^{-1} (column-major, ld s), zeros above the diagonal
+  // zeros above the diagonal block
   for (int q = 0; q < w; ++q)
-    for (int r = t; r < s; r += NT)
-      gstore(Linv + (int64_t)(j0 + q) * s + r,
-             r < j0 ? zero_of<T>() : Planes<T>::from(&xs[0][(r - j0) * XP + q], MAXS * XP));
+    for (int row = t; row < j0; row += NT) gstore(Linv + (int64_t)(j0 + q) * s + row, zero_of<T>());
 }
 
 // All of the normalization (Alg. 1 steps 1-2, LDL^T form of Section 2.3) of
