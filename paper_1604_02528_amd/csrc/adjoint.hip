@@ -198,7 +198,7 @@ __device__ void bi_sc(const BCtx<T> &bx, const Geo &g, int a, int a2, double *sm
   acc_to_lds<T>(acc, smem);
   lds_barrier();
   scatter_lower<T>(*bx.cx.pl, g.rp, g.c, i0, k0, smem, bx.W,
-                   [](T v, bool diag) { return SOps<T>::scale(diag ? -0.5 : -1.0, v); });
+                   [](double v, bool diag) { return (diag ? -0.5 : -1.0) * v; });
 }
 
 // F = Tbar E

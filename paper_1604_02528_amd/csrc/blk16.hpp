@@ -85,6 +85,13 @@ __device__ __forceinline__ void st_off(cplx *base, uint32_t b, cplx v) {
   *reinterpret_cast<SELINV_GAS double *>(q) = v.re;
   *reinterpret_cast<SELINV_GAS double *>(q + 8) = v.im;
 }
+// The order of a strip's rows over the lanes for blocks that are added to the
+// ancestors' panels (see blk_atomic): complex rows are dealt to even and odd
+// lanes, row t / 2 + 8 (t % 2) to lane t.
+template <typename T> __device__ __forceinline__ int strip_row(int t) {
+  return Planes<T>::P == 2 ? (t >> 1) + 8 * (t & 1) : t;
+}
+
 // This lane's row of a block, opaque: the addresses below are cheap to form
 // and cost registers when kept from a block's load to its store.
 __device__ __forceinline__ int blk_row() {
@@ -94,9 +101,10 @@ __device__ __forceinline__ int blk_row() {
 }
 // Rows [0, rows) and columns [0, cols) of a 16 x 16 block at Q (wave-uniform,
 // leading dimension ld); zeros outside (read from Q's first element).
-template <typename T>
+// STRIP: rows in the order of strip_row.
+template <typename T, bool STRIP = false>
 __device__ __forceinline__ Blk<T> blk_load(const T *Q, int ld, int rows, int cols) {
-  const int r = blk_row(), g = (threadIdx.x & 63) >> 4;
+  const int r = STRIP ? strip_row<T>(blk_row()) : blk_row(), g = (threadIdx.x & 63) >> 4;
   T v[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
@@ -106,9 +114,9 @@ __device__ __forceinline__ Blk<T> blk_load(const T *Q, int ld, int rows, int col
   for (int q = 0; q < 4; ++q) blk_set(b, q, masked(v[q], opaque_mask(r < rows && 4 * q + g < cols)));
   return b;
 }
-template <typename T>
+template <typename T, bool STRIP = false>
 __device__ __forceinline__ void blk_store(const Blk<T> &b, T *Q, int ld, int rows, int cols) {
-  const int r = blk_row(), g = (threadIdx.x & 63) >> 4;
+  const int r = STRIP ? strip_row<T>(blk_row()) : blk_row(), g = (threadIdx.x & 63) >> 4;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
     if (r < rows && 4 * q + g < cols) st_off(Q, (uint32_t)((4 * q + g) * ld + r) * (uint32_t)sizeof(T), blk_get(b, q));
@@ -142,6 +150,35 @@ template <int L> __device__ __forceinline__ double bcast16(double w) {
 template <int L> __device__ __forceinline__ cplx bcast16(cplx w) { return cplx{bcast16<L>(w.re), bcast16<L>(w.im)}; }
 template <int L> __device__ __forceinline__ void fmac16(double &acc, double w, double y) {
   asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(w), "v"(y), "n"(L));
+}
+
+// quad_perm moves between neighbouring lanes.
+template <int CTRL> __device__ __forceinline__ int32_t quad(int32_t v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL> __device__ __forceinline__ double quad(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)quad<CTRL>((int32_t)(uint32_t)u), hi = (uint32_t)quad<CTRL>((int32_t)(u >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// u added to the entries of an ancestor's column: row i0 + strip_row(lane % 16)
+// at base[pos], where k <= row < c.  Complex: the two lanes of a pair hold
+// rows m and m + 8 of the strip; they exchange one plane each, and both add to
+// row m, then both to row m + 8, so that one instruction covers eight whole
+// entries in a row (real and imaginary parts by themselves touch every cache
+// line twice; the atomics bound the updates of narrow nodes).
+__device__ __forceinline__ void blk_atomic(double *base, int32_t pos, int i0, int k, int c, double u) {
+  const int i = i0 + (threadIdx.x & 15);
+  if (i < c && k <= i) unsafeAtomicAdd(base + pos, u);
+}
+__device__ __forceinline__ void blk_atomic(cplx *base, int32_t pos, int i0, int k, int c, cplx u) {
+  const int odd = threadIdx.x & 1, i = i0 + ((threadIdx.x & 15) >> 1);
+  const double other = quad<0xb1>(odd ? u.re : u.im);  // [1, 0, 3, 2]
+  const int32_t pa = quad<0xa0>(pos), pb = quad<0xf5>(pos);  // [0, 0, 2, 2], [1, 1, 3, 3]
+  double *q = reinterpret_cast<double *>(base) + odd;
+  if (i < c && k <= i) unsafeAtomicAdd(q + 2 * (int64_t)pa, odd ? other : u.re);
+  if (i + 8 < c && k <= i + 8) unsafeAtomicAdd(q + 2 * (int64_t)pb, odd ? u.im : other);
 }
 
 template <int L> __device__ __forceinline__ void fmac16_t(double &acc, double w, double y) { fmac16<L>(acc, w, y); }

@@ -244,8 +244,9 @@ template <typename T> __device__ __forceinline__ void ldl16_store(const double *
 // dependent rounds of loads (record -> panel and row tables -> positions), so
 // one launch does everything and a CU holds many nodes at once (four launches
 // on 64 x 64 tiles before; 31 x 31 FP64 grid: 0.27 -> 0.08 ms for its ten depths;
-// 16 Hermitian 30^3 matrices, the lower 13 depths: 10.5 -> 2.9 ms, where the
-// atomics of nodes with c near 64 bound it).
+// 16 Hermitian 30^3 matrices, the lower 13 depths: 10.5 -> 1.7 ms, where the
+// atomics of nodes with c near 64 bound it: 1.9 ms with the two planes of an
+// entry added by separate instructions, 1.1 with whole entries, see blk_atomic).
 // ---------------------------------------------------------------------------
 // x of ldl16 from the panel.
 template <typename T>
@@ -274,7 +275,7 @@ __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__
   const int s = uniform(nd.s), c = uniform(nd.c), ld = s + c;
   T *Pl = Pall + l * pl.panel_elems;
   T *Q = Pl + nd.off;
-  const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
+  const int lane = threadIdx.x, r = strip_row<T>(lane & 15), g = lane >> 4;
   const double cs = pl.csign;
   const int kq = min(lane, c - 1);
   const int64_t kc = c > 0 ? gp(pl.kcol)[nd.rp + kq] : 0, kp = c > 0 ? gp(pl.kpos)[nd.rp + kq] : 0;
@@ -283,7 +284,7 @@ __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__
   Blk<T> wb[NST];
 #pragma unroll
   for (int i = 0; i < NST; ++i)
-    if (16 * i < c) wb[i] = blk_load<T>(Q + s + 16 * i, ld, c - 16 * i, s);
+    if (16 * i < c) wb[i] = blk_load<T, true>(Q + s + 16 * i, ld, c - 16 * i, s);
   rcol[lane] = kc;
   rpos[lane] = kp;
   wave_lds_fence();
@@ -293,7 +294,7 @@ __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__
   auto load_pos = [&](int j) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int kg = 16 * j + 4 * v + g;
+      const int kg = 16 * j + strip_row<T>(4 * v + g);
       const int64_t rp = rpos[kg];
 #pragma unroll
       for (int i = 0; i < NST; ++i) {
@@ -313,7 +314,7 @@ __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__
     Blk<T> w = blk_zero<T>();
     blk_mma<T>(m, wb[i], w, nv);
     wb[i] = w;
-    blk_store<T>(blk_scale_rows<T>(w, ls + kLdlD, kLdlLds), Q + s + 16 * i, ld, c - 16 * i, s);
+    blk_store<T, true>(blk_scale_rows<T>(w, ls + kLdlD, kLdlLds), Q + s + 16 * i, ld, c - 16 * i, s);
   }
 #pragma unroll
   for (int j = 0; j < NST; ++j) {
@@ -322,7 +323,7 @@ __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__
     const Blk<T> lj = blk_neg_cj<T>(blk_scale_rows<T>(wb[j], ls + kLdlD, kLdlLds), cs);
     int64_t col[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) col[v] = rcol[16 * j + 4 * v + g];
+    for (int v = 0; v < 4; ++v) col[v] = rcol[16 * j + strip_row<T>(4 * v + g)];
 #pragma unroll
     for (int i = j; i < NST; ++i) {
       if (16 * i >= c) break;
@@ -330,8 +331,8 @@ __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__
       blk_mma<T>(lj, wb[i], u, nv);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int ig = 16 * i + r, kg = 16 * j + 4 * v + g;
-        if (ig < c && kg <= ig) atomic_add_t(Pl + col[v] + pos[j & 1][i][v], blk_get(u, v));
+        const int kg = 16 * j + strip_row<T>(4 * v + g);
+        blk_atomic(Pl + col[v], pos[j & 1][i][v], 16 * i, kg, c, blk_get(u, v));
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -356,7 +357,7 @@ __global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ p
   const int s = uniform(nd.s), c = uniform(nd.c), ld = s + c;
   T *Pl = Pall + l * pl.panel_elems;
   T *Q = Pl + nd.off;
-  const int wv = uniform((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wv = uniform((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, r = strip_row<T>(lane & 15), g = lane >> 4;
   const double cs = pl.csign;
   if (threadIdx.x < kFacMidC) {
     const int kq = min((int)threadIdx.x, c - 1);
@@ -369,7 +370,7 @@ __global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ p
 #pragma unroll
   for (int q = 0; q < NST / W; ++q) {
     const int i = wv + W * q;
-    if (16 * i < c) sb[q] = blk_load<T>(Q + s + 16 * i, ld, c - 16 * i, s);
+    if (16 * i < c) sb[q] = blk_load<T, true>(Q + s + 16 * i, ld, c - 16 * i, s);
   }
   lds_barrier();
   // pair e = wv + W q of strips (i, j), i >= j, row by row
@@ -384,7 +385,7 @@ __global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ p
     if (16 * pi[q] >= c) continue;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int ig = 16 * pi[q] + r, kg = 16 * pj[q] + 4 * v + g;
+      const int ig = 16 * pi[q] + r, kg = 16 * pj[q] + strip_row<T>(4 * v + g);
       pos[q][v] = gp(pl.posarr)[(rpos[kg] + ig) & opaque_mask(ig < c && ig >= kg)];
     }
   }
@@ -404,7 +405,7 @@ __global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ p
     const Blk<T> lo = blk_scale_rows<T>(w, ls + kLdlD, kLdlLds);
     blk_to_lds<T>(w, wp + 256 * i, LP);
     blk_to_lds<T>(blk_neg_cj<T>(lo, cs), lp + 256 * i, LP);
-    blk_store<T>(lo, Q + s + 16 * i, ld, c - 16 * i, s);
+    blk_store<T, true>(lo, Q + s + 16 * i, ld, c - 16 * i, s);
   }
   lds_barrier();
 #pragma unroll
@@ -414,8 +415,8 @@ __global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ p
     blk_mma<T>(blk_from_lds<T>(lp + 256 * pj[q], LP), blk_from_lds<T>(wp + 256 * pi[q], LP), u, nv);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int ig = 16 * pi[q] + r, kg = 16 * pj[q] + 4 * v + g;
-      if (ig < c && kg <= ig) atomic_add_t(Pl + rcol[kg] + pos[q][v], blk_get(u, v));
+      const int kg = 16 * pj[q] + strip_row<T>(4 * v + g);
+      blk_atomic(Pl + rcol[kg], pos[q][v], 16 * pi[q], kg, c, blk_get(u, v));
     }
   }
 }
@@ -640,7 +641,8 @@ template <typename T, int TK> struct FacLoadB : LoadDenseAIl<T, TK> {
 //           over all columns of the node, with atomic adds.
 // MFMA-bound on wide nodes, by the atomics on narrow ones.  Branch-free
 // interleaved stages and the 3M form at two workgroups a CU; 16 Hermitian 30^3
-// matrices: 12.7 ms of updates (nodes beyond the single-wavefront ones) -> 7.3 ms.
+// matrices: 12.7 ms of updates (nodes beyond the single-wavefront ones) -> 5.5 ms
+// (6.8 before the atomics took whole complex entries).
 template <typename T, bool INNER>
 __global__ void __launch_bounds__(NT, 2)
     k_fac_update(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs, const int4 *tiles, int32_t ntiles) {
@@ -697,7 +699,7 @@ __global__ void __launch_bounds__(NT, 2)
       if (ig < c && kg < nc && ig >= kg) gstore(R + (int64_t)kg * ld + ig, v[q] - lds_get<T>(smem, i, w + 4 * q));
     }
   } else {
-    scatter_lower<T>(pl, rp, c, i0, k0, smem, Pl, [](T v, bool) { return SOps<T>::scale(-1.0, v); });
+    scatter_lower<T>(pl, rp, c, i0, k0, smem, Pl, [](double v, bool) { return -v; });
   }
 }
 

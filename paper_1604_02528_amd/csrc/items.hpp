@@ -80,23 +80,32 @@ __device__ __forceinline__ void atomic_add_t(cplx *p, cplx v) {
 // added to the ancestors' entries of S_{C,C} in a panel-layout array, with
 // f(value, diagonal) applied: the positions of all of a thread's elements
 // first, then the adds.
+// Complex entries: neighbouring lanes take the two planes of one entry, so
+// that an atomic instruction covers whole cache lines.
 template <typename T, class F>
 __device__ __forceinline__ void scatter_lower(const DevPlan &pl, int64_t rp, int c, int i0, int k0, const double *smem,
                                               T *base, F f) {
-  constexpr int Q = 64 * 64 / NT;
-  const int i = threadIdx.x & 63, w = uniform((int)(threadIdx.x >> 6)), ig = i0 + i;
-  int32_t pos[Q];
+  constexpr int P = Planes<T>::P, Q = 64 * 64 / NT;
+  const int lane = threadIdx.x & 63, w = uniform((int)(threadIdx.x >> 6)), p = P == 2 ? lane & 1 : 0;
   int64_t col[Q];
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int kg = k0 + w + 4 * q, kc = min(kg, c - 1);
-    col[q] = uniform64(gp(pl.kcol)[rp + kc]);
-    pos[q] = gp(pl.posarr)[(gp(pl.kpos)[rp + kc] + ig) & opaque_mask(ig < c && kg < c && ig >= kg)];
-  }
+  for (int q = 0; q < Q; ++q) col[q] = uniform64(gp(pl.kcol)[rp + min(k0 + w + 4 * q, c - 1)]);
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int kg = k0 + w + 4 * q;
-    if (ig < c && kg < c && ig >= kg) atomic_add_t(base + col[q] + pos[q], f(lds_get<T>(smem, i, w + 4 * q), ig == kg));
+  for (int h = 0; h < P; ++h) {
+    const int i = lane / P + 64 / P * h, ig = i0 + i;
+    int32_t pos[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int kg = k0 + w + 4 * q;
+      pos[q] = gp(pl.posarr)[(gp(pl.kpos)[rp + min(kg, c - 1)] + ig) & opaque_mask(ig < c && kg < c && ig >= kg)];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int kg = k0 + w + 4 * q;
+      if (ig < c && kg < c && ig >= kg)
+        unsafeAtomicAdd(reinterpret_cast<double *>(base + col[q] + pos[q]) + p,
+                        f(smem[p * 64 * PITCH + (w + 4 * q) * PITCH + i], ig == kg));
+    }
   }
 }
 
