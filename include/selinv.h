@@ -180,7 +180,7 @@ typedef struct {
   int64_t abar_bytes;    /* adjoint / selinv_extract output on A's pattern, batch * nnz(A) scalars
                             (SELINV_LU64: batch * 2 nnz(A)) */
   int64_t trace_bytes;   /* optional selinv_trace buffer */
-  int64_t tables_bytes;  /* leading part of work_bytes: the plan tables, written on upload and then only read */
+  int64_t tables_bytes;  /* leading part of work_bytes: the forward path's plan tables, written on upload and then only read */
 } selinv_sizes_t;
 
 selinv_status selinv_sizes(const selinv_ctx *h, selinv_sizes_t *s);

@@ -114,7 +114,10 @@ struct HostPlan {
         apos, adiag, aflip, bitems, pushrecs, y128recs, fac_nodes, fac_rb, fac_tiles, dpos, plan, plan2, linv, dinv, part, gbuf, ypart,
         cnt, ctrl, fwd_end, adj_z, adj_l, adj_s, adj_t, adj_f, adj_d, ferr, fldet, finv, end;
   } off{};
-  int64_t tables_bytes = 0;  // [0, tables_bytes) is uploaded once
+  // uploaded once: [0, tables_bytes), what the forward path reads, and behind
+  // the scratch [aux_off, aux_off + aux_bytes), the lists of the adjoint and
+  // of the device factorization
+  int64_t tables_bytes = 0, aux_off = 0, aux_bytes = 0;
 };
 
 template <typename V>
@@ -391,7 +394,8 @@ void back_items(const HostPlan &H, int64_t K, int32_t type, std::vector<Item> &o
 }
 
 void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t dense_min_c, int64_t dense_max_bytes,
-                int64_t split_min_k, int sched, const TuneTable *tt, bool adjoint, bool herm, bool lu, HostPlan &H) {
+                int64_t split_min_k, int sched, const TuneTable *tt, bool adjoint, bool herm, bool lu, HostPlan &H,
+                bool lu_small = true) {
   const int64_t ns = S.nsuper();
   H.lu = lu;
   // the push form (Alg. 2) runs one launch per depth and step like the level
@@ -401,9 +405,8 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   const bool per_level = sched != SELINV_SCHED_PERSISTENT;
   // The LU form of Alg. 1 (Section 2.1) runs the level schedule with
   // gathered or dense-buffer GEMM-1 tiles (the buffer holds all of
-  // X_{C,C}, its upper part from the X^T panel set): no split contraction,
-  // R phase, tune table, single-item or single-wavefront node and no
-  // single-wavefront normalization.
+  // X_{C,C}, its upper part from the X^T panel set) and the single-wavefront
+  // nodes: no split contraction, R phase, tune table or single-workgroup node.
   if (push) dense_min_c = -1;
   if (push || lu) {
     split_min_k = -1;
@@ -539,6 +542,10 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   for (int64_t K = 0; K < ns; ++K)
     if (H.node_yoff[K] >= 0 || H.node_defer[K])
       rtiles[S.sdepth[K]] += batch * ((S.nrows(K) + kTileM - 1) / kTileM) * ((S.width(K) + kTileN - 1) / kTileN);
+  // single-wavefront nodes address X through 32-bit byte offsets
+  const int64_t pan_bytes = (lu ? 2 : 1) * S.panel_elems * scalar_bytes;
+  const bool tiny_ok = pan_bytes < (int64_t(1) << 32) && (!lu || lu_small);
+  auto lu_tiny = [&](int64_t K) { return tiny_ok && H.node_c[K] <= kTinyCF && H.node_s[K] <= kTinyS; };
   H.item_ptr.assign(ns + 1, 0);
   H.nph.assign((size_t)kPhases * ns, 0);
   auto nph = [&](int ph, int64_t K) -> int32_t & { return H.nph[(size_t)ph * ns + K]; };
@@ -554,7 +561,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
         for (int32_t b = 0; b <= a; ++b) H.items.push_back(Item{(int32_t)K, ITEM_G, a, b});
       nph(0, K) = nr * (nr + 1) / 2;
     }
-    if (c <= kSmallC && s <= kSmallS && !push && !lu) {
+    if (!push && (lu ? lu_tiny(K) : c <= kSmallC && s <= kSmallS)) {
       H.items.push_back(Item{(int32_t)K, ITEM_S, 0, 0});
       nph(3, K) = 1;
       continue;
@@ -614,12 +621,10 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   H.toff.clear();
   H.tiny_dptr.assign(S.depth + 1, 0);
   H.tiny_dadj.assign(S.depth, 0);
-  // small nodes address X through 32-bit byte offsets
-  const bool tiny_ok = !lu && S.panel_elems * scalar_bytes < (int64_t(1) << 32);
   // the forward sweep's single-wavefront nodes: c <= kTinyCF (complex plans
   // run the ones beyond kTinyC in a kernel of their own)
   const int64_t tiny_cf = kTinyCF;
-  auto adj_tiny = [&](int64_t K) { return !push && tiny_ok && H.node_c[K] <= kTinyC && H.node_s[K] <= kTinyS; };
+  auto adj_tiny = [&](int64_t K) { return !push && !lu && tiny_ok && H.node_c[K] <= kTinyC && H.node_s[K] <= kTinyS; };
   H.push.clear();
   H.y128.clear();
   if (push) {
@@ -748,8 +753,9 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
             for (int64_t k = 0; k <= i; ++k) {
               const uint32_t v = (uint32_t)((H.kcol[rp + k] + S.posarr[H.kpos[rp + k] + i]) * scalar_bytes);
               H.toff[t0 + i * c + k] = v;
-              // entry (k, i), k < i, is X(i, k) transposed: conjugated in a Hermitian plan
-              H.toff[t0 + k * c + i] = v | (herm && k < i ? 1u : 0u);
+              // entry (k, i), k < i, is X(i, k) transposed: conjugated in a Hermitian plan, in the X^T set of an LU plan
+              H.toff[t0 + k * c + i] =
+                  lu && k < i ? v + (uint32_t)(S.panel_elems * scalar_bytes) : v | (herm && k < i ? 1u : 0u);
             }
         }
         if (pass == 0) {
@@ -823,7 +829,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   H.blaunch.clear();
   {
     std::vector<std::vector<int64_t>> bydepth(S.depth);
-    for (int64_t K = 0; K < ns; ++K)
+    for (int64_t K = 0; K < ns && !lu; ++K)  // (the LU form has no adjoint)
       if (!adj_tiny(K)) bydepth[S.sdepth[K]].push_back(K);
     int32_t bstart = 0;
     auto close = [&](int32_t step) {
@@ -916,7 +922,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
       }
       for (int64_t K : bydepth[d]) {
         const int32_t s = H.node_s[K], c = H.node_c[K];
-        if (s <= kSmallNormS && !lu) {
+        if (s <= kSmallNormS) {
           H.small_nodes.push_back((int32_t)K);
           continue;
         }
@@ -940,7 +946,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   H.fac_tiles.clear();
   H.fac_lev.clear();
   H.fin_elems = 0;
-  {
+  if (!lu) {  // (nor a device factorization)
     std::vector<std::vector<int64_t>> bydepth(S.depth);
     for (int64_t K = 0; K < ns; ++K) bydepth[S.sdepth[K]].push_back(K);
     // whole-node kernels: one block of columns, and strips that fit the registers (one wavefront) or LDS (four)
@@ -1046,13 +1052,8 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   o.apos = take(8 * (int64_t)H.apos.size());
   o.adiag = take((int64_t)H.adiag.size());
   o.aflip = take((int64_t)H.aflip.size());
-  o.bitems = take(16 * (int64_t)H.bitems.size());
   o.pushrecs = take((int64_t)sizeof(PushRec) * (int64_t)H.push.size());
   o.y128recs = take((int64_t)sizeof(Item) * (int64_t)H.y128.size());
-  o.fac_nodes = take((int64_t)sizeof(FacNode) * (int64_t)H.fac_nodes.size());
-  o.fac_rb = take(8 * (int64_t)H.fac_rb.size());
-  o.fac_tiles = take(16 * (int64_t)H.fac_tiles.size());
-  o.dpos = take(8 * (int64_t)H.dpos.size());
   H.tables_bytes = p;
   o.plan = take((int64_t)sizeof(DevPlan));
   o.plan2 = take((int64_t)sizeof(DevPlan));  // the plan of the second half of the batch (see batch_half)
@@ -1076,6 +1077,13 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   o.ferr = take(8 * batch);
   o.fldet = take(16 * batch * ldet_parts(S.n));
   o.finv = take(H.lu ? 0 : scalar_bytes * batch * H.fin_elems);
+  H.aux_off = p;
+  o.bitems = take(16 * (int64_t)H.bitems.size());
+  o.fac_nodes = take((int64_t)sizeof(FacNode) * (int64_t)H.fac_nodes.size());
+  o.fac_rb = take(8 * (int64_t)H.fac_rb.size());
+  o.fac_tiles = take(16 * (int64_t)H.fac_tiles.size());
+  o.dpos = take(8 * (int64_t)H.dpos.size());
+  H.aux_bytes = p - H.aux_off;
   o.end = p;
 }
 
@@ -1085,7 +1093,7 @@ struct selinv_ctx {
   Symbolic S;
   selinv_opts opts{};
   HostPlan H;
-  std::vector<unsigned char> image;  // tables image (host)
+  std::vector<unsigned char> image, image_aux;  // tables images (host)
   std::string err;
   int64_t info[2] = {-1, -1};
   std::vector<double> logdet;        // 2 per matrix
@@ -1383,6 +1391,8 @@ void build_image(selinv_ctx *h) {
   const auto &o = H.off;
   h->image.assign((size_t)H.tables_bytes, 0);
   auto &img = h->image;
+  h->image_aux.assign((size_t)H.aux_bytes, 0);
+  auto &aux = h->image_aux;
   put(img, o.node_s, H.node_s);
   put(img, o.node_c, H.node_c);
   put(img, o.node_off, H.node_off);
@@ -1415,18 +1425,21 @@ void build_image(selinv_ctx *h) {
   put(img, o.apos, H.apos);
   put(img, o.adiag, H.adiag);
   put(img, o.aflip, H.aflip);
-  put(img, o.bitems, H.bitems);
+  put(aux, o.bitems - H.aux_off, H.bitems);
   put(img, o.pushrecs, H.push);
   put(img, o.y128recs, H.y128);
-  put(img, o.fac_nodes, H.fac_nodes);
-  put(img, o.fac_rb, H.fac_rb);
-  put(img, o.fac_tiles, H.fac_tiles);
-  put(img, o.dpos, H.dpos);
+  put(aux, o.fac_nodes - H.aux_off, H.fac_nodes);
+  put(aux, o.fac_rb - H.aux_off, H.fac_rb);
+  put(aux, o.fac_tiles - H.aux_off, H.fac_tiles);
+  put(aux, o.dpos - H.aux_off, H.dpos);
 }
 
 selinv_status ensure_uploaded(selinv_ctx *h, void *work, hipStream_t st) {
   if (h->uploaded_to == work) return SELINV_OK;
   hipError_t e = hipMemcpyAsync(work, h->image.data(), h->image.size(), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess && !h->image_aux.empty())
+    e = hipMemcpyAsync(static_cast<unsigned char *>(work) + h->H.aux_off, h->image_aux.data(), h->image_aux.size(),
+                       hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return hip_err(h, e, "table upload");
   h->plan_host = make_devplan(h, work);
   e = hipMemcpyAsync(static_cast<unsigned char *>(work) + h->H.off.plan, &h->plan_host, sizeof(DevPlan),
@@ -1554,6 +1567,17 @@ selinv_status selinv_analyze(int64_t n, const int64_t *colptr, const int64_t *ro
                (o.tune_cache && o.tune_cache[0]) ? &tt : nullptr,
                o.adjoint >= 0 && o.dtype != SELINV_H128 && o.dtype != SELINV_LU64, o.dtype == SELINV_H128,
                o.dtype == SELINV_LU64, h->H);
+    // the offset tables of an LU plan's single-wavefront nodes (up to half of
+    // its tables) must not be what keeps it out of the fixed work area: such a
+    // plan does without these nodes (30^3, four shifts: 6.6 ms for 4.1), which
+    // selinv_normalize_run_noalloc would otherwise refuse outright
+    if (h->H.lu && h->H.off.fwd_end > kNoAllocBytes &&
+        h->H.off.fwd_end - 4 * (int64_t)h->H.toff.size() - (int64_t)sizeof(TinyRec) * (int64_t)h->H.tiny.size() <=
+            kNoAllocBytes) {
+      HostPlan alt;
+      build_plan(h->S, o.batch, h->sbytes(), min_c, max_b, split_k, o.sched, nullptr, false, false, true, alt, false);
+      if (alt.off.fwd_end <= kNoAllocBytes) h->H = std::move(alt);
+    }
     if ((int64_t)h->H.items.size() * (int64_t)o.batch >= (int64_t)INT32_MAX)
       return set_err(h, SELINV_ENOMEM, "too many work items for int32 item ids");
     build_image(h);

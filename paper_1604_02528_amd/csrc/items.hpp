@@ -1148,6 +1148,100 @@ __device__ __forceinline__ void do_tiny64(const TinyRec &r, const uint32_t *toff
   }
 }
 
+// A whole small node of an LU plan (c <= CM, s <= kTinyS) in one wavefront, as
+// do_tiny for both panel sets: lane (i, grp) holds X_{C,C}(i, k) and X_{C,C}(k, i)
+// for k = grp + G u (the table gives the first; the second is the same
+// position of the other set, half8 bytes away), 16 of each at a time, and
+// accumulates X_{C,C} Lhat and (X_{C,C})^T Uhat^T.
+//   X_{C,K} = -X_{C,C} Lhat, X_{K,C}^T = -(X_{C,C})^T Uhat^T,
+//   X_KK = Dt^{-1} - Uhat X_{C,K}, stored into the first set and transposed into the second
+template <int CM>
+__device__ __forceinline__ void do_tiny_lu(const TinyRec &r, const uint32_t *toff, int64_t half, const double *L, double *X,
+                                           double *ls, double *us, double *ys) {
+  constexpr int G = 64 / CM, U = CM / G, UC = U < 16 ? U : 16, LDC = kTinyCF, QL = CM * kTinyS / 64;
+  const int lane = threadIdx.x, i = lane % CM, grp = lane / CM;
+  const int s = r.s, c = r.c;
+  const int64_t ld = s + c;
+  const uint32_t *tb = toff + r.tbl;
+  const uint32_t rowb = 4u * ((uint32_t)(i * c + grp) & opaque_mask32(i < c)), half8 = (uint32_t)(8 * half);
+  uint32_t o[UC];
+#pragma unroll
+  for (int u = 0; u < UC; ++u) o[u] = ld_off(tb, rowb + 4u * (G * u));
+  double lv[QL], uv[QL];
+#pragma unroll
+  for (int q = 0; q < QL; ++q) {
+    const int e = lane + 64 * q, k = e % CM, j = e / CM;
+    const int64_t m = opaque_mask(k < c && j < s);
+    lv[q] = gload(L + r.off + ((j * ld + s + k) & m));
+    uv[q] = gload(L + half + r.off + ((j * ld + s + k) & m));
+  }
+  const int x = lane % kTinyS, y = lane / kTinyS;
+  const double dxy = gload(L + r.off + ((y * ld + x) & opaque_mask(x < s && y < s)));
+#pragma unroll
+  for (int q = 0; q < QL; ++q) {
+    const int e = lane + 64 * q, k = e % CM, j = e / CM;
+    const int64_t m = opaque_mask(k < c && j < s);
+    ls[j * LDC + k] = masked(lv[q], m);
+    us[j * LDC + k] = masked(uv[q], m);
+  }
+  __syncthreads();
+  double al[kTinyS], au[kTinyS];
+#pragma unroll
+  for (int j = 0; j < kTinyS; ++j) al[j] = au[j] = 0.0;
+#pragma unroll
+  for (int u0 = 0; u0 < U; u0 += UC) {
+    if (G * u0 >= c) break;
+    double xl[UC], xu[UC];
+#pragma unroll
+    for (int u = 0; u < UC; ++u) {
+      const int k = grp + G * (u0 + u);
+      const uint32_t ok = opaque_mask32(i < c && k < c);
+      xl[u] = ld_off(X, o[u] & ok);
+      xu[u] = ld_off(X, (i >= k ? o[u] + half8 : o[u] - half8) & ok);
+    }
+    if (u0 + UC < U) {
+#pragma unroll
+      for (int u = 0; u < UC; ++u) o[u] = ld_off(tb, rowb + 4u * (G * (u0 + UC + u)));
+    }
+#pragma unroll
+    for (int u = 0; u < UC; ++u) {
+      const int k = grp + G * (u0 + u);
+      const int64_t m = opaque_mask(i < c && k < c);
+      const double a = masked(xl[u], m), b = masked(xu[u], m);
+#pragma unroll
+      for (int j = 0; j < kTinyS; ++j)
+        if (j < s) {
+          al[j] += a * ls[j * LDC + k];
+          au[j] += b * us[j * LDC + k];
+        }
+    }
+  }
+#pragma unroll
+  for (int m = CM; m < 64; m <<= 1)
+#pragma unroll
+    for (int j = 0; j < kTinyS; ++j)
+      if (j < s) {
+        al[j] += shfl_xor_t(al[j], m);
+        au[j] += shfl_xor_t(au[j], m);
+      }
+  if (grp == 0 && i < c) {
+#pragma unroll
+    for (int j = 0; j < kTinyS; ++j)
+      if (j < s) {
+        gstore(X + r.off + j * ld + s + i, -al[j]);
+        gstore(X + half + r.off + j * ld + s + i, -au[j]);
+        ys[j * LDC + i] = al[j];
+      }
+  }
+  __syncthreads();
+  if (x < s && y < s) {
+    double t = dxy;
+    for (int q = 0; q < c; ++q) t += us[x * LDC + q] * ys[y * LDC + q];
+    gstore(X + r.off + y * ld + x, t);
+    gstore(X + half + r.off + x * ld + y, t);
+  }
+}
+
 // LU plans (gathered X_{C,C}, unsplit nodes): the GEMM-1 tile of the upper
 // part, rows 64a.. and columns 64b.. of X_{K,C}^T = -(X_{C,C})^T Uhat^T, where
 // Uhat^T is the normalized U^T panel set and (X_{C,C})^T is gathered with the

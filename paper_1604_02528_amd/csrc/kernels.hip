@@ -394,6 +394,40 @@ __global__ void __launch_bounds__(64) k_tiny(const DevPlan *__restrict__ plp, co
   }
 }
 
+// Small nodes of one level of an LU plan, one wavefront each (see do_tiny_lu;
+// as 64 x 64 tiles of both panel sets and a diagonal block they took most of a
+// traversal: 30^3, four shifts, normalization and traversal 6.65 -> 4.10 ms).
+__global__ void __launch_bounds__(64) k_tiny_lu(const DevPlan *__restrict__ plp, const double *Lp, double *Xp,
+                                                const TinyRec *__restrict__ recs, int32_t count, int32_t list_pos) {
+  const DevPlan &pl = *plp;
+  __shared__ double ls[kTinyS * kTinyCF], us[kTinyS * kTinyCF], ys[kTinyS * kTinyCF];
+  const int64_t g = blockIdx.x;
+  const int64_t l = g / count;
+  const TinyRec r = recs[g - l * count];
+  const int64_t t_start = pl.trace ? wall_clock64() : 0;
+  const double *L = Lp + l * pl.panel_elems;
+  double *X = Xp + l * pl.panel_elems;
+  if (r.c <= 8)
+    do_tiny_lu<8>(r, pl.toff, pl.half, L, X, ls, us, ys);
+  else if (r.c <= 16)
+    do_tiny_lu<16>(r, pl.toff, pl.half, L, X, ls, us, ys);
+  else if (r.c <= 32)
+    do_tiny_lu<32>(r, pl.toff, pl.half, L, X, ls, us, ys);
+  else
+    do_tiny_lu<64>(r, pl.toff, pl.half, L, X, ls, us, ys);
+  if (pl.trace) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int64_t *tr = pl.trace + 8 * ((int64_t)list_pos * pl.batch + g);
+      tr[0] = l * pl.nitems + r.it;
+      tr[1] = blockIdx.x;
+      tr[2] = t_start;
+      tr[3] = t_start;
+      tr[4] = wall_clock64();
+    }
+  }
+}
+
 // Complex single-wavefront nodes with kTinyC < c <= kTinyCF (the
 // forward-only part of a depth's list): do_tiny64, in a kernel of its own so
 // that the narrower nodes keep k_tiny's registers and LDS.
@@ -708,13 +742,15 @@ __global__ void __launch_bounds__(NT, MAXS == 64 || Planes<T>::P == 1 ? 3 : 2)
 // ^T in a Hermitian plan), and
 // Lhat_{C,K} = L_{C,K} L_KK^{-1} one row per lane.  L_KK is read into LDS
 // before anything is written, and each row of L_{C,K} is read by the lane that
-// overwrites it, so Src may alias Lp.
-template <typename T>
+// overwrites it, so Src may alias Lp.  LU: the same for both panel sets, with
+// Dt^{-1} = U_KK^{-1} D^{-1} L_KK^{-1} (no Dt).
+template <typename T, bool LU>
 __global__ void __launch_bounds__(64) k_normalize_small(const DevPlan *__restrict__ plp, const T *Src_all, T *Lp_all,
                                                         T *dt_all, const int32_t *__restrict__ nodes, int32_t count) {
   constexpr int S = kSmallNormS, SP = S + 1;
   const DevPlan &pl = *plp;
-  __shared__ T lk[S * SP], xs[S * SP], dv[S];
+  constexpr int H = LU ? 2 : 1;  // panel sets
+  __shared__ T lk[H][S * SP], xs[H][S * SP], dv[S];
   const int64_t g = blockIdx.x;
   const int64_t l = g / count;
   const int K = nodes[g - l * count];
@@ -727,19 +763,24 @@ __global__ void __launch_bounds__(64) k_normalize_small(const DevPlan *__restric
 #pragma unroll
   for (int u = 0; u < S * S / 64; ++u) {
     const int e = t + 64 * u, i = e % S, k = e / S;
-    lk[i * SP + k] = (i < s && k < s) ? Q[(int64_t)k * ld + i] : zero_of<T>();
-    xs[i * SP + k] = zero_of<T>();  // the rows k >= s are read (times zero) by the Lhat loop below
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      lk[h][i * SP + k] = (i < s && k < s) ? Q[h * pl.half + (int64_t)k * ld + i] : zero_of<T>();
+      xs[h][i * SP + k] = zero_of<T>();  // the rows k >= s are read (times zero) by the Lhat loop below
+    }
   }
   __syncthreads();
   if (t < s) {  // column t of L_KK^{-1}, kept in LDS (only this lane touches it)
-    const T d = SOps<T>::div(SOps<T>::one(), lk[t * SP + t]);
+    const T d = SOps<T>::div(SOps<T>::one(), lk[0][t * SP + t]);
     dv[t] = d;
     gstore(dinv + t, d);
-    for (int i = 0; i < s; ++i) {
-      T v = (i == t) ? SOps<T>::one() : zero_of<T>();
-      for (int k = t; k < i; ++k) v -= lk[i * SP + k] * xs[k * SP + t];
-      xs[i * SP + t] = v;
-    }
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+      for (int i = 0; i < s; ++i) {
+        T v = (i == t) ? SOps<T>::one() : zero_of<T>();
+        for (int k = t; k < i; ++k) v -= lk[h][i * SP + k] * xs[h][k * SP + t];
+        xs[h][i * SP + t] = v;
+      }
   }
   __syncthreads();
 #pragma unroll
@@ -748,13 +789,13 @@ __global__ void __launch_bounds__(64) k_normalize_small(const DevPlan *__restric
     if (a < s && b < s) {
       const double cs = pl.csign;
       T acc = zero_of<T>();
-      for (int k = a > b ? a : b; k < s; ++k) acc += (cj(xs[k * SP + a], cs) * dv[k]) * xs[k * SP + b];
+      for (int k = a > b ? a : b; k < s; ++k) acc += (cj(xs[H - 1][k * SP + a], cs) * dv[k]) * xs[0][k * SP + b];
       P[(int64_t)b * ld + a] = acc;
       if (dt_all) {
         T dd = zero_of<T>();
         for (int k = 0; k <= (a < b ? a : b); ++k) {
-          const T la = (a == k) ? SOps<T>::one() : lk[a * SP + k], lb = (b == k) ? SOps<T>::one() : lk[b * SP + k];
-          dd += (la * lk[k * SP + k]) * cj(lb, cs);
+          const T la = (a == k) ? SOps<T>::one() : lk[0][a * SP + k], lb = (b == k) ? SOps<T>::one() : lk[0][b * SP + k];
+          dd += (la * lk[0][k * SP + k]) * cj(lb, cs);
         }
         dt_all[l * pl.sq_elems + gp(pl.node_sq)[K] + (int64_t)b * s + a] = dd;
       }
@@ -763,16 +804,19 @@ __global__ void __launch_bounds__(64) k_normalize_small(const DevPlan *__restric
   for (int i0 = 0; i0 < c; i0 += 64) {
     const int i = i0 + t;
     if (i < c) {
-      T lr[S];
 #pragma unroll
-      for (int k = 0; k < S; ++k) lr[k] = k < s ? Q[(int64_t)k * ld + s + i] : zero_of<T>();
+      for (int h = 0; h < H; ++h) {
+        T lr[S];
+#pragma unroll
+        for (int k = 0; k < S; ++k) lr[k] = k < s ? Q[h * pl.half + (int64_t)k * ld + s + i] : zero_of<T>();
 #pragma unroll 1
-      for (int q = 0; q < s; ++q) {
-        T v = zero_of<T>();
+        for (int q = 0; q < s; ++q) {
+          T v = zero_of<T>();
 #pragma unroll
-        for (int k = 0; k < S; ++k)
-          if (k >= q && k < s) v += lr[k] * xs[k * SP + q];
-        P[(int64_t)q * ld + s + i] = v;
+          for (int k = 0; k < S; ++k)
+            if (k >= q && k < s) v += lr[k] * xs[h][k * SP + q];
+          P[h * pl.half + (int64_t)q * ld + s + i] = v;
+        }
       }
     }
   }
@@ -1006,12 +1050,13 @@ static hipError_t normalize_impl(const DevPlan &pl, const DevPlan *dpl, const La
     return aux.norm_cut[5 * (part + 1) + j] - b;
   };
   int32_t b;
-  // LU plans (no single-wavefront nodes) normalize both panel sets
+  // LU plans normalize both panel sets
   const int nsets = pl.half > 0 ? 2 : 1;
   const int32_t nsm = (steps & NORM_INV) ? range(0, aux.nsmall, b) : 0;
   if (nsm > 0)
-    hipLaunchKernelGGL(k_normalize_small<T>, dim3((unsigned)(nsm * pl.batch)), dim3(64), 0, st, dpl, Q, Lp,
-                       reinterpret_cast<T *>(dt), aux.small_nodes + b, nsm);
+    hipLaunchKernelGGL((nsets > 1 ? k_normalize_small<T, true> : k_normalize_small<T, false>),
+                       dim3((unsigned)(nsm * pl.batch)), dim3(64), 0, st, dpl, Q, Lp, reinterpret_cast<T *>(dt),
+                       aux.small_nodes + b, nsm);
   const int32_t nna = (steps & NORM_INV) ? range(1, aux.nchunks_narrow, b) : 0;
   if (nna > 0)
     hipLaunchKernelGGL((k_normalize_inv<T, 64>), dim3((unsigned)(nna * pl.batch * nsets)), dim3(NT), 0, st, dpl, Q,
@@ -1049,7 +1094,11 @@ template <typename T>
 static void launch_level(const DevPlan &pl, const DevPlan *dpl, const LaunchAux &aux, const T *Lp, T *Xp, T *Pp,
                          hipStream_t st, int q, int32_t b, int32_t e) {
   if (e <= b) return;
-  if (aux.lvl_kind[q] == LVL_TINY) {
+  if (aux.lvl_kind[q] == LVL_TINY && pl.half > 0) {
+    hipLaunchKernelGGL(k_tiny_lu, dim3((unsigned)((e - b) * pl.batch)), dim3(64), 0, st, dpl,
+                       reinterpret_cast<const double *>(Lp), reinterpret_cast<double *>(Xp),
+                       aux.tiny + aux.lvl_tiny[q] + (b - aux.lvl_ptr[q]), e - b, b);
+  } else if (aux.lvl_kind[q] == LVL_TINY) {
     // complex plans: the forward-only nodes (from lvl_tsplit[q]) in k_tiny64
     const int32_t ts = sizeof(T) == 16 && aux.lvl_tsplit[q] >= 0 ? aux.lvl_tsplit[q] : aux.lvl_ptr[q + 1];
     const int32_t m0 = std::min(e, std::max(b, ts));
