@@ -89,6 +89,9 @@ struct HostPlan {
   std::vector<int4> grp_ranges;   // {group, launch, first position, end position}
   std::vector<LRec> lvl_recs;  // the items of lvl_items with their nodes, in level order
   std::vector<TinyRec> tiny;  // single-wavefront nodes, in launch order
+  std::vector<int32_t> node_g2;  // row ranges of the node's GEMM-2 in k_gemm2_dense (0: shares of its row tiles)
+  std::vector<LRec> g2;          // its tiles, before the launch of their diagonal blocks (see LaunchAux)
+  std::vector<int32_t> g2_ptr, g2_mid, g2_cut;
   std::vector<PushRec> push;  // push-form tiles (SELINV_SCHED_PUSH), in launch order
   std::vector<uint32_t> toff;  // their X_{C,C} tables (byte offsets into the panel array)
   std::vector<int2> chunks, chunks_narrow, rblocks;
@@ -110,7 +113,7 @@ struct HostPlan {
   struct Off {
     int64_t node_s, node_c, node_off, node_rowptr, node_sq, node_first, node_poff, kcol, kpos, posarr, items, item_ptr,
         nph, node_split, node_kchunk, node_yoff, node_goff, node_ldg, node_parent, order, lvl_items, lvl_recs, chunks, chunks_narrow, rblocks, small_nodes,
-        sq_tiles, tiny, toff,
+        sq_tiles, tiny, toff, g2,
         apos, adiag, aflip, bitems, pushrecs, y128recs, fac_nodes, fac_rb, fac_tiles, dpos, plan, plan2, linv, dinv, part, gbuf, ypart,
         cnt, ctrl, fwd_end, adj_z, adj_l, adj_s, adj_t, adj_f, adj_d, ferr, fldet, finv, end;
   } off{};
@@ -136,6 +139,10 @@ void put(std::vector<unsigned char> &img, int64_t off, const std::vector<V> &v) 
 // dependencies, can never deadlock.
 constexpr int kSimWorkers = 256;
 constexpr int64_t kDefaultDenseMinC = 256;
+// Row tiles from which GEMM-2 is a product of its own (from 8 on only: the
+// same within 0.4% either way, 30.07 for 30.17 ms and 3.10 for 3.08 ms on
+// 32 complex 30^3 shifts and one FP64 40^3 matrix).
+constexpr int64_t kG2Rows = 4;
 constexpr int64_t kSplitTarget = 512;  // GEMM-1 tiles that keep every CU busy (2 per CU)
 constexpr int64_t kSplitMax = 8;
 constexpr int64_t kSplitMinK = 320;    // default shortest contraction part
@@ -455,6 +462,26 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   // the top depths: every depth down to here fills at most a quarter of the GPU
   int64_t top_depth = -1;
   while (top_depth + 1 < S.depth && dtiles[top_depth + 1] * 4 <= kSplitTarget) ++top_depth;
+  // GEMM-2 as a product of its own (level schedule): nodes with several
+  // 64-column blocks and at least kG2Rows row tiles.  Its row ranges are as
+  // few as fill the GPU with the depth's tiles, of two row tiles at least.
+  H.node_g2.assign(ns, 0);
+  if (sched == SELINV_SCHED_LEVELS) {
+    auto nq_of = [&](int64_t K) { return (S.width(K) + kTileN - 1) / kTileN; };
+    auto nr_of = [&](int64_t K) { return (S.nrows(K) + kTileM - 1) / kTileM; };
+    std::vector<int64_t> tiles(S.depth, 0);
+    for (int64_t K = 0; K < ns; ++K)
+      if (nq_of(K) > 1 && nr_of(K) >= kG2Rows && !tile128[K]) {
+        H.node_g2[K] = 1;
+        tiles[S.sdepth[K]] += batch * nq_of(K) * nq_of(K);
+      }
+    for (int64_t K = 0; K < ns; ++K) {
+      if (!H.node_g2[K]) continue;
+      const int64_t nr = nr_of(K), t = tiles[S.sdepth[K]];
+      const int64_t want = std::min<int64_t>(nr / 2, (kSplitTarget + t - 1) / t), ct = (nr + want - 1) / want;
+      H.node_g2[K] = (int32_t)((nr + ct - 1) / ct);
+    }
+  }
   for (int64_t K = 0; K < ns; ++K) {
     const int64_t s = S.width(K), c = S.nrows(K);
     H.node_kchunk[K] = (int32_t)c;
@@ -483,7 +510,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
     // at a depth with few tiles, also takes the R phase (one part): its
     // tiles' GEMM-2 shares are then cut into R items instead of running
     // block after block at the end of each GEMM-1 tile.
-    if (parts <= 1 && (push || lu || !(nq > 1 && dtiles[S.sdepth[K]] * nq <= kSplitTarget))) continue;
+    if (parts <= 1 && (push || lu || H.node_g2[K] || !(nq > 1 && dtiles[S.sdepth[K]] * nq <= kSplitTarget))) continue;
     H.node_split[K] = (int32_t)parts;
     H.node_kchunk[K] = (int32_t)chunk;
     H.node_yoff[K] = H.y_elems;
@@ -627,6 +654,8 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   auto adj_tiny = [&](int64_t K) { return !push && !lu && tiny_ok && H.node_c[K] <= kTinyC && H.node_s[K] <= kTinyS; };
   H.push.clear();
   H.y128.clear();
+  std::vector<Item> g2_items;
+  std::vector<int3> g2_at;  // {launch, its first tile, the second subtree group's first tile}
   if (push) {
     // per depth, root first: the D step of the depth's nodes (P items, then
     // D items), then every tile its nodes push into their descendants
@@ -693,6 +722,22 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
     for (int64_t d = 0; d < S.depth; ++d) {
       H.lvl_depth_first[d] = (int32_t)H.lvl_ptr.size() - 1;
       for (int ph = 0; ph < kPhases; ++ph) {
+        if (ph == 3) {
+          // the GEMM-2 tiles of the depth, before the launch of its diagonal blocks
+          const size_t q = H.lvl_ptr.size() - 1;
+          const int32_t first = (int32_t)g2_items.size();
+          int32_t mid = -1;
+          for (int64_t K : bydepth[d]) {
+            const bool second = !H.node_grp.empty() && H.node_grp[K] == 2;
+            if (second && mid < 0) mid = (int32_t)g2_items.size();
+            const int32_t nq = (H.node_s[K] + kTileN - 1) / kTileN;
+            for (int32_t part = 0; part < H.node_g2[K]; ++part)
+              for (int32_t b = 0; b < nq; ++b)
+                for (int32_t a = 0; a < nq; ++a) g2_items.push_back(Item{(int32_t)K, ITEM_P, a, b | (part << 16)});
+          }
+          if ((int32_t)g2_items.size() > first)
+            g2_at.push_back(int3{(int32_t)q, first, mid < 0 ? (int32_t)g2_items.size() : mid});
+        }
         // phase 1: gathered GEMM-1 tiles, the fused ones of nodes with a dense
         // buffer, and k_ydense's tiles; phase 3: diagonal blocks and
         // single-workgroup nodes: a launch each
@@ -795,15 +840,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
       H.grp_rptr[nl] = (int32_t)H.grp_ranges.size();
     }
   }
-  H.lvl_recs.resize(H.lvl_items.size());
-  for (size_t q = 0; q < H.lvl_items.size(); ++q) {
-    const int32_t kind =
-        H.lvl_kind[std::upper_bound(H.lvl_ptr.begin(), H.lvl_ptr.end(), (int32_t)q) - H.lvl_ptr.begin() - 1];
-    if (kind == LVL_PUSH || kind == LVL_Y128) {
-      H.lvl_recs[q] = LRec{};  // push tiles and 128-tile records carry their own records
-      continue;
-    }
-    const Item &it = H.items[H.lvl_items[q]];
+  auto record = [&](const Item &it) {
     const int64_t K = it.K;
     NodeInfo n{};
     n.K = it.K;
@@ -812,7 +849,9 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
     n.ldg = H.node_ldg[K];
     n.split = H.node_split[K];
     n.kchunk = H.node_kchunk[K];
-    n.defer2 = H.node_defer[K];
+    n.defer2 = H.node_defer[K] || H.node_g2[K];
+    n.g2 = H.node_g2[K] > 0;
+    n.np = n.g2 ? H.node_g2[K] : (n.c + kTileM - 1) / kTileM;
     // the dense buffer of a node whose GEMM-1 runs in k_ydense holds the
     // lower triangle only (k_ydense reads the rest mirrored)
     n.glow = H.node_ykern[K] && !H.node_y128[K] && !lu;
@@ -821,7 +860,32 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
     n.goff = H.node_goff[K];
     n.poff = H.node_poff[K];
     n.yoff = H.node_yoff[K];
-    H.lvl_recs[q] = LRec{it, n};
+    return LRec{it, n};
+  };
+  H.lvl_recs.resize(H.lvl_items.size());
+  for (size_t q = 0; q < H.lvl_items.size(); ++q) {
+    const int32_t kind =
+        H.lvl_kind[std::upper_bound(H.lvl_ptr.begin(), H.lvl_ptr.end(), (int32_t)q) - H.lvl_ptr.begin() - 1];
+    if (kind == LVL_PUSH || kind == LVL_Y128) {
+      H.lvl_recs[q] = LRec{};  // push tiles and 128-tile records carry their own records
+      continue;
+    }
+    H.lvl_recs[q] = record(H.items[H.lvl_items[q]]);
+  }
+  // GEMM-2 tiles by launch
+  const int32_t nl = (int32_t)H.lvl_ptr.size() - 1, n2 = (int32_t)g2_items.size();
+  H.g2.clear();
+  for (const Item &it : g2_items) H.g2.push_back(record(it));
+  H.g2_ptr.assign(nl + 1, 0);
+  H.g2_mid.assign(nl, 0);
+  H.g2_cut.assign(nl, INT32_MAX);
+  for (size_t i = 0; i < g2_at.size(); ++i) {
+    const int32_t q = g2_at[i].x, end = i + 1 < g2_at.size() ? g2_at[i + 1].y : n2;
+    for (int32_t p = q + 1; p <= nl; ++p) H.g2_ptr[p] = end;
+    H.g2_mid[q] = g2_at[i].z;
+    if (g2_at[i].z == end) continue;
+    for (int32_t p = H.lvl_ptr[q + 1] - 1; p >= H.lvl_ptr[q]; --p)
+      if (H.node_grp[H.items[H.lvl_items[p]].K] == 2) H.g2_cut[q] = p;
   }
   // adjoint launches (see adjoint.hip): R1 leaves -> root (deepest level
   // first), R2 for all nodes, then R3 root -> leaves
@@ -1044,6 +1108,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   o.lvl_recs = take((int64_t)sizeof(LRec) * (int64_t)H.lvl_items.size());
   o.tiny = take((int64_t)sizeof(TinyRec) * (int64_t)H.tiny.size());
   o.toff = take(4 * (int64_t)H.toff.size());
+  o.g2 = take((int64_t)sizeof(LRec) * (int64_t)H.g2.size());
   o.chunks = take(8 * (int64_t)H.chunks.size());
   o.chunks_narrow = take(8 * (int64_t)H.chunks_narrow.size());
   o.small_nodes = take(4 * (int64_t)H.small_nodes.size());
@@ -1376,6 +1441,10 @@ LaunchAux make_aux(const selinv_ctx *h, void *work) {
   a.push = (const PushRec *)(b + H.off.pushrecs);
   a.y128 = (const Item *)(b + H.off.y128recs);
   a.tiny = (const TinyRec *)(b + H.off.tiny);
+  a.g2 = (const LRec *)(b + H.off.g2);
+  a.g2_ptr = H.g2_ptr.data();
+  a.g2_mid = H.g2_mid.data();
+  a.g2_cut = H.g2_cut.data();
   a.nlvl = (int32_t)H.lvl_ptr.size() - 1;
   a.blaunch = H.blaunch.data();
   a.nblaunch = (int32_t)H.blaunch.size();
@@ -1417,6 +1486,7 @@ void build_image(selinv_ctx *h) {
   put(img, o.lvl_recs, H.lvl_recs);
   put(img, o.tiny, H.tiny);
   put(img, o.toff, H.toff);
+  put(img, o.g2, H.g2);
   put(img, o.chunks, H.chunks);
   put(img, o.chunks_narrow, H.chunks_narrow);
   put(img, o.small_nodes, H.small_nodes);

@@ -46,6 +46,8 @@ __device__ __forceinline__ NodeInfo uniform(const NodeInfo &a) {
   n.goff = uniform64(a.goff);
   n.poff = uniform64(a.poff);
   n.yoff = uniform64(a.yoff);
+  n.np = uniform(a.np);
+  n.g2 = uniform(a.g2);
   return n;
 }
 
@@ -65,7 +67,8 @@ __device__ __forceinline__ NodeInfo node_info(const DevPlan &pl, int K) {
   n.goff = uniform64(gp(pl.node_goff)[K]);
   n.poff = uniform64(gp(pl.node_poff)[K]);
   n.yoff = uniform64(gp(pl.node_yoff)[K]);
-  n.pad2 = 0;
+  n.np = (n.c + 63) / 64;
+  n.g2 = 0;
   return n;
 }
 
@@ -445,6 +448,40 @@ __device__ __forceinline__ void do_ygather(const Ctx<T> &cx, const NodeInfo &nd,
   }
 }
 
+// Rows i0 .. i0 + 63, columns [j0, j1) of X_{C,K} from a split node's partial tiles.
+template <typename T>
+__device__ __forceinline__ void sum_columns(const Ctx<T> &cx, const NodeInfo &nd, int i0, int j0, int j1) {
+  const int s = nd.s, c = nd.c, parts = nd.split;
+  constexpr int U = 4, PB = 4 / Planes<T>::P;  // columns of a wavefront, parts per round trip
+  const int i = i0 + (int)(threadIdx.x & 63), w = uniform((int)(threadIdx.x >> 6));
+  const uint32_t row = (uint32_t)(i < c ? i : 0) * (uint32_t)sizeof(T);
+  const T *Y = static_cast<const T *>(cx.Yp) + nd.yoff;
+  T *X = cx.Xp + nd.off + s + i;
+  for (int j = j0 + w; j < j1; j += U * (NT / 64)) {
+    T sum[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum[u] = zero_of<T>();
+    for (int p0 = 0; p0 < parts; p0 += PB) {
+      T v[PB][U];
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          v[p][u] = ld_off(Y + ((int64_t)min(p0 + p, parts - 1) * s + min(j + u * (NT / 64), j1 - 1)) * c, row);
+#pragma unroll
+      for (int p = 0; p < PB; ++p) {
+        if (p > 0 && p0 + p >= parts) break;
+#pragma unroll
+        for (int u = 0; u < U; ++u) sum[u] += v[p][u];
+      }
+    }
+    if (i < c)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j + u * (NT / 64) < j1) gstore(X + (int64_t)(j + u * (NT / 64)) * (s + c), SOps<T>::scale(-1.0, sum[u]));
+  }
+}
+
 // Sum of a split node's partial tiles (a, b) into X, then the row tile's share
 // of GEMM-2 (the step-3 and step-4 work that an unsplit tile does itself).
 // With br = b | r << 16 | rq << 24 and rq > 1, the tile's GEMM-2 share is cut
@@ -460,6 +497,12 @@ __device__ void do_rtile(const Ctx<T> &cx, const NodeInfo &nd, int a, int br, do
   const int parts = uniform(nd.split);
   const T *Y = static_cast<const T *>(cx.Yp) + nd.yoff;
   const int i0 = a * 64, j0 = b * 64;
+  if constexpr (!COH) {
+    if (uniform(nd.g2)) {  // the sum alone: columns [64 r / rq, 64 (r + 1) / rq) of the tile
+      sum_columns<T>(cx, nd, i0, j0 + 64 * r / rq, min(s, j0 + 64 * (r + 1) / rq));
+      return;
+    }
+  }
   constexpr int Q = 64 * 64 / NT;
   T sum[Q];
 #pragma unroll
@@ -611,15 +654,38 @@ __device__ __forceinline__ void do_ytile_dense(const Ctx<T> &cx, const NodeInfo 
   }
 }
 
+// GEMM-2 tile: rows 64 a .. and columns 64 b .. of P = Lhat^T X_{C,K} over the
+// row range `part` of np (LU: Uhat X_{C,K}), into the node's partial product
+// `part`.  Both operands run along the contraction.
+template <typename T>
+__device__ __forceinline__ void do_gemm2(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, int part, double *smem) {
+  const int s = uniform(nd.s), c = uniform(nd.c), ld = s + c;
+  const int nr = (c + 63) / 64, ct = 64 * ((nr + nd.np - 1) / nd.np);  // rows of a range
+  const int kb = part * ct, ke = min(c, kb + ct);
+  constexpr int TK = DenseTK<T>::TK;
+  LoadDenseBC<T, TK> la{cx.Lp + cx.pl->half, nd.off, ld, s, ke, 64 * a, s};
+  la.cs = cx.pl->csign;
+  LoadDenseB<T, TK> lb{cx.Xp, nd.off, ld, s, ke, 64 * b, s};
+  Acc<T> acc;
+  gemm_dense_il<T, true>(kb, ke, la, lb, smem, acc);
+  acc_to_lds<T>(acc, smem);
+  lds_barrier();
+  T *P = cx.Pp + nd.poff + (int64_t)part * s * s;
+  for (int e = threadIdx.x; e < 64 * 64; e += NT) {
+    const int x = e & 63, j = e >> 6;
+    if (64 * a + x < s && 64 * b + j < s) gstore(P + (int64_t)(64 * b + j) * s + 64 * a + x, lds_get<T>(smem, x, j));
+  }
+}
+
 // Blocks (a, b) and (b, a), a >= b, of sym(Src - sum_r P_r) into Dst, where
 // Src and Dst are s x s column-major with leading dimensions sld and dld and
-// P_r are the node's row-tile partial products.
+// P_r are the node's np partial products.
 template <typename T, bool COH>
 __device__ void dtile_core(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, double *smem, const T *Dti, int sld, T *Xkk,
                            int dld) {
   const DevPlan &pl = *cx.pl;
-  const int s = nd.s, c = nd.c;
-  const int nr = (c + 63) / 64;
+  const int s = nd.s;
+  const int nr = nd.np;
   const int64_t pb = nd.poff;
   const int64_t ss = (int64_t)s * s;
   const int a0 = a * 64, b0 = b * 64;
@@ -727,8 +793,8 @@ __device__ void dtile_slab(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, i
   constexpr int W = kDSlabW, WP = kDSlabP, QE = 64 * W / NT;
   constexpr int R = Planes<T>::P == 1 ? 4 : 2;  // row tiles per round trip
   const DevPlan &pl = *cx.pl;
-  const int s = nd.s, c = nd.c;
-  const int nr = uniform((c + 63) / 64);
+  const int s = nd.s;
+  const int nr = uniform(nd.np);
   const int64_t pb = nd.poff;
   const int64_t ss = (int64_t)s * s;
   const int a0 = a * 64, b0 = b * 64 + sl * W;

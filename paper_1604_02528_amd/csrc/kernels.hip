@@ -133,6 +133,28 @@ __global__ void __launch_bounds__(NT, 2) k_gemm2_list(const DevPlan *__restrict_
   }
 }
 
+// GEMM-2 of the nodes with several 64-column blocks as a product of its own:
+// each tile of Lhat^T X_{C,K} is contracted over a range of rows that is as
+// long as the depth's tiles allow while they fill the GPU.  A share per 64-row
+// tile at the end of GEMM-1 writes, and the diagonal blocks read back, an s x s
+// block per 64 rows, and its products of depth 64 run unpipelined.
+// Normalization and traversal, before and after: 32 complex 30^3 shifts 32.2
+// and 30.1 ms, 27-point 64^3, two shifts, 128.6 and 124.6 ms, FP64 40^3 3.15
+// and 3.09 ms, LU form 30^3, four shifts, 4.10 and 4.00 ms.
+template <typename T>
+__global__ void __launch_bounds__(NT, 2) k_gemm2_dense(const DevPlan *__restrict__ plp, const T *Lp, T *Xp, T *Pp,
+                                                       const LRec *recs, int32_t count) {
+  const DevPlan &pl = *plp;
+  constexpr int kStages = 2 * dense_stage_doubles<T, DenseTK<T>::TK>();
+  __shared__ double smem[kStages > tile_doubles<T>() ? kStages : tile_doubles<T>()];
+  const int64_t g = blockIdx.x;
+  const int64_t l = g / count;
+  Ctx<T> cx{&pl, Lp + l * pl.panel_elems, Xp + l * pl.panel_elems, Pp + l * pl.part_elems, nullptr, nullptr};
+  const LRec rec = recs[g - l * count];
+  const Item it = uniform(rec.it);
+  do_gemm2<T>(cx, uniform(rec.nd), it.a, it.b & 0xffff, it.b >> 16, smem);
+}
+
 // Rows of the trace for a launch of the list kernels below.
 __device__ __forceinline__ void trace_item(const DevPlan &pl, const int32_t *list, int64_t l, int64_t q, int64_t g,
                                            int32_t list_pos, int64_t t_start) {
@@ -1094,6 +1116,13 @@ template <typename T>
 static void launch_level(const DevPlan &pl, const DevPlan *dpl, const LaunchAux &aux, const T *Lp, T *Xp, T *Pp,
                          hipStream_t st, int q, int32_t b, int32_t e) {
   if (e <= b) return;
+  if (aux.g2_ptr[q + 1] > aux.g2_ptr[q]) {  // GEMM-2 of the nodes whose diagonal blocks this launch runs
+    const int32_t g0 = b < aux.g2_cut[q] ? aux.g2_ptr[q] : aux.g2_mid[q];
+    const int32_t g1 = e > aux.g2_cut[q] ? aux.g2_ptr[q + 1] : aux.g2_mid[q];
+    if (g1 > g0)
+      hipLaunchKernelGGL(k_gemm2_dense<T>, dim3((unsigned)((g1 - g0) * pl.batch)), dim3(NT), 0, st, dpl, Lp, Xp, Pp,
+                         aux.g2 + g0, g1 - g0);
+  }
   if (aux.lvl_kind[q] == LVL_TINY && pl.half > 0) {
     hipLaunchKernelGGL(k_tiny_lu, dim3((unsigned)((e - b) * pl.batch)), dim3(64), 0, st, dpl,
                        reinterpret_cast<const double *>(Lp), reinterpret_cast<double *>(Xp),

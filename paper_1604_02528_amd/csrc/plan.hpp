@@ -17,6 +17,8 @@
 //           unsplit nodes of sparsely filled depths whose share spans several
 //           64-row blocks); with rq > 1 the share is cut into rq items by
 //           64-row blocks of the s x s product and item r = 0 stores the tile.
+//           Where k_gemm2_dense runs the node's GEMM-2, the rq items share the
+//           tile's columns instead and only sum.
 //   ITEM_D  (K, a, b), a >= b: blocks (a, b) and (b, a) of X_KK = Dt_K^{-1} -
 //           Lhat_{C,K}^T X_{C,K} (step 4), symmetrized (Section 2.3).  Nodes
 //           with at least kDSlabRows row tiles split each block pair into
@@ -104,7 +106,8 @@ struct alignas(16) NodeInfo {
                                         // glow: the dense buffer holds the lower triangle and the diagonal
                                         // 64 x 64 blocks only (its GEMM-1 reads the rest mirrored)
   int64_t off, rp, goff;     // panel offset, first row of C(K) in the row tables, dense buffer (-1: none)
-  int64_t poff, yoff, pad2;  // GEMM-2 partial products, partial tiles of a split contraction
+  int64_t poff, yoff;        // GEMM-2 partial products, partial tiles of a split contraction
+  int32_t np, g2;            // s x s blocks of GEMM-2 partial products; GEMM-2 in k_gemm2_dense (over np row ranges)
 };
 struct alignas(16) LRec {
   Item it;
@@ -231,6 +234,11 @@ struct LaunchAux {
   const Item *y128;         // 128 x 128 GEMM-1 tiles of FP64 dense-buffer nodes (LVL_Y128 launches
                             // start at lvl_tiny[q]): {K, ITEM_Y, row tile, column tile | part << 16}
   const TinyRec *tiny;      // single-wavefront node records, in launch order
+  // GEMM-2 tiles {K, -, 64-column block of Lhat, 64-column block of X_{C,K} | part << 16} (see
+  // k_gemm2_dense): [g2_ptr[q], g2_ptr[q + 1]) run before level launch q, those from g2_mid[q] on
+  // before its positions from g2_cut[q] on (the second subtree group's).  Host arrays [nlvl (+ 1)].
+  const LRec *g2;
+  const int32_t *g2_ptr, *g2_mid, *g2_cut;
   int32_t nlvl;
   const int4 *blaunch;        // host array: adjoint launches {BackStep, first, count, 0} in order: bitems
                               // [first, first + count), or small-node records (BS_TINY_R1, BS_TINY_R3)

@@ -692,6 +692,23 @@ template <typename T, int TK> struct LoadDenseB {
   }
 };
 
+// The same block as a left operand, A(x, kk), conjugated where cs = -1 (the
+// stages of both operands are laid out alike).
+template <typename T, int TK> struct LoadDenseBC : LoadDenseB<T, TK> {
+  using LoadDenseB<T, TK>::LoadDenseB;
+  static constexpr int E = LoadDenseB<T, TK>::E;
+  double cs = 1.0;
+  __device__ __forceinline__ void store_bf(double *stg, int plane_off, int k0, const DVals<T, TK> &v) const {
+    constexpr int P = Planes<T>::P;
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      const T x = cj(masked(v.v[m], this->mask(k0, m)), cs);
+#pragma unroll
+      for (int p = 0; p < P; ++p) stg[(plane_off + p) * TK * PITCH + this->slot(k0, m)] = Planes<T>::get(x, p);
+    }
+  }
+};
+
 // B(k, x) = M[k * ld + x0 + x] for k < kend, x0 + x < xmax: a row-major view
 // (the transpose of a column-major block); lanes run along x, and the row of a
 // slot, k0 + (t >> 6) + 4 m, is uniform in a wave.
