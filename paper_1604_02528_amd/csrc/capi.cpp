@@ -94,7 +94,8 @@ struct HostPlan {
   std::vector<int32_t> g2_ptr, g2_mid, g2_cut;
   std::vector<PushRec> push;  // push-form tiles (SELINV_SCHED_PUSH), in launch order
   std::vector<uint32_t> toff;  // their X_{C,C} tables (byte offsets into the panel array)
-  std::vector<int2> chunks, chunks_narrow, rblocks;
+  std::vector<int2> chunks, chunks_narrow, rblocks, rtiles;
+  std::vector<int32_t> rt_cut;
   std::vector<int32_t> small_nodes;  // normalized by the single-wavefront kernel
   std::vector<int4> sq_tiles;
   std::vector<int64_t> apos;
@@ -112,7 +113,7 @@ struct HostPlan {
   // byte offsets inside the work buffer
   struct Off {
     int64_t node_s, node_c, node_off, node_rowptr, node_sq, node_first, node_poff, kcol, kpos, posarr, items, item_ptr,
-        nph, node_split, node_kchunk, node_yoff, node_goff, node_ldg, node_parent, order, lvl_items, lvl_recs, chunks, chunks_narrow, rblocks, small_nodes,
+        nph, node_split, node_kchunk, node_yoff, node_goff, node_ldg, node_parent, order, lvl_items, lvl_recs, chunks, chunks_narrow, rblocks, rtiles, small_nodes,
         sq_tiles, tiny, toff, g2,
         apos, adiag, aflip, bitems, pushrecs, y128recs, fac_nodes, fac_rb, fac_tiles, dpos, plan, plan2, linv, dinv, part, gbuf, ypart,
         cnt, ctrl, fwd_end, adj_z, adj_l, adj_s, adj_t, adj_f, adj_d, ferr, fldet, finv, end;
@@ -934,6 +935,8 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   H.chunks.clear();
   H.chunks_narrow.clear();
   H.rblocks.clear();
+  H.rtiles.clear();
+  H.rt_cut.clear();
   H.sq_tiles.clear();
   H.small_nodes.clear();
   H.lvl_cut.clear();
@@ -972,6 +975,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
       H.norm_cut.push_back((int32_t)H.chunks.size());
       H.norm_cut.push_back((int32_t)H.rblocks.size());
       H.norm_cut.push_back((int32_t)H.sq_tiles.size());
+      H.rt_cut.push_back((int32_t)H.rtiles.size());
     };
     mark();
     H.lvl_cut.push_back(0);
@@ -992,7 +996,15 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
         }
         const int32_t nch = (s + 15) / 16;  // 16-column blocks of L_KK^{-1} (s <= 256)
         for (int32_t q = 0; q < nch; ++q) (s <= 64 ? H.chunks_narrow : H.chunks).push_back(int2{(int32_t)K, q});
-        for (int32_t a = 0; a < (c + kTileM - 1) / kTileM; ++a) H.rblocks.push_back(int2{(int32_t)K, a});
+        const int32_t nrb = (c + kTileM - 1) / kTileM, ncb = (s + kTileN - 1) / kTileN;
+        for (int32_t a = 0; a < nrb; ++a) H.rblocks.push_back(int2{(int32_t)K, a});
+        // eight row blocks at a time, column block by column block: workgroups
+        // eight apart run on one XCD, whose L2 then holds the rows for all of them
+        if (scalar_bytes == 8)
+          for (int32_t a0 = 0; a0 < nrb; a0 += 8)
+            for (int32_t x = 0; x < ncb; ++x)
+              for (int32_t a = a0; a < std::min(nrb, a0 + 8); ++a)
+                H.rtiles.push_back(int2{(int32_t)K, a | x << kRowBlockBits});
         const int32_t nt = (s + 31) / 32;
         for (int32_t a = 0; a < nt; ++a)
           for (int32_t b = 0; b < nt; ++b) H.sq_tiles.push_back(int4{(int32_t)K, a, b, 0});
@@ -1113,6 +1125,7 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   o.chunks_narrow = take(8 * (int64_t)H.chunks_narrow.size());
   o.small_nodes = take(4 * (int64_t)H.small_nodes.size());
   o.rblocks = take(8 * (int64_t)H.rblocks.size());
+  o.rtiles = take(8 * (int64_t)H.rtiles.size());
   o.sq_tiles = take(16 * (int64_t)H.sq_tiles.size());
   o.apos = take(8 * (int64_t)H.apos.size());
   o.adiag = take((int64_t)H.adiag.size());
@@ -1430,6 +1443,9 @@ LaunchAux make_aux(const selinv_ctx *h, void *work) {
   a.nchunks_narrow = (int32_t)H.chunks_narrow.size();
   a.rblocks = (const int2 *)(b + H.off.rblocks);
   a.nrblocks = (int32_t)H.rblocks.size();
+  a.rtiles = (const int2 *)(b + H.off.rtiles);
+  a.nrtiles = (int32_t)H.rtiles.size();
+  a.rt_cut = H.rt_cut.data();
   a.sq_tiles = (const int4 *)(b + H.off.sq_tiles);
   a.nsq_tiles = (int32_t)H.sq_tiles.size();
   a.lvl_items = (const int32_t *)(b + H.off.lvl_items);
@@ -1491,6 +1507,7 @@ void build_image(selinv_ctx *h) {
   put(img, o.chunks_narrow, H.chunks_narrow);
   put(img, o.small_nodes, H.small_nodes);
   put(img, o.rblocks, H.rblocks);
+  put(img, o.rtiles, H.rtiles);
   put(img, o.sq_tiles, H.sq_tiles);
   put(img, o.apos, H.apos);
   put(img, o.adiag, H.adiag);

@@ -844,13 +844,17 @@ __global__ void __launch_bounds__(64) k_normalize_small(const DevPlan *__restric
   }
 }
 
-// Lhat_{C,K} = L_{C,K} L_KK^{-1} (Alg. 1 steps 1-2) for one 64-row block a of
-// C(K), column tiles left to right on MFMA (hs = 1, LU plans: Uhat_{K,C}^T =
-// U_{K,C}^T U_KK^{-T} in the second panel set).  Column x of Lhat needs only
-// columns k >= x of L (L_KK^{-1} is lower triangular), so a workgroup that
-// owns its row block and writes tile b after finishing it never reads a
-// column it has already overwritten: Q may alias P.
-template <typename T>
+// Lhat_{C,K} = L_{C,K} L_KK^{-1} (Alg. 1 steps 1-2) on MFMA (hs = 1, LU plans:
+// Uhat_{K,C}^T = U_{K,C}^T U_KK^{-T} in the second panel set).  Column x of
+// Lhat needs columns k >= x of L only (L_KK^{-1} is lower triangular), so a
+// workgroup that takes all tiles of a 64-row block, left to right (TILE =
+// false), never reads a column that it has overwritten: Q may alias P.  TILE:
+// one 64 x 64 tile to a workgroup, for FP64 panels that are not normalized in
+// place; there a row block at a time leaves a few long workgroups (40^3: 3.10
+// and 3.07 ms with the traversal; LU form 30^3, four shifts: 4.01 and 3.94).
+// Complex launches are bound by the panels' traffic, which reading the row
+// block once per tile adds to (32 shifts of 30^3: 30.1 and 30.5 ms).
+template <typename T, bool TILE>
 __global__ void __launch_bounds__(NT, 2)
     k_normalize_gemm(const DevPlan *__restrict__ plp, const T *Src_all, T *Lp_all, const int2 *rblocks, int32_t nrb,
                      int nsets) {
@@ -865,22 +869,23 @@ __global__ void __launch_bounds__(NT, 2)
   const int64_t g = blockIdx.x - hs * per;
   const int64_t l = g / nrb;
   const int2 rb = rblocks[g - l * nrb];
-  const int K = uniform(rb.x), i0 = uniform(rb.y) * 64;
+  const int K = uniform(rb.x), i0 = uniform(rb.y & kRowBlockMask) * 64, xt = TILE ? uniform(rb.y >> kRowBlockBits) * 64 : 0;
   const int s = uniform(gp(pl.node_s)[K]), c = uniform(gp(pl.node_c)[K]), ld = s + c;
   const int64_t off = gp(pl.node_off)[K] + hs * pl.half;
   const T *Q = Src_all + l * pl.panel_elems + off;
   T *P = Lp_all + l * pl.panel_elems + off;
   const T *Linv = reinterpret_cast<const T *>(pl.linv) + (hs * pl.batch + l) * pl.sq_elems + gp(pl.node_sq)[K];
-  for (int x0 = 0; x0 < s; x0 += 64) {
-    LoadDenseA<T, TK> la{Q + s, ld, c, s, i0};      // L_{C,K}(i, k)
+  const int xend = TILE ? xt + 1 : s;
+  for (int x0 = xt; x0 < xend; x0 += 64) {
+    LoadDenseAIl<T, TK> la{Q + s, ld, c, s, i0};    // L_{C,K}(i, k)
     LoadDenseB<T, TK> lb{Linv, 0, s, 0, s, x0, s};  // L_KK^{-1}(k, x)
     Acc<T> acc;
-    gemm_dense<T, true>(x0, s, la, lb, smem, acc);  // complex: three real product chains
+    gemm_dense_il<T, true>(x0, s, la, lb, smem, acc);  // complex: three real product chains
     acc_to_lds<T>(acc, smem);
     lds_barrier();
     for (int e = threadIdx.x; e < 64 * 64; e += NT) {
       const int i = e & 63, x = e >> 6;
-      if (i0 + i < c && x0 + x < s) P[(int64_t)(x0 + x) * ld + s + i0 + i] = lds_get<T>(smem, i, x);
+      if (i0 + i < c && x0 + x < s) gstore(P + (int64_t)(x0 + x) * ld + s + i0 + i, lds_get<T>(smem, i, x));
     }
     lds_barrier();
   }
@@ -1088,9 +1093,14 @@ static hipError_t normalize_impl(const DevPlan &pl, const DevPlan *dpl, const La
     hipLaunchKernelGGL((k_normalize_inv<T, 256>), dim3((unsigned)(nch * pl.batch * nsets)), dim3(NT), 0, st, dpl, Q,
                        aux.chunks + b, nch, nsets);
   const int32_t nrb = (steps & NORM_GEMM) ? range(3, aux.nrblocks, b) : 0;
-  if (nrb > 0)
-    hipLaunchKernelGGL(k_normalize_gemm<T>, dim3((unsigned)(nrb * pl.batch * nsets)), dim3(NT), 0, st, dpl, Q, Lp,
+  if (nrb > 0 && sizeof(T) == 8 && src != panels) {
+    const int32_t b0 = part < 0 ? 0 : aux.rt_cut[part], nt = (part < 0 ? aux.nrtiles : aux.rt_cut[part + 1]) - b0;
+    hipLaunchKernelGGL((k_normalize_gemm<T, true>), dim3((unsigned)(nt * pl.batch * nsets)), dim3(NT), 0, st, dpl, Q, Lp,
+                       aux.rtiles + b0, nt, nsets);
+  } else if (nrb > 0) {
+    hipLaunchKernelGGL((k_normalize_gemm<T, false>), dim3((unsigned)(nrb * pl.batch * nsets)), dim3(NT), 0, st, dpl, Q, Lp,
                        aux.rblocks + b, nrb, nsets);
+  }
   const int32_t nsq = (steps & NORM_SQ) ? range(4, aux.nsq_tiles, b) : 0;
   if (nsq > 0) {
     if (dt)

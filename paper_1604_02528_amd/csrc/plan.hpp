@@ -90,6 +90,7 @@ constexpr int kTileM = 64;   // GEMM-1 rows per item
 constexpr int kTileN = 64;   // columns per item (of s)
 constexpr int kSmallC = 64;  // fused single-item node bounds
 constexpr int kSmallNormS = 16;  // widest node normalized by the single-wavefront kernel
+constexpr int kRowBlockBits = 28, kRowBlockMask = (1 << kRowBlockBits) - 1;  // (s <= 256: four column blocks)
 constexpr int kDSlabW = 16;     // column slab of a split ITEM_D
 constexpr int kDSlabRows = 4;   // row tiles from which ITEM_D splits
 constexpr int kSmallS = 64;
@@ -222,6 +223,9 @@ struct LaunchAux {
   int32_t nchunks_narrow;
   const int2 *rblocks;      // normalization GEMM row blocks (K, 64-row block of C(K))
   int32_t nrblocks;
+  const int2 *rtiles;       // its tiles, FP64 (K, row block | 64-column block << kRowBlockBits)
+  int32_t nrtiles;
+  const int32_t *rt_cut;    // host array: their normalization chunks (see norm_cut)
   const int4 *sq_tiles;     // normalization 32 x 32 tiles (K, ti, tj, 0)
   int32_t nsq_tiles;
   const int32_t *lvl_items; // item ids grouped by (level, phase)

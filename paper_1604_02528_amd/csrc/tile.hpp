@@ -827,32 +827,16 @@ __device__ __forceinline__ void stage_compute_3m(const double *stg, Acc3M &acc) 
 // register sets alternate, so the loads of a stage are issued two
 // stage-computations before they are stored to LDS; waits are counted waits
 // on the older set only.  kb, ke and accumulate must be wave-uniform.
-// G3: complex products in the three-chain form (Acc3M) instead of four.
-template <typename T, bool G3 = false, class LA, class LB>
+template <typename T, class LA, class LB>
 __device__ __forceinline__ void gemm_dense(int kb, int ke, const LA &la, const LB &lb, double *smem, Acc<T> &acc,
                                            bool accumulate = false) {
   constexpr int TK = DenseTK<T>::TK, P = Planes<T>::P;
-  constexpr bool M3 = G3 && P == 2;
   constexpr int SD = dense_stage_doubles<T, TK>();
   using V = DVals<T, TK>;
   if (!accumulate) acc_zero<T>(acc);
   const int nk = (ke - kb + TK - 1) / TK;
   if (nk <= 0) return;
-  Acc3M a3;
-  if constexpr (M3) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) a3.v[q][bi][bj] = d4{0.0, 0.0, 0.0, 0.0};
-  }
-  auto compute = [&](const double *stg) {
-    if constexpr (M3)
-      stage_compute_3m<TK>(stg, a3);
-    else
-      stage_compute<T, TK>(stg, acc);
-  };
+  auto compute = [&](const double *stg) { stage_compute<T, TK>(stg, acc); };
   const int klast = kb + (nk - 1) * TK;
   auto kat = [&](int j) { return min(kb + j * TK, klast); };
   V a0, b0, a1, b1;
@@ -883,17 +867,6 @@ __device__ __forceinline__ void gemm_dense(int kb, int ke, const LA &la, const L
     la.load(kat(kt + 4), a0);
     lb.load(kat(kt + 4), b0);
     __builtin_amdgcn_sched_barrier(0);
-  }
-  if constexpr (M3) {
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < 2; ++bj) {
-        const d4 re = a3.v[0][bi][bj] - a3.v[1][bi][bj];
-        const d4 im = a3.v[2][bi][bj] - a3.v[0][bi][bj] - a3.v[1][bi][bj];
-        acc.v[0][bi][bj] += re;
-        acc.v[1][bi][bj] += im;
-      }
   }
   lds_barrier();  // the caller reuses the stage buffers
 }
