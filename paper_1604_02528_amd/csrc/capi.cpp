@@ -92,6 +92,12 @@ struct HostPlan {
   std::vector<int32_t> node_g2;  // row ranges of the node's GEMM-2 in k_gemm2_dense (0: shares of its row tiles)
   std::vector<LRec> g2;          // its tiles, before the launch of their diagonal blocks (see LaunchAux)
   std::vector<int32_t> g2_ptr, g2_mid, g2_cut;
+  // bottom subtrees of single-wavefront nodes, one workgroup each (see subtrees)
+  std::vector<TinyRec> sub_rec;             // records by group and step
+  std::vector<int32_t> sub_step;            // first record of each step (and the end)
+  std::vector<int2> sub_grp;                // {first step, steps}
+  int32_t sub_split = 0, sub_width = 0;     // groups of the first stream; widest step
+  std::vector<int32_t> lvl_u0, lvl_u1;      // [nlvl]: the positions that no group holds (single-wavefront launches)
   std::vector<PushRec> push;  // push-form tiles (SELINV_SCHED_PUSH), in launch order
   std::vector<uint32_t> toff;  // their X_{C,C} tables (byte offsets into the panel array)
   std::vector<int2> chunks, chunks_narrow, rblocks, rtiles;
@@ -114,7 +120,7 @@ struct HostPlan {
   struct Off {
     int64_t node_s, node_c, node_off, node_rowptr, node_sq, node_first, node_poff, kcol, kpos, posarr, items, item_ptr,
         nph, node_split, node_kchunk, node_yoff, node_goff, node_ldg, node_parent, order, lvl_items, lvl_recs, chunks, chunks_narrow, rblocks, rtiles, small_nodes,
-        sq_tiles, tiny, toff, g2,
+        sq_tiles, tiny, toff, g2, sub_rec, sub_step, sub_grp,
         apos, adiag, aflip, bitems, pushrecs, y128recs, fac_nodes, fac_rb, fac_tiles, dpos, plan, plan2, linv, dinv, part, gbuf, ypart,
         cnt, ctrl, fwd_end, adj_z, adj_l, adj_s, adj_t, adj_f, adj_d, ferr, fldet, finv, end;
   } off{};
@@ -401,6 +407,35 @@ void back_items(const HostPlan &H, int64_t K, int32_t type, std::vector<Item> &o
   }
 }
 
+// The bottom subtrees that one workgroup runs on its own: the largest ones
+// whose nodes all satisfy ok, at most kSubWidth of them at one depth and at
+// most kSubHeight depths.  Their nodes depend on each other and on finished
+// nodes above them only, so a depth costs a workgroup barrier in place of a
+// launch.  in[K]: the depths of K's subtree if K belongs to one, else 0.
+std::vector<int32_t> subtrees(const Symbolic &S, const std::function<bool(int64_t)> &ok) {
+  const int64_t ns = S.nsuper();
+  std::vector<int32_t> in(ns, 0);
+  std::vector<std::vector<int32_t>> width(ns);  // nodes of K's subtree by depth below K
+  std::vector<uint8_t> bad(ns, 0);              // a child outside any subtree
+  for (int64_t K = 0; K < ns; ++K) {
+    std::vector<int32_t> &w = width[K];
+    if (w.empty()) w.push_back(0);
+    w[0] = 1;
+    const bool fits = !bad[K] && ok(K) && (int32_t)w.size() <= kSubHeight &&
+                      *std::max_element(w.begin(), w.end()) <= kSubWidth;
+    const int64_t P = S.sparent[K];
+    if (fits) in[K] = (int32_t)w.size();
+    if (P >= 0 && !fits) bad[P] = 1;
+    if (P >= 0 && fits && !bad[P]) {
+      std::vector<int32_t> &v = width[P];
+      if (v.size() < w.size() + 1) v.resize(w.size() + 1, 0);
+      for (size_t i = 0; i < w.size(); ++i) v[i + 1] += w[i];
+    }
+    std::vector<int32_t>().swap(w);
+  }
+  return in;
+}
+
 void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t dense_min_c, int64_t dense_max_bytes,
                 int64_t split_min_k, int sched, const TuneTable *tt, bool adjoint, bool herm, bool lu, HostPlan &H,
                 bool lu_small = true) {
@@ -646,6 +681,8 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   H.lvl_kind.clear();
   H.lvl_tsplit.clear();
   H.tiny.clear();
+  H.lvl_u0.clear();
+  H.lvl_u1.clear();
   H.toff.clear();
   H.tiny_dptr.assign(S.depth + 1, 0);
   H.tiny_dadj.assign(S.depth, 0);
@@ -719,6 +756,15 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
     if (!H.node_grp.empty())  // group 1's nodes before group 2's at every depth: each launch is two ranges
       for (auto &v : bydepth)
         std::stable_sort(v.begin(), v.end(), [&](int64_t a, int64_t b) { return H.node_grp[a] < H.node_grp[b]; });
+    // a depth's single-wavefront nodes: the adjoint's first, and next to each
+    // other the ones outside the bottom subtrees
+    std::vector<int32_t> sub(ns, 0);
+    if (sched == SELINV_SCHED_LEVELS)
+      sub = subtrees(S, [&](int64_t K) {
+        return is_tiny(K) && (scalar_bytes == 8 || H.node_c[K] <= kTinyC) && (H.node_grp.empty() || H.node_grp[K] != 0);
+      });
+    auto tiny_class = [&](int64_t K) { return adj_tiny(K) ? (sub[K] ? 0 : 1) : (sub[K] ? 3 : 2); };
+    std::vector<int32_t> tiny_of(ns, -1);
     H.lvl_depth_first.assign(S.depth + 1, 0);
     for (int64_t d = 0; d < S.depth; ++d) {
       H.lvl_depth_first[d] = (int32_t)H.lvl_ptr.size() - 1;
@@ -783,12 +829,16 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
       const int32_t tiny_base = (int32_t)H.tiny.size();
       H.tiny_dptr[d] = tiny_base;
       // the adjoint's nodes (c <= kTinyC) first, then the forward-only ones
-      for (int pass = 0; pass < 2; ++pass) {
+      int32_t u0 = 0, u1 = 0;
+      for (int pass = 0; pass < 4; ++pass) {
+        if (pass == 1) u0 = (int32_t)H.lvl_items.size();
+        if (pass == 3) u1 = (int32_t)H.lvl_items.size();
         for (int64_t K : bydepth[d]) {
-          if (!is_tiny(K) || adj_tiny(K) != (pass == 0)) continue;
+          if (!is_tiny(K) || tiny_class(K) != pass) continue;
           const int32_t it = phase_begin(H, K, 3);
           const int64_t c = H.node_c[K], rp = S.rowptr[K];
           H.lvl_items.push_back(it);
+          tiny_of[K] = (int32_t)H.tiny.size();
           H.tiny.push_back(TinyRec{(int32_t)K, it, H.node_s[K], (int32_t)c, S.panel_off[K], (int64_t)H.toff.size()});
           // X(row i, row k), i >= k, lives in the panel of row k's supernode;
           // the table is c x c (both triangles), then one padding row of
@@ -804,16 +854,55 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
                   lu && k < i ? v + (uint32_t)(S.panel_elems * scalar_bytes) : v | (herm && k < i ? 1u : 0u);
             }
         }
-        if (pass == 0) {
+        if (pass == 1) {
           H.tiny_dadj[d] = (int32_t)H.tiny.size();
           tsplit = (int32_t)H.lvl_items.size();
         }
       }
       close(tiny_base, LVL_TINY);
+      H.lvl_u0.resize(H.lvl_ptr.size() - 1, 0);
+      H.lvl_u1.resize(H.lvl_ptr.size() - 1, 0);
+      if (H.lvl_kind.size() && H.lvl_kind.back() == LVL_TINY && H.lvl_tiny.back() == tiny_base) {
+        H.lvl_u0.back() = u0;
+        H.lvl_u1.back() = u1;
+      }
       if (d == top_depth && d + 1 < S.depth) H.lvl_top = (int32_t)H.lvl_ptr.size() - 1;
     }
     H.lvl_depth_first[S.depth] = (int32_t)H.lvl_ptr.size() - 1;
     H.tiny_dptr[S.depth] = (int32_t)H.tiny.size();
+    // the groups, those of the first stream before those of the second, tall ones first
+    H.sub_rec.clear();
+    H.sub_step.assign(1, 0);
+    H.sub_grp.clear();
+    H.sub_split = H.sub_width = 0;
+    std::vector<int64_t> roots;
+    std::vector<std::vector<int64_t>> kids(ns);
+    for (int64_t K = 0; K < ns; ++K) {
+      if (!sub[K]) continue;
+      const int64_t P = S.sparent[K];
+      if (P >= 0 && sub[P])
+        kids[P].push_back(K);
+      else
+        roots.push_back(K);
+    }
+    auto second = [&](int64_t K) { return !H.node_grp.empty() && H.node_grp[K] == 2; };
+    std::stable_sort(roots.begin(), roots.end(), [&](int64_t a, int64_t b) {
+      return second(a) != second(b) ? second(b) : sub[a] > sub[b];
+    });
+    for (int64_t R : roots) {
+      H.sub_split += !second(R);
+      const int32_t first = (int32_t)H.sub_step.size() - 1;
+      for (std::vector<int64_t> cur(1, R), next; !cur.empty(); cur.swap(next)) {
+        next.clear();
+        for (int64_t K : cur) {
+          H.sub_rec.push_back(H.tiny[tiny_of[K]]);
+          next.insert(next.end(), kids[K].begin(), kids[K].end());
+        }
+        H.sub_width = std::max(H.sub_width, (int32_t)cur.size());
+        H.sub_step.push_back((int32_t)H.sub_rec.size());
+      }
+      H.sub_grp.push_back(int2{first, (int32_t)H.sub_step.size() - 1 - first});
+    }
     // the group ranges of every launch below the chain (maximal runs of one
     // group; a single-wavefront launch lists its adjoint nodes first, so it
     // can hold two runs of each group)
@@ -1121,6 +1210,9 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   o.tiny = take((int64_t)sizeof(TinyRec) * (int64_t)H.tiny.size());
   o.toff = take(4 * (int64_t)H.toff.size());
   o.g2 = take((int64_t)sizeof(LRec) * (int64_t)H.g2.size());
+  o.sub_rec = take((int64_t)sizeof(TinyRec) * (int64_t)H.sub_rec.size());
+  o.sub_step = take(4 * (int64_t)H.sub_step.size());
+  o.sub_grp = take(8 * (int64_t)H.sub_grp.size());
   o.chunks = take(8 * (int64_t)H.chunks.size());
   o.chunks_narrow = take(8 * (int64_t)H.chunks_narrow.size());
   o.small_nodes = take(4 * (int64_t)H.small_nodes.size());
@@ -1401,6 +1493,11 @@ hipError_t launch_groups(selinv_ctx *h, const DevPlan &pl, const DevPlan *dpl, c
       e = launch_level_range(pl, dpl, aux, h->is_complex(), panels, x, g.x == 2 ? h->tst : st, q, g.z, g.w);
     }
   }
+  if (q1 == aux.nlvl && e == hipSuccess) {  // the bottom subtrees of each group
+    e = launch_level_range(pl, dpl, aux, h->is_complex(), panels, x, st, aux.nlvl, 0, H.sub_split);
+    if (e == hipSuccess)
+      e = launch_level_range(pl, dpl, aux, h->is_complex(), panels, x, h->tst, aux.nlvl, H.sub_split, aux.nsub);
+  }
   return e;
 }
 
@@ -1461,6 +1558,14 @@ LaunchAux make_aux(const selinv_ctx *h, void *work) {
   a.g2_ptr = H.g2_ptr.data();
   a.g2_mid = H.g2_mid.data();
   a.g2_cut = H.g2_cut.data();
+  a.sub_rec = (const TinyRec *)(b + H.off.sub_rec);
+  a.nsub_rec = (int64_t)H.sub_rec.size();
+  a.sub_step = (const int32_t *)(b + H.off.sub_step);
+  a.sub_grp = (const int2 *)(b + H.off.sub_grp);
+  a.nsub = (int32_t)H.sub_grp.size();
+  a.sub_width = H.sub_width;
+  a.lvl_u0 = H.lvl_u0.data();
+  a.lvl_u1 = H.lvl_u1.data();
   a.nlvl = (int32_t)H.lvl_ptr.size() - 1;
   a.blaunch = H.blaunch.data();
   a.nblaunch = (int32_t)H.blaunch.size();
@@ -1503,6 +1608,9 @@ void build_image(selinv_ctx *h) {
   put(img, o.tiny, H.tiny);
   put(img, o.toff, H.toff);
   put(img, o.g2, H.g2);
+  put(img, o.sub_rec, H.sub_rec);
+  put(img, o.sub_step, H.sub_step);
+  put(img, o.sub_grp, H.sub_grp);
   put(img, o.chunks, H.chunks);
   put(img, o.chunks_narrow, H.chunks_narrow);
   put(img, o.small_nodes, H.small_nodes);
@@ -1659,7 +1767,8 @@ selinv_status selinv_analyze(int64_t n, const int64_t *colptr, const int64_t *ro
     // plan does without these nodes (30^3, four shifts: 6.6 ms for 4.1), which
     // selinv_normalize_run_noalloc would otherwise refuse outright
     if (h->H.lu && h->H.off.fwd_end > kNoAllocBytes &&
-        h->H.off.fwd_end - 4 * (int64_t)h->H.toff.size() - (int64_t)sizeof(TinyRec) * (int64_t)h->H.tiny.size() <=
+        h->H.off.fwd_end - 4 * (int64_t)h->H.toff.size() -
+                (int64_t)sizeof(TinyRec) * (int64_t)(h->H.tiny.size() + h->H.sub_rec.size()) <=
             kNoAllocBytes) {
       HostPlan alt;
       build_plan(h->S, o.batch, h->sbytes(), min_c, max_b, split_k, o.sched, nullptr, false, false, true, alt, false);

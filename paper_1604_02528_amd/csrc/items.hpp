@@ -8,6 +8,7 @@
 
 #include <cstdint>
 
+#include "blk16.hpp"
 #include "plan.hpp"
 #include "scalar.hpp"
 #include "tile.hpp"
@@ -1041,36 +1042,70 @@ __device__ void do_stile(const Ctx<T> &cx, const NodeInfo &nd, double *smem, int
   lds_barrier();
 }
 
-// A whole small node (c <= CM <= kTinyCF, s <= kTinyS) of one matrix in one
+// A whole small node (c <= CM <= kTinyCF, s <= SM <= kTinyS) of one matrix in one
 // wavefront, for the level schedule.  Three dependent memory rounds: the
 // record, then the byte offsets of X_{C,C} in the panel array (host table:
 // c x c row-major, then padding), Lhat and Dt^{-1}, then the X_{C,C} values.
 // Lane (i, grp) holds X_{C,C}(i, k) for k = grp + G u; the partial sums of
 // X_{C,C} Lhat over the G lane groups are combined with a fixed butterfly, so
-// the result does not depend on timing.  LDS blocks are c x s with leading
-// dimension tiny_ldc<T>().  HERM: a Hermitian plan (conjugate transposes).
+// the result does not depend on timing.  LDS blocks are CM x SM, a row's SM
+// entries together and zero past c and s, so that every product reads without
+// a branch and many reads are in flight (a branch on j < s around each read
+// waited for it alone: a launch of complex nodes with 32 < c <= 64, 32 shifts of
+// 30^3, took 188 us, now 77).  HERM: a Hermitian plan (conjugate
+// transposes).
 //   Y = -X_{C,C} Lhat (stored into X_{C,K});  T = Dt^{-1} - Lhat^T Y;
 //   X_{K,K} = (T + T^T) / 2                      (Alg. 1, Eqs. (2.9)-(2.10))
-template <typename T, int CM, bool HERM>
-__device__ __forceinline__ void do_tiny(const TinyRec &r, const uint32_t *toff, const T *L, T *X, T *ls, T *ys) {
+
+// Lhat (or Uhat^T) from its lanes' registers (entry e = lane + 64 q: k = e % CM, j = e / CM) into LDS.
+template <int CM, int SM> constexpr int tiny_ql() { return CM * SM >= 64 ? CM * SM / 64 : 1; }
+template <typename T, int CM, int SM>
+__device__ __forceinline__ void tiny_load(const TinyRec &r, int lane, const T *L, T (&lv)[tiny_ql<CM, SM>()]) {
+#pragma unroll
+  for (int q = 0; q < tiny_ql<CM, SM>(); ++q) {
+    const int e = lane + 64 * q, k = e % CM, j = e / CM;
+    lv[q] = gload(L + r.off + ((j * (r.s + r.c) + r.s + k) & opaque_mask(k < r.c && j < r.s)));
+  }
+}
+template <typename T, int CM, int SM>
+__device__ __forceinline__ void tiny_put(const TinyRec &r, int lane, const T (&lv)[tiny_ql<CM, SM>()], T *ls) {
+#pragma unroll
+  for (int q = 0; q < tiny_ql<CM, SM>(); ++q) {
+    const int e = lane + 64 * q, k = e % CM, j = e / CM;
+    if (CM * SM >= 64 || e < CM * SM) ls[k * SM + j] = masked(lv[q], opaque_mask(k < r.c && j < r.s));
+  }
+}
+
+// X_KK = sym(Dt^{-1} + Lhat^T ys), entry (x, y) on lane x + 8 y.
+template <typename T, int SM, bool HERM>
+__device__ __forceinline__ void tiny_diag(const TinyRec &r, int x, int y, T dxy, T dyx, const T *ls, const T *ys, T *X) {
   constexpr double cs = HERM ? -1.0 : 1.0;
-  constexpr int G = 64 / CM, U = CM / G, LDC = tiny_ldc<T>();
-  const int lane = threadIdx.x, i = lane % CM, grp = lane / CM;
+  if (x < r.s && y < r.s) {
+    T rxy = zero_of<T>(), ryx = zero_of<T>();
+    for (int q0 = 0; q0 < r.c; q0 += 8)
+#pragma unroll
+      for (int q = q0; q < q0 + 8; ++q) {
+        rxy += cj(ls[q * SM + x], cs) * ys[q * SM + y];
+        ryx += cj(ls[q * SM + y], cs) * ys[q * SM + x];
+      }
+    X[r.off + y * (r.s + r.c) + x] = SOps<T>::scale(0.5, (dxy + rxy) + cj(dyx + ryx, cs));
+  }
+}
+
+template <typename T, int CM, int SM, bool HERM>
+__device__ __forceinline__ void do_tiny(const TinyRec &r, int lane, const uint32_t *toff, const T *L, T *X, T *ls, T *ys) {
+  constexpr int G = 64 / CM, U = CM / G;
+  const int i = lane % CM, grp = lane / CM;
   const int s = r.s, c = r.c;
   const int64_t ld = s + c;
   const uint32_t *tb = toff + r.tbl;
-  // round 2: the offsets of this lane's X_{C,C}(i, k); Lhat as ls[j * LDC + k]; Dt^{-1}(x, y), (y, x)
+  // round 2: the offsets of this lane's X_{C,C}(i, k); Lhat; Dt^{-1}(x, y), (y, x)
   const uint32_t rowb = 4u * ((uint32_t)(i * c + grp) & opaque_mask32(i < c));
   uint32_t o[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) o[u] = ld_off(tb, rowb + 4u * (G * u));
-  constexpr int QL = CM * kTinyS / 64;
-  T lv[QL];
-#pragma unroll
-  for (int q = 0; q < QL; ++q) {
-    const int e = lane + 64 * q, k = e % CM, j = e / CM;
-    lv[q] = gload(L + r.off + ((j * ld + s + k) & opaque_mask(k < c && j < s)));
-  }
+  T lv[tiny_ql<CM, SM>()];
+  tiny_load<T, CM, SM>(r, lane, L, lv);
   const int x = lane % kTinyS, y = lane / kTinyS;
   const int64_t dm = opaque_mask(x < s && y < s);
   const T dxy = gload(L + r.off + ((y * ld + x) & dm)), dyx = gload(L + r.off + ((x * ld + y) & dm));
@@ -1087,79 +1122,63 @@ __device__ __forceinline__ void do_tiny(const TinyRec &r, const uint32_t *toff, 
       xv[u] = ld_off(X, o[u]);
     }
   }
+  tiny_put<T, CM, SM>(r, lane, lv, ls);
+  wave_lds_fence();
+  T acc[SM];
 #pragma unroll
-  for (int q = 0; q < QL; ++q) {
-    const int e = lane + 64 * q, k = e % CM, j = e / CM;
-    ls[j * LDC + k] = masked(lv[q], opaque_mask(k < c && j < s));
-  }
-  __syncthreads();
-  T acc[kTinyS];
-#pragma unroll
-  for (int j = 0; j < kTinyS; ++j) acc[j] = zero_of<T>();
+  for (int j = 0; j < SM; ++j) acc[j] = zero_of<T>();
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int k = grp + G * u;
     T g = masked(xv[u], opaque_mask(i < c && k < c));
     if constexpr (HERM) g = cj(g, ((cbits >> u) & 1u) ? -1.0 : 1.0);
 #pragma unroll
-    for (int j = 0; j < kTinyS; ++j)
-      if (j < s) acc[j] += g * ls[j * LDC + k];
+    for (int j = 0; j < SM; ++j) acc[j] += g * ls[k * SM + j];
   }
 #pragma unroll
   for (int m = CM; m < 64; m <<= 1)
 #pragma unroll
-    for (int j = 0; j < kTinyS; ++j)
-      if (j < s) acc[j] += shfl_xor_t(acc[j], m);
-  if (grp == 0 && i < c) {
+    for (int j = 0; j < SM; ++j) acc[j] += shfl_xor_t(acc[j], m);
+  if (grp == 0) {
 #pragma unroll
-    for (int j = 0; j < kTinyS; ++j)
-      if (j < s) {
-        X[r.off + j * ld + s + i] = SOps<T>::scale(-1.0, acc[j]);
-        ys[j * LDC + i] = acc[j];
-      }
-  }
-  __syncthreads();
-  // T = Dt^{-1} + Lhat^T (X_{C,C} Lhat); X_KK = (T + T^T) / 2 (^H and
-  // conjugated Lhat in a Hermitian plan)
-  if (x < s && y < s) {
-    T rxy = zero_of<T>(), ryx = zero_of<T>();
-    for (int q = 0; q < c; ++q) {
-      rxy += cj(ls[x * LDC + q], cs) * ys[y * LDC + q];
-      ryx += cj(ls[y * LDC + q], cs) * ys[x * LDC + q];
+    for (int j = 0; j < SM; ++j) {
+      if (j < s && i < c) X[r.off + j * ld + s + i] = SOps<T>::scale(-1.0, acc[j]);
+      ys[i * SM + j] = acc[j];
     }
-    X[r.off + y * ld + x] = SOps<T>::scale(0.5, (dxy + rxy) + cj(dyx + ryx, cs));
   }
+  wave_lds_fence();
+  tiny_diag<T, SM, HERM>(r, x, y, dxy, dyx, ls, ys, X);
 }
 
-// The same for 32 < c <= kTinyCF (FP64): lane i holds row i of X_{C,C}, and
-// the contraction runs in two halves of 32 columns so that one half's
-// offsets and one half's values are in registers at a time; Y(i, j) is
-// accumulated in LDS (each lane owns its row), one column j at a time.  Four
-// dependent rounds: the record; Lhat, Dt^{-1} and the first half's offsets;
-// the first half's values with the second half's offsets; the second half's
-// values.  HERM: a Hermitian plan (bit 0 of an offset marks an entry read
-// conjugated; the diagonal block takes Lhat^H and the conjugate transpose).
-template <typename T, bool HERM = false>
-__device__ __forceinline__ void do_tiny64(const TinyRec &r, const uint32_t *toff, const T *L, T *X, T *ls, T *ys) {
-  constexpr int H = kTinyCF / 2, LDC = kTinyCF;
-  constexpr double cs = HERM ? -1.0 : 1.0;
-  const int i = threadIdx.x;
+// The same for 32 < c <= kTinyCF: lane i holds row i of X_{C,C}, and the
+// contraction runs in two halves of 32 columns so that one half's offsets and
+// one half's values are in registers at a time.  Four dependent rounds: the
+// record; Lhat, Dt^{-1} and the first half's offsets; the first half's values
+// with the second half's offsets; the second half's values.  HERM: a Hermitian
+// plan (bit 0 of an offset marks an entry read conjugated; the diagonal block
+// takes Lhat^H and the conjugate transpose).
+__device__ __forceinline__ void hold(double &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void hold(cplx &x) {
+  hold(x.re);
+  hold(x.im);
+}
+template <typename T, int SM, bool HERM = false>
+__device__ __forceinline__ void do_tiny64(const TinyRec &r, int lane, const uint32_t *toff, const T *L, T *X, T *ls, T *ys) {
+  constexpr int H = kTinyCF / 2, CM = kTinyCF;
+  const int i = lane;
   const int s = r.s, c = r.c;
   const int64_t ld = s + c;
   const uint32_t *tb = toff + r.tbl;
-  constexpr int QL = kTinyCF * kTinyS / 64;
-  T lv[QL];
-#pragma unroll
-  for (int q = 0; q < QL; ++q) {
-    const int e = i + 64 * q, k = e % kTinyCF, j = e / kTinyCF;
-    lv[q] = gload(L + r.off + ((j * ld + s + k) & opaque_mask(k < c && j < s)));
-  }
+  T lv[tiny_ql<CM, SM>()];
+  tiny_load<T, CM, SM>(r, lane, L, lv);
   const int x = i % kTinyS, y = i / kTinyS;
   const int64_t dm = opaque_mask(x < s && y < s);
   const T dxy = gload(L + r.off + ((y * ld + x) & dm)), dyx = gload(L + r.off + ((x * ld + y) & dm));
   const uint32_t rowb = 4u * ((uint32_t)(i * c) & opaque_mask32(i < c));
   uint32_t o[H];
-  T xv[H];
+  T xv[H], acc[SM];
+#pragma unroll
+  for (int j = 0; j < SM; ++j) acc[j] = zero_of<T>();
 #pragma unroll
   for (int u = 0; u < H; ++u) o[u] = ld_off(tb, rowb + 4u * u);
 #pragma unroll
@@ -1178,54 +1197,49 @@ __device__ __forceinline__ void do_tiny64(const TinyRec &r, const uint32_t *toff
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < H; ++u) o[u] = ld_off(tb, rowb + 4u * (H + u));
-#pragma unroll
-      for (int q = 0; q < QL; ++q) {
-        const int e = i + 64 * q, k = e % kTinyCF, j = e / kTinyCF;
-        ls[j * LDC + k] = masked(lv[q], opaque_mask(k < c && j < s));
-      }
-      __syncthreads();
+      tiny_put<T, CM, SM>(r, lane, lv, ls);
+      wave_lds_fence();
     }
+    constexpr int UB = 16 / Planes<T>::P / (SM / 4);  // rows of Lhat in flight
 #pragma unroll
-    for (int u = 0; u < H; ++u) {
-      xv[u] = masked(xv[u], opaque_mask(i < c && H * h + u < c));
-      if constexpr (HERM) xv[u] = cj(xv[u], ((cbits >> u) & 1u) ? -1.0 : 1.0);
-    }
-#pragma unroll 1
-    for (int j = 0; j < s; ++j) {
-      T a = h ? ys[j * LDC + i] : zero_of<T>();
+    for (int u0 = 0; u0 < H; u0 += UB) {
+      // these reads stay behind the previous products (all of them in front
+      // of all products took 2000 spilled registers)
+      int at = (H * h + u0) * SM;
+      asm volatile("" : "+s"(at));
 #pragma unroll
-      for (int u = 0; u < H; ++u) {
-        a += xv[u] * ls[j * LDC + H * h + u];
-        if (u % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // bounds the Lhat reads in flight
+      for (int u = u0; u < u0 + UB; ++u) {
+        T g = masked(xv[u], opaque_mask(i < c && H * h + u < c));
+        if constexpr (HERM) g = cj(g, ((cbits >> u) & 1u) ? -1.0 : 1.0);
+#pragma unroll
+        for (int j = 0; j < SM; ++j) acc[j] += g * ls[at + (u - u0) * SM + j];
       }
-      ys[j * LDC + i] = a;
+#pragma unroll
+      for (int j = 0; j < SM; ++j) hold(acc[j]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
-  if (i < c)
-    for (int j = 0; j < s; ++j) X[r.off + j * ld + s + i] = SOps<T>::scale(-1.0, ys[j * LDC + i]);
-  __syncthreads();
-  if (x < s && y < s) {
-    T rxy = zero_of<T>(), ryx = zero_of<T>();
-    for (int q = 0; q < c; ++q) {
-      rxy += cj(ls[x * LDC + q], cs) * ys[y * LDC + q];
-      ryx += cj(ls[y * LDC + q], cs) * ys[x * LDC + q];
-    }
-    X[r.off + y * ld + x] = SOps<T>::scale(0.5, (dxy + rxy) + cj(dyx + ryx, cs));
+#pragma unroll
+  for (int j = 0; j < SM; ++j) {
+    if (j < s && i < c) X[r.off + j * ld + s + i] = SOps<T>::scale(-1.0, acc[j]);
+    ys[i * SM + j] = acc[j];
   }
+  wave_lds_fence();
+  tiny_diag<T, SM, HERM>(r, x, y, dxy, dyx, ls, ys, X);
 }
 
-// A whole small node of an LU plan (c <= CM, s <= kTinyS) in one wavefront, as
+// A whole small node of an LU plan (c <= CM, s <= SM) in one wavefront, as
 // do_tiny for both panel sets: lane (i, grp) holds X_{C,C}(i, k) and X_{C,C}(k, i)
 // for k = grp + G u (the table gives the first; the second is the same
 // position of the other set, half8 bytes away), 16 of each at a time, and
 // accumulates X_{C,C} Lhat and (X_{C,C})^T Uhat^T.
 //   X_{C,K} = -X_{C,C} Lhat, X_{K,C}^T = -(X_{C,C})^T Uhat^T,
 //   X_KK = Dt^{-1} - Uhat X_{C,K}, stored into the first set and transposed into the second
-template <int CM>
-__device__ __forceinline__ void do_tiny_lu(const TinyRec &r, const uint32_t *toff, int64_t half, const double *L, double *X,
-                                           double *ls, double *us, double *ys) {
-  constexpr int G = 64 / CM, U = CM / G, UC = U < 16 ? U : 16, LDC = kTinyCF, QL = CM * kTinyS / 64;
-  const int lane = threadIdx.x, i = lane % CM, grp = lane / CM;
+template <int CM, int SM>
+__device__ __forceinline__ void do_tiny_lu(const TinyRec &r, int lane, const uint32_t *toff, int64_t half, const double *L,
+                                           double *X, double *ls, double *us, double *ys) {
+  constexpr int G = 64 / CM, U = CM / G, UC = U < 16 ? U : 16;
+  const int i = lane % CM, grp = lane / CM;
   const int s = r.s, c = r.c;
   const int64_t ld = s + c;
   const uint32_t *tb = toff + r.tbl;
@@ -1233,27 +1247,17 @@ __device__ __forceinline__ void do_tiny_lu(const TinyRec &r, const uint32_t *tof
   uint32_t o[UC];
 #pragma unroll
   for (int u = 0; u < UC; ++u) o[u] = ld_off(tb, rowb + 4u * (G * u));
-  double lv[QL], uv[QL];
-#pragma unroll
-  for (int q = 0; q < QL; ++q) {
-    const int e = lane + 64 * q, k = e % CM, j = e / CM;
-    const int64_t m = opaque_mask(k < c && j < s);
-    lv[q] = gload(L + r.off + ((j * ld + s + k) & m));
-    uv[q] = gload(L + half + r.off + ((j * ld + s + k) & m));
-  }
+  double lv[tiny_ql<CM, SM>()], uv[tiny_ql<CM, SM>()];
+  tiny_load<double, CM, SM>(r, lane, L, lv);
+  tiny_load<double, CM, SM>(r, lane, L + half, uv);
   const int x = lane % kTinyS, y = lane / kTinyS;
   const double dxy = gload(L + r.off + ((y * ld + x) & opaque_mask(x < s && y < s)));
+  tiny_put<double, CM, SM>(r, lane, lv, ls);
+  tiny_put<double, CM, SM>(r, lane, uv, us);
+  wave_lds_fence();
+  double al[SM], au[SM];
 #pragma unroll
-  for (int q = 0; q < QL; ++q) {
-    const int e = lane + 64 * q, k = e % CM, j = e / CM;
-    const int64_t m = opaque_mask(k < c && j < s);
-    ls[j * LDC + k] = masked(lv[q], m);
-    us[j * LDC + k] = masked(uv[q], m);
-  }
-  __syncthreads();
-  double al[kTinyS], au[kTinyS];
-#pragma unroll
-  for (int j = 0; j < kTinyS; ++j) al[j] = au[j] = 0.0;
+  for (int j = 0; j < SM; ++j) al[j] = au[j] = 0.0;
 #pragma unroll
   for (int u0 = 0; u0 < U; u0 += UC) {
     if (G * u0 >= c) break;
@@ -1275,34 +1279,36 @@ __device__ __forceinline__ void do_tiny_lu(const TinyRec &r, const uint32_t *tof
       const int64_t m = opaque_mask(i < c && k < c);
       const double a = masked(xl[u], m), b = masked(xu[u], m);
 #pragma unroll
-      for (int j = 0; j < kTinyS; ++j)
-        if (j < s) {
-          al[j] += a * ls[j * LDC + k];
-          au[j] += b * us[j * LDC + k];
-        }
+      for (int j = 0; j < SM; ++j) {
+        al[j] += a * ls[k * SM + j];
+        au[j] += b * us[k * SM + j];
+      }
+      if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // bounds the reads in flight
     }
   }
 #pragma unroll
   for (int m = CM; m < 64; m <<= 1)
 #pragma unroll
-    for (int j = 0; j < kTinyS; ++j)
-      if (j < s) {
-        al[j] += shfl_xor_t(al[j], m);
-        au[j] += shfl_xor_t(au[j], m);
-      }
-  if (grp == 0 && i < c) {
+    for (int j = 0; j < SM; ++j) {
+      al[j] += shfl_xor_t(al[j], m);
+      au[j] += shfl_xor_t(au[j], m);
+    }
+  if (grp == 0) {
 #pragma unroll
-    for (int j = 0; j < kTinyS; ++j)
-      if (j < s) {
+    for (int j = 0; j < SM; ++j) {
+      if (j < s && i < c) {
         gstore(X + r.off + j * ld + s + i, -al[j]);
         gstore(X + half + r.off + j * ld + s + i, -au[j]);
-        ys[j * LDC + i] = al[j];
       }
+      ys[i * SM + j] = al[j];
+    }
   }
-  __syncthreads();
+  wave_lds_fence();
   if (x < s && y < s) {
     double t = dxy;
-    for (int q = 0; q < c; ++q) t += us[x * LDC + q] * ys[y * LDC + q];
+    for (int q0 = 0; q0 < c; q0 += 8)
+#pragma unroll
+      for (int q = q0; q < q0 + 8; ++q) t += us[q * SM + x] * ys[q * SM + y];
     gstore(X + r.off + y * ld + x, t);
     gstore(X + half + r.off + x * ld + y, t);
   }

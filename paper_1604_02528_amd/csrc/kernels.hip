@@ -381,28 +381,60 @@ __global__ void __launch_bounds__(NT, 2) k_ydense128(const DevPlan *__restrict__
   }
 }
 
+template <typename T, int SM, bool HERM>
+__device__ __forceinline__ void tiny_rows(const TinyRec &r, int lane, const uint32_t *toff, const T *L, T *X, T *ls, T *ys) {
+  if (r.c <= 8)
+    do_tiny<T, 8, SM, HERM>(r, lane, toff, L, X, ls, ys);
+  else if (r.c <= 16)
+    do_tiny<T, 16, SM, HERM>(r, lane, toff, L, X, ls, ys);
+  else if constexpr (sizeof(T) == 16)  // complex launches send c > kTinyC to k_tiny64
+    do_tiny<T, 32, SM, HERM>(r, lane, toff, L, X, ls, ys);
+  else if (r.c <= 32)
+    do_tiny<T, 32, SM, HERM>(r, lane, toff, L, X, ls, ys);
+  else
+    do_tiny64<T, SM>(r, lane, toff, L, X, ls, ys);
+}
+template <typename T, bool HERM>
+__device__ __forceinline__ void tiny_node(const TinyRec &r, int lane, const uint32_t *toff, const T *L, T *X, T *ls, T *ys) {
+  if (r.s <= kTinyS / 2)
+    tiny_rows<T, kTinyS / 2, HERM>(r, lane, toff, L, X, ls, ys);
+  else
+    tiny_rows<T, kTinyS, HERM>(r, lane, toff, L, X, ls, ys);
+}
+
+template <int SM>
+__device__ __forceinline__ void tiny_lu_rows(const TinyRec &r, int lane, const uint32_t *toff, int64_t half, const double *L,
+                                             double *X, double *ls, double *us, double *ys) {
+  if (r.c <= 8)
+    do_tiny_lu<8, SM>(r, lane, toff, half, L, X, ls, us, ys);
+  else if (r.c <= 16)
+    do_tiny_lu<16, SM>(r, lane, toff, half, L, X, ls, us, ys);
+  else if (r.c <= 32)
+    do_tiny_lu<32, SM>(r, lane, toff, half, L, X, ls, us, ys);
+  else
+    do_tiny_lu<64, SM>(r, lane, toff, half, L, X, ls, us, ys);
+}
+__device__ __forceinline__ void tiny_lu_node(const TinyRec &r, int lane, const uint32_t *toff, int64_t half, const double *L,
+                                             double *X, double *ls, double *us, double *ys) {
+  if (r.s <= kTinyS / 2)
+    tiny_lu_rows<kTinyS / 2>(r, lane, toff, half, L, X, ls, us, ys);
+  else
+    tiny_lu_rows<kTinyS>(r, lane, toff, half, L, X, ls, us, ys);
+}
+
 // Small nodes of one level, one wavefront each (see do_tiny).
 template <typename T, bool HERM>
 __global__ void __launch_bounds__(64) k_tiny(const DevPlan *__restrict__ plp, const T *Lp, T *Xp,
                                              const TinyRec *__restrict__ recs, int32_t count, int32_t list_pos) {
   const DevPlan &pl = *plp;
-  __shared__ T ls[kTinyS * tiny_ldc<T>()], ys[kTinyS * tiny_ldc<T>()];
+  __shared__ __align__(16) T ls[kTinyS * tiny_ldc<T>()], ys[kTinyS * tiny_ldc<T>()];
   const int64_t g = blockIdx.x;
   const int64_t l = g / count;
   const TinyRec r = recs[g - l * count];
   const int64_t t_start = pl.trace ? wall_clock64() : 0;
   const T *L = Lp + l * pl.panel_elems;
   T *X = Xp + l * pl.panel_elems;
-  if (r.c <= 8)
-    do_tiny<T, 8, HERM>(r, pl.toff, L, X, ls, ys);
-  else if (r.c <= 16)
-    do_tiny<T, 16, HERM>(r, pl.toff, L, X, ls, ys);
-  else if constexpr (sizeof(T) == 16)  // complex launches send c > kTinyC to k_tiny64
-    do_tiny<T, 32, HERM>(r, pl.toff, L, X, ls, ys);
-  else if (r.c <= 32)
-    do_tiny<T, 32, HERM>(r, pl.toff, L, X, ls, ys);
-  else
-    do_tiny64<T>(r, pl.toff, L, X, ls, ys);
+  tiny_node<T, HERM>(r, threadIdx.x, pl.toff, L, X, ls, ys);
   if (pl.trace) {
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -422,21 +454,14 @@ __global__ void __launch_bounds__(64) k_tiny(const DevPlan *__restrict__ plp, co
 __global__ void __launch_bounds__(64) k_tiny_lu(const DevPlan *__restrict__ plp, const double *Lp, double *Xp,
                                                 const TinyRec *__restrict__ recs, int32_t count, int32_t list_pos) {
   const DevPlan &pl = *plp;
-  __shared__ double ls[kTinyS * kTinyCF], us[kTinyS * kTinyCF], ys[kTinyS * kTinyCF];
+  __shared__ __align__(16) double ls[kTinyS * kTinyCF], us[kTinyS * kTinyCF], ys[kTinyS * kTinyCF];
   const int64_t g = blockIdx.x;
   const int64_t l = g / count;
   const TinyRec r = recs[g - l * count];
   const int64_t t_start = pl.trace ? wall_clock64() : 0;
   const double *L = Lp + l * pl.panel_elems;
   double *X = Xp + l * pl.panel_elems;
-  if (r.c <= 8)
-    do_tiny_lu<8>(r, pl.toff, pl.half, L, X, ls, us, ys);
-  else if (r.c <= 16)
-    do_tiny_lu<16>(r, pl.toff, pl.half, L, X, ls, us, ys);
-  else if (r.c <= 32)
-    do_tiny_lu<32>(r, pl.toff, pl.half, L, X, ls, us, ys);
-  else
-    do_tiny_lu<64>(r, pl.toff, pl.half, L, X, ls, us, ys);
+  tiny_lu_node(r, threadIdx.x, pl.toff, pl.half, L, X, ls, us, ys);
   if (pl.trace) {
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -447,6 +472,60 @@ __global__ void __launch_bounds__(64) k_tiny_lu(const DevPlan *__restrict__ plp,
       tr[3] = t_start;
       tr[4] = wall_clock64();
     }
+  }
+}
+
+// Bottom subtrees of small nodes, one workgroup each: depth by depth, a
+// wavefront per node, a workgroup barrier between depths (every X_{C,C} entry
+// comes from above the subtree, finished before this launch, or from this
+// workgroup).  A launch per depth costs 6 us of latency-bound work and 2 to 4
+// between launches.  A node's record, offset table and Lhat do not depend on
+// X: the lines of a wavefront's next node are touched while it works on the
+// current one, so that only its X_{C,C} loads are left to wait for.  With the
+// branch-free do_tiny: solve of a 31 x 31 grid 249 -> 216 us, normalization
+// and traversal of 40^3 3.06 -> 2.97 ms, LU form 30^3, four shifts, 3.94 -> 3.81 ms.
+enum SubKind { SUB_SYM = 0, SUB_HERM = 1, SUB_LU = 2 };
+template <typename T, int KIND>
+__global__ void __launch_bounds__(64 * kSubWaves) k_sub(const DevPlan *__restrict__ plp, const T *Lp, T *Xp,
+                                                        const TinyRec *__restrict__ recs, const int2 *__restrict__ grp,
+                                                        const int32_t *__restrict__ step, int32_t count) {
+  extern __shared__ __align__(16) unsigned char sub_smem[];
+  constexpr int BLK = kTinyS * tiny_ldc<T>();
+  const DevPlan &pl = *plp;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), nw = (int)(blockDim.x >> 6);
+  T *ls = reinterpret_cast<T *>(sub_smem) + (KIND == SUB_LU ? 3 : 2) * BLK * wv;
+  const int64_t g = blockIdx.x;
+  const int64_t l = g / count;
+  const int2 gr = grp[g - l * count];
+  const T *L = Lp + l * pl.panel_elems;
+  T *X = Xp + l * pl.panel_elems;
+  const int end = gr.x + gr.y;
+  int b = step[gr.x], e = step[gr.x + 1];
+  TinyRec r = recs[min(b + wv, e - 1)];
+  for (int q = gr.x; q < end; ++q) {
+    // the next step's first node of this wavefront
+    const int qn = min(q + 1, end - 1), bn = step[qn], en = step[qn + 1];
+    const TinyRec rn = recs[min(bn + wv, en - 1)];
+    // one load a 128-byte line: its table, its panel
+    const uint32_t at = 128u * (threadIdx.x & 63);
+    const uint32_t tb = 4u * (uint32_t)(rn.c * rn.c), pb = (uint32_t)((rn.s + rn.c) * rn.s) * (uint32_t)sizeof(T);
+    const uint32_t touch_t = ld_off(pl.toff + rn.tbl, min(at, tb));
+    const double touch_p = ld_off(reinterpret_cast<const double *>(L + rn.off), min(at, pb - 8u));
+    for (int i = b + wv; i < e; i += nw) {
+      if (i > b + wv) r = recs[i];
+      int lane = threadIdx.x & 63;
+      asm volatile("" : "+v"(lane));  // no lane's offsets held over the loop, for every variant at once
+      if constexpr (KIND == SUB_LU)
+        tiny_lu_node(r, lane, pl.toff, pl.half, L, X, ls, ls + BLK, ls + 2 * BLK);
+      else
+        tiny_node<T, KIND == SUB_HERM>(r, lane, pl.toff, L, X, ls, ls + BLK);
+      wave_lds_fence();
+    }
+    asm volatile("" ::"v"(touch_t), "v"(touch_p));
+    __syncthreads();
+    r = rn;
+    b = bn;
+    e = en;
   }
 }
 
@@ -462,7 +541,10 @@ __global__ void __launch_bounds__(64) k_tiny64(const DevPlan *__restrict__ plp, 
   const int64_t l = g / count;
   const TinyRec r = recs[g - l * count];
   const int64_t t_start = pl.trace ? wall_clock64() : 0;
-  do_tiny64<T, HERM>(r, pl.toff, Lp + l * pl.panel_elems, Xp + l * pl.panel_elems, ls, ys);
+  if (r.s <= kTinyS / 2)
+    do_tiny64<T, kTinyS / 2, HERM>(r, threadIdx.x, pl.toff, Lp + l * pl.panel_elems, Xp + l * pl.panel_elems, ls, ys);
+  else
+    do_tiny64<T, kTinyS, HERM>(r, threadIdx.x, pl.toff, Lp + l * pl.panel_elems, Xp + l * pl.panel_elems, ls, ys);
   if (pl.trace) {
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1118,6 +1200,39 @@ hipError_t launch_normalize(const DevPlan &pl, const DevPlan *dpl, const LaunchA
                : normalize_impl<double>(pl, dpl, aux, src, panels, dt, st, part, steps);
 }
 
+// Whether this launch takes the bottom subtrees (see k_sub): a traced run
+// lists every node at its depth; and where the nodes of a depth fill the GPU
+// for longer than a launch takes, a launch per depth is as fast or faster (its
+// wavefronts never wait for others of their subtree; the wavefront slots of the
+// GPU eight times over; 18 k and 21 k nodes gain as above, 59 k lose 1.4% on
+// 16 Hermitian 30^3 matrices, 118 k 1.9% on 32 complex shifts).
+static bool use_sub(const DevPlan &pl, const LaunchAux &aux) {
+  return aux.nsub > 0 && !pl.trace && aux.nsub_rec * pl.batch <= kSubNodes;
+}
+
+// Groups [b, e) of the bottom subtrees.
+template <typename T>
+static void launch_sub(const DevPlan &pl, const DevPlan *dpl, const LaunchAux &aux, const T *Lp, T *Xp, hipStream_t st,
+                       int32_t b, int32_t e) {
+  if (e <= b || !use_sub(pl, aux)) return;
+  const bool lu = pl.half > 0;
+  // (three LDS blocks per wavefront of an LU plan: 64 KB hold five)
+  const int nw = std::min(aux.sub_width, lu ? 4 : kSubWaves);
+  const dim3 grid((unsigned)((e - b) * pl.batch)), block(64 * nw);
+  const size_t smem = sizeof(T) * (lu ? 3 : 2) * kTinyS * tiny_ldc<T>() * nw;
+  if constexpr (sizeof(T) == 8) {
+    if (lu)
+      hipLaunchKernelGGL((k_sub<T, SUB_LU>), grid, block, smem, st, dpl, Lp, Xp, aux.sub_rec, aux.sub_grp + b, aux.sub_step,
+                         e - b);
+    else
+      hipLaunchKernelGGL((k_sub<T, SUB_SYM>), grid, block, smem, st, dpl, Lp, Xp, aux.sub_rec, aux.sub_grp + b, aux.sub_step,
+                         e - b);
+  } else {
+    hipLaunchKernelGGL((pl.csign < 0 ? k_sub<T, SUB_HERM> : k_sub<T, SUB_SYM>), grid, block, smem, st, dpl, Lp, Xp, aux.sub_rec,
+                       aux.sub_grp + b, aux.sub_step, e - b);
+  }
+}
+
 // Positions [b, e) of level launch q (a sub-range of [lvl_ptr[q],
 // lvl_ptr[q + 1]): the records of a single-wavefront, push or 128-tile launch
 // are laid out in the launch's order, so a sub-range starts b - lvl_ptr[q]
@@ -1125,6 +1240,11 @@ hipError_t launch_normalize(const DevPlan &pl, const DevPlan *dpl, const LaunchA
 template <typename T>
 static void launch_level(const DevPlan &pl, const DevPlan *dpl, const LaunchAux &aux, const T *Lp, T *Xp, T *Pp,
                          hipStream_t st, int q, int32_t b, int32_t e) {
+  if (q == aux.nlvl) return launch_sub<T>(pl, dpl, aux, Lp, Xp, st, b, e);
+  if (aux.lvl_kind[q] == LVL_TINY && use_sub(pl, aux)) {
+    b = std::max(b, aux.lvl_u0[q]);
+    e = std::min(e, aux.lvl_u1[q]);
+  }
   if (e <= b) return;
   if (aux.g2_ptr[q + 1] > aux.g2_ptr[q]) {  // GEMM-2 of the nodes whose diagonal blocks this launch runs
     const int32_t g0 = b < aux.g2_cut[q] ? aux.g2_ptr[q] : aux.g2_mid[q];
@@ -1193,6 +1313,7 @@ static hipError_t run_impl(const DevPlan &pl, const DevPlan *dpl, const LaunchAu
   }
   if (sched == 1 || sched == 2) {
     for (int q = q0; q < q1; ++q) launch_level<T>(pl, dpl, aux, Lp, Xp, Pp, st, q, aux.lvl_ptr[q], aux.lvl_ptr[q + 1]);
+    if (q1 == aux.nlvl) launch_sub<T>(pl, dpl, aux, Lp, Xp, st, 0, aux.nsub);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_sched_init, dim3(256), dim3(256), 0, st, dpl);
@@ -1200,7 +1321,8 @@ static hipError_t run_impl(const DevPlan &pl, const DevPlan *dpl, const LaunchAu
   return hipGetLastError();
 }
 
-// Positions [b, e) of level launch q alone, on st (level schedule).
+// Positions [b, e) of level launch q alone, on st (level schedule); q = nlvl:
+// groups [b, e) of the bottom subtrees.
 hipError_t launch_level_range(const DevPlan &pl, const DevPlan *dpl, const LaunchAux &aux, bool cplx_, const void *panels,
                               void *x, hipStream_t st, int q, int32_t b, int32_t e) {
   if (cplx_)

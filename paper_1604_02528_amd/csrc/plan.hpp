@@ -127,6 +127,11 @@ struct alignas(16) LRec {
 constexpr int kTinyC = 32;
 constexpr int kTinyCF = 64;
 constexpr int kTinyS = 8;
+// Bottom subtrees of such nodes run in one workgroup each (see k_sub).
+constexpr int kSubWidth = 16;   // most nodes of one depth
+constexpr int kSubHeight = 32;  // most depths
+constexpr int kSubWaves = 8;    // wavefronts of a workgroup
+constexpr int64_t kSubNodes = 32768;  // most nodes of a launch (over the batch)
 // leading dimension of the forward sweep's LDS blocks
 template <typename T> __host__ __device__ constexpr int tiny_ldc() { return sizeof(T) == 8 ? kTinyCF : kTinyC; }
 struct alignas(16) TinyRec {
@@ -243,6 +248,14 @@ struct LaunchAux {
   // before its positions from g2_cut[q] on (the second subtree group's).  Host arrays [nlvl (+ 1)].
   const LRec *g2;
   const int32_t *g2_ptr, *g2_mid, *g2_cut;
+  // Bottom subtrees: group g runs the steps [sub_grp[g].x, sub_grp[g].x + sub_grp[g].y),
+  // step q the records sub_rec[sub_step[q] .. sub_step[q + 1]).
+  const TinyRec *sub_rec;
+  const int32_t *sub_step;
+  int64_t nsub_rec;
+  const int2 *sub_grp;
+  int32_t nsub, sub_width;        // groups; records of the widest step
+  const int32_t *lvl_u0, *lvl_u1; // host arrays [nlvl]: the positions of a single-wavefront launch in no group
   int32_t nlvl;
   const int4 *blaunch;        // host array: adjoint launches {BackStep, first, count, 0} in order: bitems
                               // [first, first + count), or small-node records (BS_TINY_R1, BS_TINY_R3)
