@@ -276,7 +276,8 @@ selinv_status selinv_factor_device(selinv_ctx *h, const void *values_dev, void *
  * A single-matrix plan runs the two subtree groups below the top chain of
  * the tree (selinv_items which = 4) the same way, group 1 on `stream` and
  * group 2 on the second stream, each group's dense X_{C,C} buffers in a
- * region of their own.  A traced run (selinv_trace) keeps one stream.
+ * region of their own.  A plan whose launches are too small to gain from it,
+ * and a traced run (selinv_trace), keep one stream.
  * EDEVICE when the stream or events cannot be created.
  */
 selinv_status selinv_run(selinv_ctx *h, const void *panels_dev, void *x_dev, void *work_dev, void *stream);

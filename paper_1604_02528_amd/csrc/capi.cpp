@@ -84,6 +84,7 @@ struct HostPlan {
   // single-matrix level plans: the subtrees under the top chain of the tree
   // in two groups that run on two streams (see subtree_groups)
   std::vector<int8_t> node_grp;   // 0: a node of the top chain (or no split); 1, 2: its subtree's group
+  bool two_streams = false;       // halves of the batch or subtree groups on two streams (see kTwoStreamWork)
   int32_t grp_q = -1;             // first level launch below the chain (-1: no split)
   std::vector<int32_t> grp_rptr;  // [nlvl + 1]: the group ranges of launch q
   std::vector<int4> grp_ranges;   // {group, launch, first position, end position}
@@ -146,6 +147,16 @@ void put(std::vector<unsigned char> &img, int64_t off, const std::vector<V> &v) 
 // dependencies, can never deadlock.
 constexpr int kSimWorkers = 256;
 constexpr int64_t kDefaultDenseMinC = 256;
+// Work of GEMM-1 and GEMM-2 per etree depth (2 c^2 s + 2 c s^2 over the batch,
+// twice for LU) from which a traversal runs on two streams.  Below, its
+// launches wait on latency, and two streams only double them.  One stream for
+// two, at 0.10 G: FP64 20^3, four matrices, 854 and 945 us; 0.17 G: two complex
+// 24^3 shifts 1818 and 2069; 0.22 G: 27-point 23x17x29, three shifts, with the
+// factorization 3577 and 3705; 0.33 G: LU 24^3, two shifts, 1234 and 1298, FP64
+// 30^3 1269 and 1300 (but 24^3, 0.08 G: 880 and 865); 0.42 G: FP64 26^3, three
+// matrices, 1467 and 1405; 0.50 G: FP64 34^3 2133 and 2002; 1.3 G: 40^3 3236
+// and 2983; 2.6 G: LU 30^3, four shifts, 4105 and 3815.
+constexpr double kTwoStreamWork = 0.37e9;
 // Row tiles from which GEMM-2 is a product of its own (from 8 on only: the
 // same within 0.4% either way, 30.07 for 30.17 ms and 3.10 for 3.08 ms on
 // 32 complex 30^3 shifts and one FP64 40^3 matrix).
@@ -576,6 +587,12 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
       }
     }
   }
+  double work = 0.0;
+  for (int64_t K = 0; K < ns; ++K) {
+    const double s = (double)S.width(K), c = (double)S.nrows(K);
+    work += 2.0 * c * s * (c + s);
+  }
+  H.two_streams = work * (double)batch * (lu ? 2.0 : 1.0) >= kTwoStreamWork * (double)S.depth;
   // work items, phase by phase (see plan.hpp)
   H.node_grp.clear();
   H.grp_q = -1;
@@ -1435,11 +1452,11 @@ DevPlan half_plan(const DevPlan &pl, int64_t bh, int64_t sbytes) {
 // Under the level schedule a batch runs as two halves, matrices [0, bh) on
 // the caller's stream and [bh, batch) on a second stream: the halves share
 // no data, and the launches of each fill the other's launch tails.  0: one
-// stream (other schedules, a single matrix, or a traced run, whose trace rows
-// are laid out for one launch over the whole batch).
+// stream (other schedules, a single matrix, a plan of little work, or a traced
+// run, whose trace rows are laid out for one launch over the whole batch).
 int64_t batch_half(const selinv_ctx *h) {
   const int64_t B = h->opts.batch;
-  return h->opts.sched == SELINV_SCHED_LEVELS && B >= 2 && !h->trace ? (B + 1) / 2 : 0;
+  return h->opts.sched == SELINV_SCHED_LEVELS && B >= 2 && !h->trace && h->H.two_streams ? (B + 1) / 2 : 0;
 }
 
 // The second traversal stream and its fork and join events (all or nothing).
@@ -1470,7 +1487,13 @@ selinv_status ensure_tstream(selinv_ctx *h) {
 // the launches above the groups on st, then (after a fork event) group 1's
 // ranges on st and group 2's on the traversal stream.  No split for a traced
 // run (its trace rows are laid out for one stream).
-bool use_groups(const selinv_ctx *h) { return h->H.grp_q >= 0 && !h->trace; }
+bool use_groups(const selinv_ctx *h) { return h->H.grp_q >= 0 && !h->trace && h->H.two_streams; }
+
+// A plan with halves or groups stays on the device of its first traversal,
+// also where its work keeps it on one stream.
+bool bound_to_device(const selinv_ctx *h) {
+  return !h->trace && (h->H.grp_q >= 0 || (h->opts.sched == SELINV_SCHED_LEVELS && h->opts.batch >= 2));
+}
 
 // Level launches [q0, q1) of a plan with subtree groups; `forked` records
 // whether the traversal stream has been forked off st (once, at the first
@@ -1502,18 +1525,23 @@ hipError_t launch_groups(selinv_ctx *h, const DevPlan &pl, const DevPlan *dpl, c
 }
 
 // Level launches [q0, q1) of both halves of the batch (bh > 0): the first
-// half on st, the second on the traversal stream with the second half's plan.
+// half on st, the second on the traversal stream with the second half's plan,
+// launch by launch, so that neither stream waits for the host.
 hipError_t launch_halves(const selinv_ctx *h, const DevPlan &pl, const LaunchAux &aux, void *work, const void *panels,
                          void *x, hipStream_t st, int q0, int q1, int64_t bh) {
   DevPlan a = pl;
   a.batch = bh;
-  hipError_t e = launch_run(a, dev_plan(h, work), aux, h->is_complex(), h->opts.sched, panels, x, 0, h->grid, st, q0, q1);
-  if (e != hipSuccess) return e;
   const DevPlan b = half_plan(pl, bh, h->sbytes());
   const int64_t off = bh * pl.panel_elems * h->sbytes();
   const DevPlan *db = reinterpret_cast<const DevPlan *>(static_cast<unsigned char *>(work) + h->H.off.plan2);
-  return launch_run(b, db, aux, h->is_complex(), h->opts.sched, static_cast<const unsigned char *>(panels) + off,
-                    static_cast<unsigned char *>(x) + off, 0, h->grid, h->tst, q0, q1);
+  hipError_t e = hipSuccess;
+  for (int q = q0; q < q1 && e == hipSuccess; ++q) {
+    e = launch_run(a, dev_plan(h, work), aux, h->is_complex(), h->opts.sched, panels, x, 0, h->grid, st, q, q + 1);
+    if (e == hipSuccess)
+      e = launch_run(b, db, aux, h->is_complex(), h->opts.sched, static_cast<const unsigned char *>(panels) + off,
+                     static_cast<unsigned char *>(x) + off, 0, h->grid, h->tst, q, q + 1);
+  }
+  return e;
 }
 
 FactorAux make_fac_aux(const selinv_ctx *h, void *work) {
@@ -1965,9 +1993,11 @@ selinv_status selinv_run(selinv_ctx *h, const void *panels_dev, void *x_dev, voi
   DevPlan pl = make_devplan(h, work_dev);
   LaunchAux aux = make_aux(h, work_dev);
   const int64_t bh = batch_half(h);
-  if (bh > 0) {
+  if (bound_to_device(h)) {
     ss = ensure_tstream(h);
     if (ss != SELINV_OK) return ss;
+  }
+  if (bh > 0) {
     e = hipEventRecord(h->ev_tfork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(h->tst, h->ev_tfork, 0);
     if (e == hipSuccess) e = launch_halves(h, pl, aux, work_dev, panels_dev, x_dev, st, 0, aux.nlvl, bh);
@@ -1978,8 +2008,6 @@ selinv_status selinv_run(selinv_ctx *h, const void *panels_dev, void *x_dev, voi
       return hip_err(h, e, "selinv launch");
     }
   } else if (use_groups(h)) {
-    ss = ensure_tstream(h);
-    if (ss != SELINV_OK) return ss;
     bool forked = false;
     e = launch_groups(h, pl, dev_plan(h, work_dev), aux, panels_dev, x_dev, st, 0, aux.nlvl, forked);
     if (e == hipSuccess && forked) e = hipEventRecord(h->ev_tjoin, h->tst);
@@ -2043,7 +2071,7 @@ selinv_status selinv_normalize_run(selinv_ctx *h, const void *ldlt_dev, void *pa
   }
   const int64_t bh = batch_half(h);
   const bool groups = bh == 0 && use_groups(h);
-  if (bh > 0 || groups) {
+  if (bound_to_device(h)) {
     ss = ensure_tstream(h);
     if (ss != SELINV_OK) return ss;
   }
