@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(NT, Planes<T>::P == 1 && !LU ? 4 : 2) k_gather
   }
 }
 
-// GEMM-2 shares of a depth (the R and P items, Alg. 1 step 4): one tile of
+// Split sums and GEMM-2 shares of a depth (the R and P items, Alg. 1 step 4): one tile of
 // LDS and no GEMM-1 operand stages (and, for complex, no Lhat prefetch), so
 // that two workgroups share a CU also for complex (one in k_items_list).
 template <typename T>
@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(NT, 2) k_ygather(const DevPlan *__restrict__ p
 }
 
 // GEMM-1 tiles of nodes with a dense X_{C,C} buffer (see do_ytile_dense),
-// each followed by its GEMM-2 share when unsplit: dense loaders only, so it
+// each followed by its GEMM-2 share when unsplit and narrow: dense loaders only, so it
 // fits two workgroups per CU also for complex.
 template <typename T>
 __global__ void __launch_bounds__(NT, 2) k_ydense(const DevPlan *__restrict__ plp, const T *Lp, T *Xp, T *Pp,
