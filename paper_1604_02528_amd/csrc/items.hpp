@@ -1143,7 +1143,7 @@ __device__ __forceinline__ void do_tiny(const TinyRec &r, int lane, const uint32
 #pragma unroll
     for (int j = 0; j < SM; ++j) {
       if (j < s && i < c) X[r.off + j * ld + s + i] = SOps<T>::scale(-1.0, acc[j]);
-      ys[i * SM + j] = acc[j];
+      ys[i * SM + j] = masked(acc[j], opaque_mask(i < c));  // (0 times an infinite entry of Lhat past c)
     }
   }
   wave_lds_fence();
@@ -1222,7 +1222,7 @@ __device__ __forceinline__ void do_tiny64(const TinyRec &r, int lane, const uint
 #pragma unroll
   for (int j = 0; j < SM; ++j) {
     if (j < s && i < c) X[r.off + j * ld + s + i] = SOps<T>::scale(-1.0, acc[j]);
-    ys[i * SM + j] = acc[j];
+    ys[i * SM + j] = masked(acc[j], opaque_mask(i < c));  // (0 times an infinite entry of Lhat past c)
   }
   wave_lds_fence();
   tiny_diag<T, SM, HERM>(r, x, y, dxy, dyx, ls, ys, X);
@@ -1300,7 +1300,7 @@ __device__ __forceinline__ void do_tiny_lu(const TinyRec &r, int lane, const uin
         gstore(X + r.off + j * ld + s + i, -al[j]);
         gstore(X + half + r.off + j * ld + s + i, -au[j]);
       }
-      ys[i * SM + j] = al[j];
+      ys[i * SM + j] = masked(al[j], opaque_mask(i < c));
     }
   }
   wave_lds_fence();

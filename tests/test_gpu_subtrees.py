@@ -102,3 +102,27 @@ def test_edges_of_the_rule(shape, m, kind):
 def test_largest_launch(batch, kind):
     """32 nodes in the subtree, halves of the batch around 32768 / 32 matrices."""
     _check("chain", 31, batch, kind, [0, 1022, 1023, batch // 2, batch - 1])
+
+
+@pytest.mark.gpu
+def test_infinite_factor_entry_stays_infinite():
+    """L_10 = inf in a 2 x 2 matrix: X_10 = -X_11 L_10 and X_00 = 1 / D_0 +
+    L_10^2 X_11 are infinite, not NaN (no padding times infinity)."""
+    import torch
+
+    from paper_1604_02528_amd import SelInv, capi
+
+    n, colptr, rowind, _, _, lo = _matrix("chain", 1, 1, "f64", 3)
+    S = SelInv(n, colptr, rowind, None, batch=1, cap=1, relax=0.0)
+    S._alloc(False)
+    ldlt = torch.from_numpy(S.factor_host(lo)).cuda()
+    at = S.packed_index()
+    assert len(at) == 3  # D_0, L_10, D_1
+    ldlt[0, int(at[1])] = float("inf")
+    st = torch.cuda.current_stream().cuda_stream
+    capi.selinv_normalize_run(S.h, ldlt, S._bufs["panels"], S._bufs["x"], S._bufs["work"], None, st)
+    S.sync()
+    x = S.panels_view("x").cpu().numpy()[0, at]
+    print(f"  x = {x}", flush=True)
+    assert np.isposinf(x[0]) and np.isneginf(x[1]) and np.isfinite(x[2])
+    S.close()
