@@ -382,7 +382,10 @@ selinv_status selinv_backward(selinv_ctx *h, const void *panels_dev, const void 
  * the context's tables (ready queues by depth class, dependency counters,
  * pushes).  Verifies that every work item is queued and run exactly once, no
  * queue overflows, a node starts only after its parent finished and phase 2
- * only after phase 1.  SELINV_OK or SELINV_EINVAL with a message.  Host only.
+ * only after phase 1.  Then the level schedule's lists: normalization chunks,
+ * subtree groups, and the GEMM-2 tiles, each launched once, with its node's
+ * diagonal blocks and on its node's stream.  SELINV_OK or SELINV_EINVAL with a
+ * message.  Host only.
  */
 selinv_status selinv_check_plan(const selinv_ctx *h);
 

@@ -984,15 +984,20 @@ void build_plan(const Symbolic &S, int64_t batch, int64_t scalar_bytes, int64_t 
   H.g2.clear();
   for (const Item &it : g2_items) H.g2.push_back(record(it));
   H.g2_ptr.assign(nl + 1, 0);
-  H.g2_mid.assign(nl, 0);
-  H.g2_cut.assign(nl, INT32_MAX);
   for (size_t i = 0; i < g2_at.size(); ++i) {
-    const int32_t q = g2_at[i].x, end = i + 1 < g2_at.size() ? g2_at[i + 1].y : n2;
-    for (int32_t p = q + 1; p <= nl; ++p) H.g2_ptr[p] = end;
-    H.g2_mid[q] = g2_at[i].z;
-    if (g2_at[i].z == end) continue;
-    for (int32_t p = H.lvl_ptr[q + 1] - 1; p >= H.lvl_ptr[q]; --p)
-      if (H.node_grp[H.items[H.lvl_items[p]].K] == 2) H.g2_cut[q] = p;
+    const int32_t end = i + 1 < g2_at.size() ? g2_at[i + 1].y : n2;
+    for (int32_t p = g2_at[i].x + 1; p <= nl; ++p) H.g2_ptr[p] = end;
+  }
+  H.g2_mid.assign(H.g2_ptr.begin() + 1, H.g2_ptr.end());
+  for (const int3 &g : g2_at) H.g2_mid[g.x] = g.z;
+  // the first position of each launch that belongs to the second subtree group
+  // (its end: none), whether or not that group has GEMM-2 tiles there
+  H.g2_cut.resize(nl);
+  for (int32_t q = 0; q < nl; ++q) {
+    H.g2_cut[q] = H.lvl_ptr[q + 1];
+    if (H.grp_q < 0) continue;
+    for (int32_t i = H.grp_rptr[q + 1] - 1; i >= H.grp_rptr[q]; --i)
+      if (H.grp_ranges[i].x == 2) H.g2_cut[q] = H.grp_ranges[i].z;
   }
   // adjoint launches (see adjoint.hip): R1 leaves -> root (deepest level
   // first), R2 for all nodes, then R3 root -> leaves
@@ -2384,7 +2389,52 @@ selinv_status selinv_check_plan(const selinv_ctx *hc) {
         if (H.node_grp[J] != 0 && H.node_grp[J] != H.node_grp[K])
           return set_err(h, SELINV_EINVAL, "plan check: a node with an ancestor in the other subtree group", K, J);
   }
-  return SELINV_OK;
+  // GEMM-2 tiles: as many as their nodes have, each launched once and with its
+  // node's diagonal blocks, by whole launches (one stream) and by the subtree
+  // groups' ranges, there by a range of its node's group (the other group's
+  // stream has not waited for the tile's operands).
+  auto check_g2 = [&](bool ranges) -> selinv_status {
+    const int64_t n2 = (int64_t)H.g2.size();
+    std::vector<uint8_t> run(n2, 0);
+    std::vector<int64_t> tiles(ns, 0);
+    auto take = [&](int32_t q, int32_t b, int32_t e, int32_t group) -> selinv_status {
+      const int2 r = g2_range(H.g2_ptr.data(), H.g2_mid.data(), H.g2_cut.data(), q, b, e);
+      if (r.x >= r.y) return SELINV_OK;
+      if (r.x < 0 || r.y > n2) return set_err(h, SELINV_EINVAL, "plan check: GEMM-2 tiles out of range", q, r.y);
+      std::vector<uint8_t> here(ns, 0);  // nodes whose diagonal blocks these positions hold
+      for (int32_t p = b; p < e; ++p) {
+        const Item &it = H.items[H.lvl_items[p]];
+        if ((H.lvl_kind[q] == LVL_DIAG || H.lvl_kind[q] == LVL_ITEMS) && it.type == ITEM_D) here[it.K] = 1;
+      }
+      for (int32_t i = r.x; i < r.y; ++i) {
+        const int64_t K = H.g2[i].it.K;
+        if (group >= 0 && H.node_grp[K] != group)
+          return set_err(h, SELINV_EINVAL, "plan check: a GEMM-2 tile launched by the other subtree group", q, K);
+        if (!here[K]) return set_err(h, SELINV_EINVAL, "plan check: a GEMM-2 tile away from its diagonal blocks", q, K);
+        if (run[i]++) return set_err(h, SELINV_EINVAL, "plan check: a GEMM-2 tile launched twice", q, K);
+        ++tiles[K];
+      }
+      return SELINV_OK;
+    };
+    selinv_status ss = SELINV_OK;
+    for (int32_t q = 0; q < nlvl && ss == SELINV_OK; ++q) {
+      if (!ranges || q < H.grp_q) {
+        if (H.lvl_ptr[q + 1] > H.lvl_ptr[q]) ss = take(q, H.lvl_ptr[q], H.lvl_ptr[q + 1], ranges ? 0 : -1);
+        continue;
+      }
+      for (int32_t i = H.grp_rptr[q]; i < H.grp_rptr[q + 1] && ss == SELINV_OK; ++i)
+        ss = take(q, H.grp_ranges[i].z, H.grp_ranges[i].w, H.grp_ranges[i].x);
+    }
+    for (int64_t K = 0; K < ns && ss == SELINV_OK; ++K) {
+      const int64_t nb = (S.width(K) + kTileN - 1) / kTileN;
+      if (tiles[K] != H.node_g2[K] * nb * nb)
+        ss = set_err(h, SELINV_EINVAL, "plan check: a node's GEMM-2 tiles are not all launched", K, tiles[K]);
+    }
+    return ss;
+  };
+  selinv_status s2 = check_g2(false);
+  if (s2 == SELINV_OK && H.grp_q >= 0) s2 = check_g2(true);
+  return s2;
 }
 
 selinv_status selinv_items(const selinv_ctx *hc, int32_t which, const int32_t **items, int64_t *n) {

@@ -1246,13 +1246,11 @@ static void launch_level(const DevPlan &pl, const DevPlan *dpl, const LaunchAux 
     e = std::min(e, aux.lvl_u1[q]);
   }
   if (e <= b) return;
-  if (aux.g2_ptr[q + 1] > aux.g2_ptr[q]) {  // GEMM-2 of the nodes whose diagonal blocks this launch runs
-    const int32_t g0 = b < aux.g2_cut[q] ? aux.g2_ptr[q] : aux.g2_mid[q];
-    const int32_t g1 = e > aux.g2_cut[q] ? aux.g2_ptr[q + 1] : aux.g2_mid[q];
-    if (g1 > g0)
-      hipLaunchKernelGGL(k_gemm2_dense<T>, dim3((unsigned)((g1 - g0) * pl.batch)), dim3(NT), 0, st, dpl, Lp, Xp, Pp,
-                         aux.g2 + g0, g1 - g0);
-  }
+  // GEMM-2 of the nodes whose diagonal blocks this launch runs
+  const int2 g2 = g2_range(aux.g2_ptr, aux.g2_mid, aux.g2_cut, q, b, e);
+  if (g2.y > g2.x)
+    hipLaunchKernelGGL(k_gemm2_dense<T>, dim3((unsigned)((g2.y - g2.x) * pl.batch)), dim3(NT), 0, st, dpl, Lp, Xp, Pp,
+                       aux.g2 + g2.x, g2.y - g2.x);
   if (aux.lvl_kind[q] == LVL_TINY && pl.half > 0) {
     hipLaunchKernelGGL(k_tiny_lu, dim3((unsigned)((e - b) * pl.batch)), dim3(64), 0, st, dpl,
                        reinterpret_cast<const double *>(Lp), reinterpret_cast<double *>(Xp),

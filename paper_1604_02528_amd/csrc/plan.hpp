@@ -149,6 +149,14 @@ enum Ctrl : int32_t { CTRL_ERR = 0, CTRL_TICKET = 32, CTRL_WORDS = 64 };
 constexpr int64_t kLdetSpan = 2048;
 __host__ __device__ constexpr int64_t ldet_parts(int64_t n) { return (n + kLdetSpan - 1) / kLdetSpan; }
 
+// The GEMM-2 tiles [x, y) that run before positions [b, e) of level launch q
+// (g2_ptr, g2_mid and g2_cut of LaunchAux).  The positions are the whole launch
+// or those of one subtree group, whose stream is not ordered against the
+// other's: a group's range takes its own nodes' tiles only.
+inline int2 g2_range(const int32_t *ptr, const int32_t *mid, const int32_t *cut, int q, int32_t b, int32_t e) {
+  return int2{b < cut[q] ? ptr[q] : mid[q], e > cut[q] ? ptr[q + 1] : mid[q]};
+}
+
 // Raw device pointers, valid for one (context, work buffer) pair.
 struct DevPlan {
   int64_t n, ns, nitems, batch, panel_elems, sq_elems, nnzA, total_rows, part_elems;
@@ -245,7 +253,8 @@ struct LaunchAux {
   const TinyRec *tiny;      // single-wavefront node records, in launch order
   // GEMM-2 tiles {K, -, 64-column block of Lhat, 64-column block of X_{C,K} | part << 16} (see
   // k_gemm2_dense): [g2_ptr[q], g2_ptr[q + 1]) run before level launch q, those from g2_mid[q] on
-  // before its positions from g2_cut[q] on (the second subtree group's).  Host arrays [nlvl (+ 1)].
+  // before its positions from g2_cut[q] on (the second subtree group's; see g2_range).  Host arrays
+  // [nlvl (+ 1)].
   const LRec *g2;
   const int32_t *g2_ptr, *g2_mid, *g2_cut;
   // Bottom subtrees: group g runs the steps [sub_grp[g].x, sub_grp[g].x + sub_grp[g].y),

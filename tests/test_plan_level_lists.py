@@ -1,0 +1,35 @@
+"""The level schedule's lists beside its launches, checked on the host plan."""
+
+import numpy as np
+import pytest
+
+from workloads import grids
+
+
+def _context(family, shape, batch=1):
+    from paper_1604_02528_amd import SelInv
+
+    rng = np.random.default_rng(11)
+    if family == "lap":
+        dtype, (colptr, rowind) = "f64", grids.weighted_laplacian_3d(shape, 0.05, rng)[:2]
+    elif family == "sten":
+        dtype, (colptr, rowind) = "c128", grids.stencil27_complex(shape, rng)[:2]
+    else:
+        dtype, (colptr, rowind) = "lu64", grids.convection_diffusion_3d(shape, rng)[:2]
+    return SelInv(int(np.prod(shape)), colptr, rowind, grids.nested_dissection(shape), dtype=dtype, batch=batch,
+                  adjoint=False, device="cpu")
+
+
+@pytest.mark.parametrize("family,shape", [("lap", (34, 34, 34)), ("lap", (40, 40, 40)), ("lap", (41, 33, 29)),
+                                          ("lap", (35, 47, 31)), ("sten", (30, 52, 44)), ("lu", (37, 25, 29)),
+                                          ("lu", (21, 60, 25))])
+def test_gemm2_tiles_of_the_subtree_groups(family, shape):
+    """Single-matrix plans with two subtree groups, among them depths whose
+    GEMM-2 nodes all lie in one group: every tile is launched exactly once, on
+    the stream of its node's group (the other stream would multiply operands
+    that nothing has ordered before it)."""
+    from paper_1604_02528_amd import capi
+
+    S = _context(family, shape)
+    assert set(capi.selinv_items(S.h, 4)[:, 0]) == {1, 2}
+    capi.selinv_check_plan(S.h)
