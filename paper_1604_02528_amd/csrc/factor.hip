@@ -640,9 +640,9 @@ template <typename T, int TK> struct FacLoadB : LoadDenseAIl<T, TK> {
 //   else:   the ancestors' entries of S_{C,C} (lower part: C-local rows i >= k)
 //           over all columns of the node, with atomic adds.
 // MFMA-bound on wide nodes, by the atomics on narrow ones.  Branch-free
-// interleaved stages and the 3M form at two workgroups a CU; 16 Hermitian 30^3
-// matrices: 12.7 ms of updates (nodes beyond the single-wavefront ones) -> 5.5 ms
-// (6.8 before the atomics took whole complex entries).
+// interleaved stages at two workgroups a CU; complex products in the
+// four-product form: the 3M form's imaginary part carries an error of the real
+// parts' size, which a nearly real pivot's imaginary part would show.
 template <typename T, bool INNER>
 __global__ void __launch_bounds__(NT, 2)
     k_fac_update(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs, const int4 *tiles, int32_t ntiles) {
@@ -680,7 +680,7 @@ __global__ void __launch_bounds__(NT, 2)
   LoadDenseAIl<T, TK> la(Q + s, ld, c, s, i0);
   FacLoadB<T, TK> lb(Q + s, ld, nc, s, k0, dls, pl.csign);
   Acc<T> acc;
-  gemm_dense_il<T, true>(0, s, la, lb, smem, acc);
+  gemm_dense_il<T, false>(0, s, la, lb, smem, acc);  // complex: four products (see above)
   acc_to_lds<T>(acc, smem);
   lds_barrier();
   const int i = threadIdx.x & 63, w = uniform((int)(threadIdx.x >> 6)), ig = i0 + i;

@@ -954,8 +954,8 @@ __device__ __forceinline__ void gemm_dense_il(int kb, int ke, const LA &la, cons
     lb.store_bf(nxt, P, kat(kt + 1), b);
     la.load_bf(kat(kt + 2), a);
     lb.load_bf(kat(kt + 2), b);
-    // MFMAs per stage: (TK / 4) steps of 2 x 2 blocks (x 3 chains in the 3M form)
-    interleave_stage<(TK / 4) * 4 * (M3 ? 3 : 1), 2 * LA::E * P, 2 * LA::E>();
+    // MFMAs per stage: (TK / 4) steps of 2 x 2 blocks (x 3 chains in the 3M form, 4 in the four-product form)
+    interleave_stage<(TK / 4) * 4 * (M3 ? 3 : P * P), 2 * LA::E * P, 2 * LA::E>();
     lds_barrier();
   }
   compute(smem + ((nk - 1) & 1) * SD);
