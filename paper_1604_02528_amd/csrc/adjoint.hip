@@ -123,10 +123,12 @@ template <typename T, int TK> struct LoadSymHalf {
   }
 };
 
-// acc (+)= A B over k < ke, complex products in the three-chain form
+// acc (+)= A B over k < ke.  Complex products in the four-product form: the
+// gradient of a nearly real matrix has imaginary parts far below the real
+// parts' rounding errors, which the 3M form would add to them.
 template <typename T, class LA, class LB>
 __device__ __forceinline__ void gemm_il(int ke, const LA &la, const LB &lb, double *smem, Acc<T> &acc, bool accumulate = false) {
-  gemm_dense_il<T, true>(0, ke, la, lb, smem, acc, accumulate);
+  gemm_dense_il<T, false>(0, ke, la, lb, smem, acc, accumulate);
 }
 
 // acc = X_{C,C}[tile rows, :] B[:, tile cols] with X_{C,C} gathered from Src (panel
@@ -264,7 +266,7 @@ __device__ void bi_m(const BCtx<T> &bx, const Geo &g, int K, int a, int b, doubl
         for (int v = 0; v < 4; ++v)
           acc.v[p][bi][bj][v] = smem[p * 64 * PITCH + (32 * wj + 16 * bj + (lane & 15)) * PITCH + 32 * wi + 16 * bi + 4 * v + (lane >> 4)];
   lds_barrier();
-  gemm2_partial<T, false, P == 1>(bx.cx, node_info(*bx.cx.pl, K), a, b, acc, smem);
+  gemm2_partial<T, false, P == 1, false>(bx.cx, node_info(*bx.cx.pl, K), a, b, acc, smem);
 }
 
 // The tile items of one step (a BackStep), each step in a kernel of its own:

@@ -224,10 +224,10 @@ __device__ void store_xtile(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, 
 // 16 XB (all 64 for FP64, 16 for complex, whose three product chains per
 // block take more registers): R's columns of a part overwrite Ls's, which
 // only that part reads.  Complex products take three real chains (see
-// Acc3M).
-template <typename T>
+// Acc3M), or four where G3 is false.
+template <typename T, bool G3 = true>
 __device__ void gemm2_block(const Acc<T> &acc, double *Ls) {
-  constexpr int P = Planes<T>::P, C = P == 1 ? 1 : 3;  // product chains
+  constexpr int P = Planes<T>::P, C = P == 2 && G3 ? 3 : P;  // accumulators of a block
   constexpr int XB = P == 1 ? 4 : 1;                   // 16-column blocks per part
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wi = w & 1, wj = w >> 1;
@@ -258,8 +258,14 @@ __device__ void gemm2_block(const Acc<T> &acc, double *Ls) {
             for (int bj = 0; bj < 2; ++bj) {
               const double b0 = acc.v[0][bi][bj][k4], b1 = acc.v[1][bi][bj][k4];
               pacc[0][xb][bj] = mfma16(a0, b0, pacc[0][xb][bj]);
-              pacc[1][xb][bj] = mfma16(a1, b1, pacc[1][xb][bj]);
-              pacc[2][xb][bj] = mfma16(a0 + a1, b0 + b1, pacc[2][xb][bj]);
+              if constexpr (C == 3) {
+                pacc[1][xb][bj] = mfma16(a1, b1, pacc[1][xb][bj]);
+                pacc[2][xb][bj] = mfma16(a0 + a1, b0 + b1, pacc[2][xb][bj]);
+              } else {
+                pacc[1][xb][bj] = mfma16(a0, b1, pacc[1][xb][bj]);
+                pacc[0][xb][bj] = mfma16(-a1, b1, pacc[0][xb][bj]);
+                pacc[1][xb][bj] = mfma16(a1, b0, pacc[1][xb][bj]);
+              }
             }
           }
         }
@@ -274,11 +280,12 @@ __device__ void gemm2_block(const Acc<T> &acc, double *Ls) {
 #pragma unroll
           for (int bj = 0; bj < 2; ++bj) {
             d4 out[P];
-            if constexpr (P == 1) {
-              out[0] = pacc[0][xb][bj];
-            } else {
+            if constexpr (C == 3) {
               out[0] = pacc[0][xb][bj] - pacc[1][xb][bj];
               out[1] = pacc[2][xb][bj] - pacc[0][xb][bj] - pacc[1][xb][bj];
+            } else {
+#pragma unroll
+              for (int p = 0; p < P; ++p) out[p] = pacc[p][xb][bj];
             }
 #pragma unroll
             for (int p = 0; p < P; ++p)
@@ -303,7 +310,7 @@ __device__ void gemm2_block(const Acc<T> &acc, double *Ls) {
 // 64qb .. 64qe - 1 of P_a only.  PF: load the next 64 columns of Lhat while
 // the current block is multiplied (off in kernels that rely on occupancy
 // instead, so that the prefetch registers do not cost a workgroup per CU).
-template <typename T, bool COH, bool PF = true>
+template <typename T, bool COH, bool PF = true, bool G3 = true>
 __device__ void gemm2_partial(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, const Acc<T> &acc, double *smem,
                               int qb = 0, int qe = 1 << 20) {
   constexpr int P = Planes<T>::P;
@@ -338,7 +345,7 @@ __device__ void gemm2_partial(const Ctx<T> &cx, const NodeInfo &nd, int a, int b
     }
     lds_barrier();
     if (PF && q0 + 64 < qend) load_l(q0 + 64);
-    gemm2_block<T>(acc, Ls);
+    gemm2_block<T, G3>(acc, Ls);
     // P = Lhat^T Y = -(Lhat^T acc)
     const double *R = Ls;
     for (int e = threadIdx.x; e < 64 * 64; e += NT) {
