@@ -58,6 +58,16 @@ __device__ __forceinline__ void blk_mma(const Blk<T> &a, const Blk<T> &b, Blk<T>
   }
 }
 
+// acc += A B, the product summed by itself first: the sums' roundings are then
+// of the update's size, and acc rounds once for 16 contraction indices (in the
+// accumulator it rounds 16 times at acc's own size).
+template <typename T> __device__ __forceinline__ void blk_mma_add(const Blk<T> &a, const Blk<T> &b, Blk<T> &acc) {
+  Blk<T> u = blk_zero<T>();
+  blk_mma<T>(a, b, u);
+#pragma unroll
+  for (int p = 0; p < Planes<T>::P; ++p) acc.p[p] += u.p[p];
+}
+
 // A block in LDS, plane p at q[p * stride]: element v * 64 + lane, so that
 // reads and writes of a register are contiguous.
 template <typename T> __device__ __forceinline__ Blk<T> blk_from_lds(const double *q, int stride) {

@@ -88,8 +88,16 @@ __device__ __forceinline__ double fast_recip(double d) {
 }
 __device__ __forceinline__ cplx fast_recip(cplx d) {
   const double r = fast_recip(fma(d.re, d.re, d.im * d.im));
-  return cplx{d.re * r, -d.im * r};
+  const cplx q{d.re * r, -d.im * r};  // r rounds three times: one more step q += q (1 - d q)
+  const cplx e{fma(-d.re, q.re, fma(d.im, q.im, 1.0)), -fma(d.re, q.im, d.im * q.re)};
+  return cplx{fma(q.re, e.re, fma(-q.im, e.im, q.re)), fma(q.re, e.im, fma(q.im, e.re, q.im))};
 }
+// x / d from di = 1 / d
+__device__ __forceinline__ double fast_quot(double x, double d, double di) {
+  const double y = x * di;
+  return fma(fma(-y, d, x), di, y);
+}
+__device__ __forceinline__ cplx fast_quot(cplx x, cplx, cplx di) { return x * di; }
 __device__ __forceinline__ uint32_t exponent_of(double v) {
   return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 52) & 0x7ffu;
 }
@@ -112,8 +120,9 @@ template <int Q> __device__ __forceinline__ void ldl_step(cplx &x, cplx w, const
 __device__ __forceinline__ double neg_y(double y, double) { return -y; }
 __device__ __forceinline__ NegY neg_y(cplx y, double sg) { return NegY{cplx{-y.re, -y.im}, cplx{sg * y.re, sg * y.im}}; }
 
-// The lanes of ldl16 in LDS: row r of L and D at [17 r + k], M(p, q) at
-// [17 (16 + q) + p], 1 / D_j at [kLdlD + j]; planes kLdlLds apart.
+// The rows of ldl16 in LDS: before it, row r of S (lower part) at [17 r + k] and
+// column q of the identity at [17 (16 + q) + p]; afterwards L and D, and M(p, q),
+// in their places, and 1 / D_j at [kLdlD + j]; planes kLdlLds apart.
 constexpr int kLdlD = 32 * 17;
 constexpr int kLdlLds = kLdlD + 16;
 template <typename T> __device__ __forceinline__ void lds_set(double *q, T v) {
@@ -121,6 +130,18 @@ template <typename T> __device__ __forceinline__ void lds_set(double *q, T v) {
   for (int p = 0; p < Planes<T>::P; ++p) q[p * kLdlLds] = Planes<T>::get(v, p);
 }
 template <typename T> __device__ __forceinline__ T lds_at(const double *q) { return Planes<T>::from(q, kLdlLds); }
+// A block of w < 16 columns is padded with the identity.
+template <typename T> __device__ __forceinline__ void ldl16_stage(const Blk<T> &b, int w, double *ls) {
+  const int r = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int c = 4 * v + g;
+    const T id = pick(r == c, SOps<T>::one(), zero_of<T>());
+    lds_set<T>(ls + 17 * r + c, pick(r < w && c <= r, blk_get(b, v), id));
+    lds_set<T>(ls + 17 * (16 + r) + c, id);
+  }
+  wave_lds_fence();
+}
 template <typename T> __device__ __forceinline__ void ldl16_put(const T (&x)[16], T dinv, double *ls) {
   const int lane = threadIdx.x & 63;
   if (lane < 32) {
@@ -131,12 +152,15 @@ template <typename T> __device__ __forceinline__ void ldl16_put(const T (&x)[16]
 }
 
 // Unpivoted LDL^T (LDL^H) of one 16 x 16 diagonal block and the inverse of
-// its L, by one wavefront: lane r < 16 holds row r of S (lower part) in x, lane
+// its L, by one wavefront: lane r < 16 has row r of S (lower part), lane
 // 16 + q column q of the identity (lanes 32 .. 63 are not used).  Step j needs
 // the same update on both:
 // row r:  S(r, q) -= L(r, j) W(q, j),  column q:  M(p, q) -= L(p, j) M(j, q),
-// i.e. x[q] -= w_q (x[j] / d_j) with w_q = S(q, j) of lane q.  A block of w < 16
-// columns is padded with the identity (its columns are skipped in fours).
+// i.e. x[q] -= w_q (x[j] / d_j) with w_q = S(q, j) of lane q.  The updates of
+// an entry are summed by themselves in x and meet the entry, read from LDS, when
+// its column's step comes: one rounding at the entry's size (the entry in x
+// itself would take one or, complex, two per step).  The columns of the padding
+// are skipped in fours.
 // Row r becomes L(r, 0 .. r - 1) and D_r, column q M(:, q), and lane j < 16
 // gets 1 / D_j.  False when a pivot is outside the range of the fast
 // reciprocal (x is then undefined).
@@ -146,20 +170,26 @@ template <typename T> __device__ __forceinline__ void ldl16_put(const T (&x)[16]
 // there is no branch per column (with scalar lane reads and branches a block
 // took 4.7 us of the 128-column kernel's 39 us, FP64).
 template <typename T>
-__device__ __forceinline__ bool ldl16(T (&x)[16], int w, double cs, T &dinv) {
+__device__ __forceinline__ bool ldl16(const double *ls, T (&x)[16], int w, double cs, T &dinv) {
   const int lane = threadIdx.x & 63;
+  const double *row = ls + 17 * (lane & 31);
   const double sg = lane < 16 ? cs : 1.0;
   dinv = SOps<T>::one();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) x[k] = zero_of<T>();
+  T next = lds_at<T>(row);
   static_for(
       [&](auto bc) {
         constexpr int b = decltype(bc)::value;
-        if (b == 0 || 4 * b < w)
+        if (b == 0 || 4 * b < w) {
           static_for(
               [&](auto jc) {
                 constexpr int j = 4 * b + decltype(jc)::value;
-                const T ww = even_row(x[j]);
-                const T di = fast_recip(bcast16<j>(ww));
-                const T y = x[j] * di;
+                const T xj = next + x[j];
+                if constexpr (j < 15) next = lds_at<T>(row + j + 1);
+                const T ww = even_row(xj);
+                const T d = bcast16<j>(ww), di = fast_recip(d);
+                const T y = fast_quot(xj, d, di);
                 const auto ny = neg_y(y, sg);
                 static_for(
                     [&](auto qc) {
@@ -169,18 +199,21 @@ __device__ __forceinline__ bool ldl16(T (&x)[16], int w, double cs, T &dinv) {
                     std::make_integer_sequence<int, 15 - j>{});
                 int ln = lane;
                 asm("" : "+v"(ln));  // the lane masks are made here: kept from step to step they spill
-                x[j] = pick((unsigned)(ln - j - 1) < (unsigned)(15 - j), y, x[j]);
+                x[j] = pick((unsigned)(ln - j - 1) < (unsigned)(15 - j), y, xj);
                 dinv = pick(ln == j, di, dinv);
               },
               std::make_integer_sequence<int, 4>{});
+        } else {
+#pragma unroll
+          for (int k = 4 * b; k < 4 * b + 4; ++k) x[k] = lds_at<T>(row + k);
+        }
       },
       std::make_integer_sequence<int, 4>{});
   return __ballot(lane < 16 && !recip_ok(dinv)) == 0;
 }
 
-// The same from LDS, with full divisions, for the blocks ldl16 turns down:
-// lanes 0 .. 31 have put their x at [17 lane].  A zero or non-finite pivot is
-// recorded (column first + j).
+// The same in LDS, with full divisions, for the blocks ldl16 turns down.  A
+// zero or non-finite pivot is recorded (column first + j).
 template <typename T>
 __device__ __forceinline__ void ldl16_wide_range(double *ls, int w, double cs, int64_t first, unsigned long long *ferr) {
   const int lane = threadIdx.x & 63, row = lane & 31;
@@ -204,19 +237,17 @@ __device__ __forceinline__ void ldl16_wide_range(double *ls, int w, double cs, i
   }
 }
 
-// Both of them; load(x) gives each lane its x again.
-template <typename T, class F>
-__device__ __forceinline__ void ldl16_block(T (&x)[16], F load, int w, double cs, double *ls, int64_t first,
-                                            unsigned long long *ferr) {
-  T dinv;
-  const bool ok = ldl16<T>(x, w, cs, dinv);
-  if (!ok) load(x);
-  ldl16_put<T>(x, dinv, ls);
+// Both of them, on a staged block.
+template <typename T>
+__device__ __forceinline__ void ldl16_block(int w, double cs, double *ls, int64_t first, unsigned long long *ferr) {
+  T x[16], dinv;
+  const bool ok = ldl16<T>(ls, x, w, cs, dinv);
   wave_lds_fence();
-  if (!ok) {
+  if (ok)
+    ldl16_put<T>(x, dinv, ls);
+  else
     ldl16_wide_range<T>(ls, w, cs, first, ferr);
-    wave_lds_fence();
-  }
+  wave_lds_fence();
 }
 
 // M as the A operand of W^T = M S^T (conjugated if Hermitian).
@@ -248,20 +279,6 @@ template <typename T> __device__ __forceinline__ void ldl16_store(const double *
 // atomics of nodes with c near 64 bound it: 1.9 ms with the two planes of an
 // entry added by separate instructions, 1.1 with whole entries, see blk_atomic).
 // ---------------------------------------------------------------------------
-// x of ldl16 from the panel.
-template <typename T>
-__device__ __forceinline__ void small_load(const T *Q, int ld, int s, T (&x)[16]) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int k = 0; k < 16; ++k)
-    x[k] = ld_off(Q, ((uint32_t)(k * ld + lane) & opaque_mask32(lane < s && k <= lane)) * (uint32_t)sizeof(T));
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const T id = pick(lane - 16 == k || (lane == k && k >= s), SOps<T>::one(), zero_of<T>());
-    x[k] = pick(lane < s && k <= lane, x[k], id);
-  }
-}
-
 template <typename T>
 __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs,
                                                   int32_t count, unsigned long long *ferr) {
@@ -279,8 +296,7 @@ __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__
   const double cs = pl.csign;
   const int kq = min(lane, c - 1);
   const int64_t kc = c > 0 ? gp(pl.kcol)[nd.rp + kq] : 0, kp = c > 0 ? gp(pl.kpos)[nd.rp + kq] : 0;
-  T x[16];
-  small_load<T>(Q, ld, s, x);
+  const Blk<T> dg = blk_load<T>(Q, ld, s, s);
   Blk<T> wb[NST];
 #pragma unroll
   for (int i = 0; i < NST; ++i)
@@ -304,7 +320,8 @@ __global__ void __launch_bounds__(64, 2) k_fac_small(const DevPlan *__restrict__
     }
   };
   load_pos(0);
-  ldl16_block<T>(x, [&](T(&y)[16]) { small_load<T>(Q, ld, s, y); }, s, cs, ls, nd.first, ferr + l);
+  ldl16_stage<T>(dg, s, ls);
+  ldl16_block<T>(s, cs, ls, nd.first, ferr + l);
   ldl16_store<T>(ls, Q, ld, s);
   const int nv = (s + 3) / 4;
   const Blk<T> m = ldl16_m<T>(ls, cs);
@@ -364,8 +381,8 @@ __global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ p
     rcol[threadIdx.x] = gp(pl.kcol)[nd.rp + kq];
     rpos[threadIdx.x] = gp(pl.kpos)[nd.rp + kq];
   }
-  T x[16];
-  if (wv == 0) small_load<T>(Q, ld, s, x);
+  Blk<T> dg;
+  if (wv == 0) dg = blk_load<T>(Q, ld, s, s);
   Blk<T> sb[NST / W];
 #pragma unroll
   for (int q = 0; q < NST / W; ++q) {
@@ -390,7 +407,8 @@ __global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ p
     }
   }
   if (wv == 0) {
-    ldl16_block<T>(x, [&](T(&y)[16]) { small_load<T>(Q, ld, s, y); }, s, cs, ls, nd.first, ferr + l);
+    ldl16_stage<T>(dg, s, ls);
+    ldl16_block<T>(s, cs, ls, nd.first, ferr + l);
     ldl16_store<T>(ls, Q, ld, s);
   }
   lds_barrier();
@@ -495,31 +513,18 @@ __global__ void __launch_bounds__(64 * kFacWaves, 2)
       if (wv == kk) store_diag(kk);
       lds_barrier();
       if (wv >= k && wv < nb)
-        blk_mma<T>(blk_from_lds<T>(lp + 256 * wv, LP), blk_from_lds<T>(wp + 256 * wv, LP), dg);
+        blk_mma_add<T>(blk_from_lds<T>(lp + 256 * wv, LP), blk_from_lds<T>(wp + 256 * wv, LP), dg);
     }
     if (wv == k) {
       const int w = min(16, s - 16 * k);
-      auto rows = [&](T(&y)[16]) {
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) ls[p * kLdlLds + r * 17 + 4 * v + g] = dg.p[p][v];
-        wave_lds_fence();
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-          const T id = pick(lane - 16 == c || (lane == c && c >= w), SOps<T>::one(), zero_of<T>());
-          y[c] = pick(lane < w && c <= lane, lds_at<T>(ls + r * 17 + c), id);
-        }
-        wave_lds_fence();
-      };
-      T x[16];
-      rows(x);
-      ldl16_block<T>(x, rows, w, cs, ls, nd.first + 16 * k, ferr + l);
+      ldl16_stage<T>(dg, w, ls);
+      ldl16_block<T>(w, cs, ls, nd.first + 16 * k, ferr + l);
     }
     if (k > 0) {
 #pragma unroll
       for (int q = 0; q < kFacSlots; ++q)
-        if (bj[q] >= k) blk_mma<T>(blk_from_lds<T>(lp + 256 * bj[q], LP), blk_from_lds<T>(wp + 256 * bi[q], LP), ob[q]);
+        if (bj[q] >= k)
+          blk_mma_add<T>(blk_from_lds<T>(lp + 256 * bj[q], LP), blk_from_lds<T>(wp + 256 * bi[q], LP), ob[q]);
     }
   }
   wave_lds_fence();
@@ -605,7 +610,7 @@ __global__ void __launch_bounds__(NT, 2)
     blk_store<T>(blk_scale_rows<T>(w, dl[k], 16), R + (int64_t)(16 * k) * ld, ld, rows, s - 16 * k);
 #pragma unroll
     for (int j = k + 1; j < NB; ++j)
-      if (j < nb) blk_mma<T>(blk_from_lds<T>(b + 256 * j, LP), w, sb[j]);
+      if (j < nb) blk_mma_add<T>(blk_from_lds<T>(b + 256 * j, LP), w, sb[j]);
   }
 }
 
