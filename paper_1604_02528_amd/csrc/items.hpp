@@ -1312,10 +1312,11 @@ __device__ __forceinline__ void do_tiny_lu(const TinyRec &r, int lane, const uin
   }
   wave_lds_fence();
   if (x < s && y < s) {
-    double t = dxy;
+    double t = 0.0;  // (added to Dt^{-1} at the end: one rounding at its size)
     for (int q0 = 0; q0 < c; q0 += 8)
 #pragma unroll
       for (int q = q0; q < q0 + 8; ++q) t += us[q * SM + x] * ys[q * SM + y];
+    t += dxy;
     gstore(X + r.off + y * ld + x, t);
     gstore(X + half + r.off + x * ld + y, t);
   }
