@@ -708,7 +708,9 @@ __global__ void __launch_bounds__(NT, 1)
 //   X(I, J) = M_I A_I,  A_I = [I = J] - sum_{J <= K < I} L(I, K) X(K, J),  M_I = L(I, I)^{-1},
 // wavefront w holding the A_I of every fourth strip in registers: once X(K, J)
 // is known (one product with M_K) it goes to LDS, and every wavefront updates
-// its strips with it.  The product's result layout is the layout of the next
+// its strips with it (a strip's 16 columns summed by themselves first, see
+// blk_mma_add: in A_I itself the errors of a 256-column L_KK^{-1} with entries
+// that grow were 1.2 to 1.5 times those of the form before).  The product's result layout is the layout of the next
 // one's B operand, so X needs no rearrangement; one barrier per strip; the
 // L(:, K + 1) are loaded while L(:, K) is used.  The M_I of a wavefront's strips
 // come first, all at once: one strip per row of 16 lanes, lane q computing
@@ -818,14 +820,14 @@ __global__ void __launch_bounds__(NT, MAXS == 64 || Planes<T>::P == 1 ? 3 : 2)
 #pragma unroll
     for (int q = 0; q < NS; ++q)
       if (wv + W * q == k + 1 && k + 1 < n) {
-        blk_mma<T>(lb[q], nx, acc[q]);
+        blk_mma_add<T>(lb[q], nx, acc[q]);
         Blk<T> xn = blk_zero<T>();
         blk_mma<T>(m_of(q), acc[q], xn);
         blk_to_lds<T>(xn, xb[(k + 1) & 1], 256);
       }
 #pragma unroll
     for (int q = 0; q < NS; ++q)
-      if (wv + W * q > k + 1 && wv + W * q < n) blk_mma<T>(lb[q], nx, acc[q]);
+      if (wv + W * q > k + 1 && wv + W * q < n) blk_mma_add<T>(lb[q], nx, acc[q]);
     if (k + 1 < n) load_l(k + 1, lb);
     // rows of strip k of columns J: wavefront w takes columns 4 w + g, lanes along the rows
     const int col = 4 * wv + g, row = 16 * k + r;
