@@ -20,6 +20,7 @@ SELINV_R64, SELINV_C128, SELINV_H128, SELINV_LU64 = 0, 1, 2, 3
 SCHED_PERSISTENT, SCHED_LEVELS, SCHED_PUSH = 0, 1, 2
 STATUS = {0: "OK", 1: "EINVAL", 2: "EPATTERN", 3: "ESINGULAR", 4: "ENOMEM", 5: "EDEVICE", 6: "ESTATE",
           7: "EUNSUPPORTED"}
+ESINGULAR = 3
 
 EXPORTED = (
     "selinv_default_opts", "selinv_version", "selinv_tune_key", "selinv_analyze", "selinv_symbolic", "selinv_sizes",
