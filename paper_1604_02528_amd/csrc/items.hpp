@@ -122,8 +122,8 @@ __device__ __forceinline__ void scatter_lower(const DevPlan &pl, int64_t rp, int
 // along i (one column k per wave and step) for the gather and the G(i, k)
 // stores; the mirror stores go through an LDS transpose so that they are
 // contiguous too.
-// MAYBE_LU = false compiles the LU branch out (a kernel that never runs an LU plan).
-template <typename T, bool MAYBE_LU = true>
+// MAYBE_LU = false: for kernels that never run an LU plan.
+template <typename T, bool MAYBE_LU>
 __device__ void do_gtile(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, double *smem, int64_t *rt, const T *Src) {
   const DevPlan &pl = *cx.pl;
   const int c = uniform(nd.c);
@@ -389,7 +389,6 @@ __device__ void do_ytile(const Ctx<T> &cx, const NodeInfo &nd, int a, int bp, do
     lds_barrier();
     LoadGather<T, COH> la{cx.Xp, pl.kcol + rp, pl.kpos + rp, pl.posarr, rt, rt + 64, c, ke, i0};
     la.cs = pl.csign;
-    la.du = pl.half;  // LU plans: X_{C,C}'s upper part from the X^T panel set
     LoadPanelK<T, false> lb{cx.Lp, off, ld, s, 0, ke, j0, s};
     gemm_tile<T>(kb, ke, la, lb, smem, acc);
   }
@@ -410,7 +409,10 @@ __device__ void do_ytile(const Ctx<T> &cx, const NodeInfo &nd, int a, int bp, do
 }
 
 // The gathered GEMM-1 tile of the level schedule's k_ygather: do_ytile without
-// the dense-buffer form, and (up) do_yutile.
+// the dense-buffer form, and (up) the tile of an LU plan's upper part, rows
+// 64a.. and columns 64b.. of X_{K,C}^T = -(X_{C,C})^T Uhat^T, gathered with the
+// two X panel sets exchanged and stored into the second (it has no GEMM-2
+// share: A^{-1}_{K,K} needs only X_{C,K}).
 template <typename T>
 __device__ __forceinline__ void do_ygather(const Ctx<T> &cx, const NodeInfo &nd, int a, int bp, bool up, double *smem,
                                            int64_t *rt) {
@@ -691,7 +693,6 @@ __device__ __forceinline__ void do_gemm2(const Ctx<T> &cx, const NodeInfo &nd, i
 template <typename T, bool COH>
 __device__ void dtile_core(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, double *smem, const T *Dti, int sld, T *Xkk,
                            int dld) {
-  const DevPlan &pl = *cx.pl;
   const int s = nd.s;
   const int nr = nd.np;
   const int64_t pb = nd.poff;
@@ -744,24 +745,6 @@ __device__ void dtile_core(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, d
     }
   }
   lds_barrier();
-  if (uniform(pl.half > 0 ? 1 : 0)) {
-    // LU plan: no symmetrization.  X_KK's blocks (a, b) and (b, a) into the
-    // L half, their transposes into the U^T half (entry (r, q) = X(q, r)).
-    T *Xu = Xkk + pl.half;
-    for (int e = threadIdx.x; e < 64 * 64; e += NT) {
-      const int i = e & 63, j = e >> 6;
-      if (a0 + i < s && b0 + j < s) {
-        Mem<COH>::st(Xkk + (int64_t)(b0 + j) * dld + a0 + i, lds_get<T>(Sab, i, j));
-        Mem<COH>::st(Xu + (int64_t)(b0 + j) * dld + a0 + i, lds_get<T>(Sba, j, i));
-      }
-      if (a != b && b0 + i < s && a0 + j < s) {
-        Mem<COH>::st(Xkk + (int64_t)(a0 + j) * dld + b0 + i, lds_get<T>(Sba, i, j));
-        Mem<COH>::st(Xu + (int64_t)(a0 + j) * dld + b0 + i, lds_get<T>(Sab, j, i));
-      }
-    }
-    lds_barrier();
-    return;
-  }
   // x(i, j) = (T[a0+i, b0+j] + T[b0+j, a0+i]) / 2 (the second term conjugated
   // in a Hermitian plan); keep it in Sab
   const double cs = cx.pl->csign;
@@ -1322,33 +1305,7 @@ __device__ __forceinline__ void do_tiny_lu(const TinyRec &r, int lane, const uin
   }
 }
 
-// LU plans (gathered X_{C,C}, unsplit nodes): the GEMM-1 tile of the upper
-// part, rows 64a.. and columns 64b.. of X_{K,C}^T = -(X_{C,C})^T Uhat^T, where
-// Uhat^T is the normalized U^T panel set and (X_{C,C})^T is gathered with the
-// two X panel sets exchanged; stored into the U half of X.  The upper part
-// takes no GEMM-2 share (A^{-1}_{K,K} needs only X_{C,K}).
-template <typename T, bool COH>
-__device__ void do_yutile(const Ctx<T> &cx, const NodeInfo &nd, int a, int b, double *smem, int64_t *rt) {
-  const DevPlan &pl = *cx.pl;
-  const int s = uniform(nd.s), c = uniform(nd.c), ld = s + c;
-  const int64_t off = nd.off, rp = nd.rp;
-  const int i0 = a * 64, j0 = b * 64;
-  if (threadIdx.x < 64) {
-    const int ig = i0 + threadIdx.x;
-    rt[threadIdx.x] = gp(pl.kcol)[rp + (ig < c ? ig : 0)];
-    rt[64 + threadIdx.x] = gp(pl.kpos)[rp + (ig < c ? ig : 0)];
-  }
-  lds_barrier();
-  Ctx<T> cu = cx;
-  cu.Xp = cx.Xp + pl.half;
-  LoadGather<T, COH> la{cu.Xp, pl.kcol + rp, pl.kpos + rp, pl.posarr, rt, rt + 64, c, c, i0};
-  la.du = -pl.half;
-  LoadPanelK<T, false> lb{cx.Lp + pl.half, off, ld, s, 0, c, j0, s};
-  Acc<T> acc;
-  gemm_tile<T>(0, c, la, lb, smem, acc);
-  store_xtile<T, COH>(cu, nd, a, b, acc, smem);
-}
-
+// Any item of a symmetric plan (an LU plan's run in kernels of their own types).
 // Inlined into the kernels, so that the node record stays in scalar registers
 // (a call would pass it through the stack).
 template <typename T, bool COH>
@@ -1356,11 +1313,9 @@ __device__ __forceinline__ void do_item(const Ctx<T> &cx, const Item &item, cons
                                         int64_t *rt) {
   const Item it = uniform(item);
   if (it.type == ITEM_G) {
-    do_gtile<T>(cx, nd, it.a, it.b, smem, rt, cx.Xp);
+    do_gtile<T, false>(cx, nd, it.a, it.b, smem, rt, cx.Xp);
   } else if (it.type == ITEM_Y) {
     do_ytile<T, COH>(cx, nd, it.a, it.b, smem, rt);
-  } else if (it.type == ITEM_YU) {
-    do_yutile<T, COH>(cx, nd, it.a, it.b, smem, rt);
   } else if (it.type == ITEM_R) {
     do_rtile<T, COH>(cx, nd, it.a, it.b, smem);
   } else if (it.type == ITEM_P) {

@@ -709,45 +709,6 @@ template <typename T, int TK> struct LoadDenseBC : LoadDenseB<T, TK> {
   }
 };
 
-// B(k, x) = M[k * ld + x0 + x] for k < kend, x0 + x < xmax: a row-major view
-// (the transpose of a column-major block); lanes run along x, and the row of a
-// slot, k0 + (t >> 6) + 4 m, is uniform in a wave.
-template <typename T, int TK> struct LoadDenseBT {
-  static constexpr int E = 64 * TK / NT;
-  static constexpr bool kConj = true;  // the transposed operand: conjugated in a Hermitian plan
-  const T *M;
-  int64_t ld;
-  int kend, kq;
-  uint32_t vcol;
-  int64_t cmask;
-  bool cols_full;
-  double cs = 1.0;  // -1: conjugate every element
-  __device__ __forceinline__ double imsign(int, int) const { return cs; }
-  __device__ __forceinline__ LoadDenseBT(const T *M_, int ld_, int kend_, int x0, int xmax)
-      : M(M_), ld(ld_), kend(kend_) {
-    const int x = x0 + (threadIdx.x & 63);
-    kq = uniform((int)(threadIdx.x >> 6));
-    vcol = (uint32_t)(x < xmax ? x : x0) * (uint32_t)sizeof(T);
-    cmask = opaque_mask(x < xmax);
-    cols_full = x0 + 64 <= xmax;
-  }
-  __device__ __forceinline__ int slot(int, int m) const {
-    const int e = threadIdx.x + NT * m;
-    return (e >> 6) * PITCH + (e & 63);
-  }
-  __device__ __forceinline__ bool all_valid(int k0) const { return cols_full && k0 + TK <= kend; }
-  __device__ __forceinline__ int64_t mask(int k0, int m) const {
-    return cmask & opaque_mask(k0 + kq + (NT / 64) * m < kend);
-  }
-  __device__ __forceinline__ void load(int k0, DVals<T, TK> &v) const {
-#pragma unroll
-    for (int m = 0; m < E; ++m) {
-      const int k = min(k0 + kq + (NT / 64) * m, kend - 1);
-      v.v[m] = ld_off(M + (int64_t)k * ld, vcol);
-    }
-  }
-};
-
 // Stage store of the dense loaders: a stage wholly inside the operand (the
 // common case) is stored without masks.
 template <typename T, class L, class V, int TK>
