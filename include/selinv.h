@@ -383,9 +383,10 @@ selinv_status selinv_backward(selinv_ctx *h, const void *panels_dev, const void 
  * pushes).  Verifies that every work item is queued and run exactly once, no
  * queue overflows, a node starts only after its parent finished and phase 2
  * only after phase 1.  Then the level schedule's lists: normalization chunks,
- * subtree groups, and the GEMM-2 tiles, each launched once, with its node's
- * diagonal blocks and on its node's stream.  SELINV_OK or SELINV_EINVAL with a
- * message.  Host only.
+ * subtree groups, the GEMM-2 tiles, each launched once, with its node's
+ * diagonal blocks and on its node's stream, and the bottom subtrees that run in
+ * one workgroup each, every small node in exactly one of them or in its depth's
+ * launch.  SELINV_OK or SELINV_EINVAL with a message.  Host only.
  */
 selinv_status selinv_check_plan(const selinv_ctx *h);
 

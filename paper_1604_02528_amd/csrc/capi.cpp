@@ -2434,7 +2434,77 @@ selinv_status selinv_check_plan(const selinv_ctx *hc) {
   };
   selinv_status s2 = check_g2(false);
   if (s2 == SELINV_OK && H.grp_q >= 0) s2 = check_g2(true);
-  return s2;
+  if (s2 != SELINV_OK) return s2;
+  // Bottom subtrees: every node of one is a single-wavefront node that the
+  // subtree's kernel takes, in one step of one subtree, its parent in the step
+  // before (the root's in none), its children in the subtree too; the subtrees
+  // of the second stream are those of the second group; and the single-wavefront
+  // launches' remaining positions are the nodes of no subtree.
+  std::vector<int32_t> in_sub(ns, -1), step_of(ns, -1);
+  const int64_t nsub = (int64_t)H.sub_grp.size();
+  if (H.sub_split > nsub || (H.grp_q < 0 && H.sub_split != nsub))
+    return set_err(h, SELINV_EINVAL, "plan check: bottom subtrees split off their stream", H.sub_split, nsub);
+  int64_t nrec = 0;
+  for (int64_t g = 0; g < nsub; ++g) {
+    const int2 gr = H.sub_grp[g];
+    if (gr.y < 1 || gr.y > kSubHeight || gr.x < 0 || gr.x + gr.y >= (int64_t)H.sub_step.size())
+      return set_err(h, SELINV_EINVAL, "plan check: a bottom subtree's steps out of range", g, gr.y);
+    for (int32_t q = gr.x; q < gr.x + gr.y; ++q) {
+      const int32_t b = H.sub_step[q], e = H.sub_step[q + 1];
+      if (b != nrec || e <= b || e > (int64_t)H.sub_rec.size() || e - b > H.sub_width || e - b > kSubWidth ||
+          (q == gr.x && e - b != 1))
+        return set_err(h, SELINV_EINVAL, "plan check: a bottom subtree's step out of range", g, q);
+      nrec = e;
+      for (int32_t i = b; i < e; ++i) {
+        const TinyRec &r = H.sub_rec[i];
+        const int64_t K = r.K, P = K >= 0 && K < ns ? S.sparent[K] : -1;
+        if (K < 0 || K >= ns || in_sub[K] >= 0)
+          return set_err(h, SELINV_EINVAL, "plan check: a node in two bottom subtrees", K, g);
+        if (r.s != S.width(K) || r.c != S.nrows(K) || r.off != S.panel_off[K] || r.s > kTinyS ||
+            r.c > (h->sbytes() == 8 ? kTinyCF : kTinyC))
+          return set_err(h, SELINV_EINVAL, "plan check: a bottom subtree's record does not fit its node", K, g);
+        if (q > gr.x && (P < 0 || in_sub[P] != g || step_of[P] != q - 1))
+          return set_err(h, SELINV_EINVAL, "plan check: a bottom subtree's node without its parent before it", K, g);
+        if (H.grp_q >= 0 && H.node_grp[K] != (g < H.sub_split ? 1 : 2))
+          return set_err(h, SELINV_EINVAL, "plan check: a bottom subtree on the other group's stream", K, g);
+        in_sub[K] = (int32_t)g;
+        step_of[K] = q;
+      }
+    }
+  }
+  if (nrec != (int64_t)H.sub_rec.size())
+    return set_err(h, SELINV_EINVAL, "plan check: bottom subtree records in no step", nrec, (int64_t)H.sub_rec.size());
+  for (int64_t K = 0; K < ns; ++K) {
+    const int64_t P = S.sparent[K];
+    if (P >= 0 && in_sub[P] >= 0 && in_sub[K] != in_sub[P])
+      return set_err(h, SELINV_EINVAL, "plan check: a child outside its parent's bottom subtree", K, P);
+    if (P >= 0 && in_sub[K] >= 0 && in_sub[P] >= 0 && step_of[K] != step_of[P] + 1)
+      return set_err(h, SELINV_EINVAL, "plan check: a bottom subtree's child in a wrong step", K, P);
+  }
+  for (int32_t q = 0; q < nlvl && nsub > 0; ++q)
+    for (int32_t p = H.lvl_ptr[q]; p < H.lvl_ptr[q + 1]; ++p) {
+      const int64_t K = H.lvl_kind[q] == LVL_Y128 ? H.y128[H.lvl_items[p]].K : H.items[H.lvl_items[p]].K;
+      const bool kept = H.lvl_kind[q] != LVL_TINY || (p >= H.lvl_u0[q] && p < H.lvl_u1[q]);
+      if (kept != (in_sub[K] < 0))
+        return set_err(h, SELINV_EINVAL, "plan check: a node launched by its depth and by a bottom subtree, or by neither", K, q);
+    }
+  // Normalization tiles (FP64): in every chunk, each 64-column tile of each of its row blocks once
+  if (h->sbytes() != 8 && !H.rtiles.empty())
+    return set_err(h, SELINV_EINVAL, "plan check: normalization tiles of a complex plan", (int64_t)H.rtiles.size());
+  if ((int64_t)H.rt_cut.size() != nq + 1 || H.rt_cut.front() != 0 || H.rt_cut.back() != (int64_t)H.rtiles.size())
+    return set_err(h, SELINV_EINVAL, "plan check: normalization tiles do not fit their chunks", nq, (int64_t)H.rtiles.size());
+  for (int64_t q = 0; q < nq && h->sbytes() == 8; ++q) {
+    std::vector<std::pair<int32_t, int32_t>> want, have;
+    for (int32_t i = H.norm_cut[5 * q + 3]; i < H.norm_cut[5 * (q + 1) + 3]; ++i)
+      for (int64_t x = 0; x < (S.width(H.rblocks[i].x) + kTileN - 1) / kTileN; ++x)
+        want.push_back({H.rblocks[i].x, H.rblocks[i].y | (int32_t)x << kRowBlockBits});
+    for (int32_t i = std::max(0, H.rt_cut[q]); i < std::min(H.rt_cut[q + 1], (int32_t)H.rtiles.size()); ++i) have.push_back({H.rtiles[i].x, H.rtiles[i].y});
+    std::sort(want.begin(), want.end());
+    std::sort(have.begin(), have.end());
+    if (want != have)
+      return set_err(h, SELINV_EINVAL, "plan check: a chunk's normalization tiles are not those of its row blocks", q, (int64_t)have.size());
+  }
+  return SELINV_OK;
 }
 
 selinv_status selinv_items(const selinv_ctx *hc, int32_t which, const int32_t **items, int64_t *n) {

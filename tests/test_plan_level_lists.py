@@ -33,3 +33,26 @@ def test_gemm2_tiles_of_the_subtree_groups(family, shape):
     S = _context(family, shape)
     assert set(capi.selinv_items(S.h, 4)[:, 0]) == {1, 2}
     capi.selinv_check_plan(S.h)
+
+
+@pytest.mark.parametrize("family,shape,batch", [("lap", (13, 9, 7), 1), ("lap", (30, 30, 30), 1), ("lap", (21, 13, 9), 5),
+                                                ("sten", (11, 9, 12), 3), ("sten", (24, 25, 26), 1), ("lu", (9, 14, 8), 2),
+                                                ("lu", (24, 24, 24), 1), ("lu", (30, 30, 30), 4)])
+def test_subtrees_and_normalization_tiles(family, shape, batch):
+    """Bottom subtrees and their depths' launches hold every small node once;
+    the normalization's tiles are its row blocks', chunk by chunk."""
+    from paper_1604_02528_amd import capi
+
+    S = _context(family, shape, batch)
+    capi.selinv_check_plan(S.h)
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 200])
+def test_subtrees_of_two_dimensional_grids(n):
+    from paper_1604_02528_amd import SelInv, capi
+
+    colptr, rowind = grids.laplacian_2d_dirichlet(n, 31, 0.1)[:2]
+    for dtype in ("f64", "c128", "h128", "lu64"):
+        S = SelInv(31 * n, colptr, rowind, grids.nested_dissection((n, 31)), dtype=dtype, device="cpu",
+                   adjoint=dtype in ("f64", "c128"))
+        capi.selinv_check_plan(S.h)
