@@ -141,7 +141,8 @@ class SelInv:
         return v
 
     def _values_device(self, values):
-        v = torch.as_tensor(values)
+        # (the library reads the memory: a lazily conjugated or negated tensor is formed first)
+        v = torch.as_tensor(values).resolve_conj().resolve_neg()
         return v.to(device=self.device, dtype=self.scalar_dtype).reshape(self.batch, self.nvals).contiguous()
 
     def factor(self, values, want_dtilde=False, on_device=False):
