@@ -73,6 +73,7 @@ KERNEL_SOURCES = [
     "paper_1604_02528_amd/csrc/tile.hpp",
     "paper_1604_02528_amd/csrc/plan.hpp",
     "paper_1604_02528_amd/csrc/scalar.hpp",
+    "paper_1604_02528_amd/csrc/blk16.hpp",
 ]
 
 
@@ -604,9 +605,12 @@ def main():
                                      "on a 1 GiB device copy)",
                      "algorithmic_bytes": algorithmic_bytes(w, args.relax),
                      "kernel": {"levels": "k_ydense (GEMM-1 tiles of nodes with a dense X_{C,C} buffer), "
-                                          "k_gather_list (gathers into those buffers), k_gemm2_list (GEMM-2 "
-                                          "shares), k_items_list (the other items) and k_tiny / k_tiny64 "
-                                          "(single-wavefront small nodes), one launch per etree depth and phase",
+                                          "k_gather_list (gathers into those buffers), k_ygather (gathered "
+                                          "GEMM-1 tiles), k_gemm2_dense (GEMM-2 of wide nodes), k_gemm2_list "
+                                          "(split sums, GEMM-2 shares), k_diag_list (diagonal blocks), "
+                                          "k_items_list (the other items) and k_tiny / k_tiny64 / k_tiny_lu "
+                                          "(single-wavefront small nodes), one launch per etree depth and "
+                                          "phase; k_sub (bottom subtrees of small nodes), one launch",
                                 "persistent": "k_persistent, one launch",
                                 "push": "k_push (the O/I/ID tiles of the left-looking form) and k_items_list "
                                         "(the D step), one launch per etree depth and step"}[args.sched],

@@ -176,7 +176,7 @@ typedef struct {
   int64_t panels_bytes;  /* factor panels, batch * panel_elems scalars */
   int64_t x_bytes;       /* selected inverse, same layout */
   int64_t work_bytes;    /* device tables, normalize scratch, counters, queue */
-  int64_t dtilde_bytes;  /* optional pivot blocks Dt_K (needed by selinv_backward) */
+  int64_t dtilde_bytes;  /* optional pivot blocks Dt_K (selinv_backward asks for them but does not read them) */
   int64_t abar_bytes;    /* adjoint / selinv_extract output on A's pattern, batch * nnz(A) scalars
                             (SELINV_LU64: batch * 2 nnz(A)) */
   int64_t trace_bytes;   /* optional selinv_trace buffer */
@@ -419,13 +419,19 @@ selinv_status selinv_trace(selinv_ctx *h, void *trace_dev);
  *     as the BackItemType of the device plan, 12 / 13 = the whole R1 / R3 of a
  *     small node in one wavefront.  The launches follow this order but take
  *     several formulas at once.
- *   which = 2: the forward traversal's launches under the level and push
- *     schedules, in order: {kind (0 work items, 1 single-wavefront nodes,
+ *   which = 2: the forward traversal's work items by launch under the level
+ *     and push schedules, in order: {kind (0 work items, 1 single-wavefront nodes,
  *     2 dense-buffer GEMM-1 tiles with their GEMM-2 shares, 3 push tiles,
  *     4 GEMM-1-only 128 x 128 tiles of FP64 nodes the tune table marks, 5 gathers into
- *     the dense X_{C,C} buffers, 6 GEMM-2 shares), items or records
- *     per matrix, type of the first item (-1 for push tiles), etree depth}.  The list is
- *     built for every plan; the persistent schedule does not launch by it.
+ *     the dense X_{C,C} buffers, 6 split sums and GEMM-2 shares), items or records
+ *     per matrix, type of the first item (-1 for push tiles), etree depth}.  Kind 0
+ *     takes three kernels: diagonal blocks (k_diag_list), gathered GEMM-1 tiles
+ *     (k_ygather) and, where a launch mixes types, k_items_list.  Not listed, since
+ *     they hold no items: the GEMM-2 products of wide nodes (k_gemm2_dense, before
+ *     the launch of their diagonal blocks), and the launch of the bottom subtrees
+ *     (k_sub, last), which takes single-wavefront nodes that are listed at their
+ *     depths.  The list is built for every plan; the persistent schedule does
+ *     not launch by it.
  *   which = 3: the normalization chunks of selinv_normalize_run (level
  *     schedule), in order: {first level launch, its etree depth,
  *     normalization work entries of the chunk, 0}.  Chunk 0 is the top

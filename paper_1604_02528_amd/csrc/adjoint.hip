@@ -32,7 +32,8 @@
 // runs in two launches between the sweeps, and N needs no product with Dt.
 // With a launch for every formula of every depth (nine), in one kernel at one
 // workgroup a CU for complex, the 200 x 200 GMRF's reverse sweep took 1.47 ms (84
-// launches of 15 us, now 1.05 ms) and four complex 20^3 shifts' 5.11 ms (now 3.54).
+// launches of 15 us, now 1.05 ms) and four complex 20^3 shifts' 5.11 ms (now 3.79,
+// 0.25 of it the fourth product of complex tiles, see gemm_il).
 // Bound by the chain of depths: few tiles each, of 20 to 150 us.
 //
 // Every step is a 64 x 64 tile on the MFMA machinery of the forward sweep;

@@ -152,10 +152,11 @@ constexpr int64_t kDefaultDenseMinC = 256;
 // launches wait on latency, and two streams only double them.  One stream for
 // two, at 0.10 G: FP64 20^3, four matrices, 854 and 945 us; 0.17 G: two complex
 // 24^3 shifts 1818 and 2069; 0.22 G: 27-point 23x17x29, three shifts, with the
-// factorization 3577 and 3705; 0.33 G: LU 24^3, two shifts, 1234 and 1298, FP64
-// 30^3 1269 and 1300 (but 24^3, 0.08 G: 880 and 865); 0.42 G: FP64 26^3, three
-// matrices, 1467 and 1405; 0.50 G: FP64 34^3 2133 and 2002; 1.3 G: 40^3 3236
-// and 2983; 2.6 G: LU 30^3, four shifts, 4105 and 3815.
+// factorization 3577 and 3705; 0.33 G: LU 24^3, two shifts, 1234 and 1298; 0.42
+// G: FP64 26^3, three matrices, 1467 and 1405; 2.6 G: LU 30^3, four shifts, 4105
+// and 3815.  The subtree groups of a single matrix lose nothing below the line
+// (FP64 24^3, 0.08 G: 889 and 857; 30^3, 0.33 G: 1301 and 1291) and gain above it
+// (34^3, 0.50 G: 2208 and 1993; 40^3, 1.3 G: 3230 and 2957).
 constexpr double kTwoStreamWork = 0.37e9;
 // Row tiles from which GEMM-2 is a product of its own (from 8 on only: the
 // same within 0.4% either way, 30.07 for 30.17 ms and 3.10 for 3.08 ms on
@@ -2517,9 +2518,8 @@ selinv_status selinv_items(const selinv_ctx *hc, int32_t which, const int32_t **
     return SELINV_OK;
   }
   if (which == 2) {
-    // the forward traversal's level launches in order (what the level and
-    // push schedules launch): {kind, items per matrix, type of the first
-    // item (-1 for a push launch), etree depth}
+    // the forward traversal's items by level launch, in order: {kind, items per
+    // matrix, type of the first item (-1 for a push launch), etree depth}
     if (h->lseq.empty()) {
       const HostPlan &H = h->H;
       int32_t depth = -1;  // a push launch follows the D step of its depth

@@ -274,7 +274,7 @@ template <typename T> __device__ __forceinline__ void ldl16_store(const double *
 // have almost no arithmetic: what bounds them is the launches and the
 // dependent rounds of loads (record -> panel and row tables -> positions), so
 // one launch does everything and a CU holds many nodes at once (four launches
-// on 64 x 64 tiles before; 31 x 31 FP64 grid: 0.27 -> 0.08 ms for its ten depths;
+// on 64 x 64 tiles before; 31 x 31 FP64 grid: 0.27 -> 0.07 ms for its ten depths;
 // 16 Hermitian 30^3 matrices, the lower 13 depths: 10.5 -> 1.7 ms, where the
 // atomics of nodes with c near 64 bound it: 1.9 ms with the two planes of an
 // entry added by separate instructions, 1.1 with whole entries, see blk_atomic).
@@ -448,7 +448,7 @@ __global__ void __launch_bounds__(NT, 2) k_fac_mid(const DevPlan *__restrict__ p
 // M S^T and L^T = D^{-1} W^T and go to LDS; every block right of the panel
 // takes its rank-16 update.  The next diagonal block is updated and factored
 // before its owner's other blocks.  What bounds it is the serial chain of the
-// ldl16 steps: 25 us (FP64) and 55 us (complex) for 128 columns; 19.9 -> 0.84 ms
+// ldl16 steps: 27 us (FP64) and 56 us (complex) for 128 columns; 19.9 -> 0.90 ms
 // of diagonal blocks a factorization on the 40^3 FP64 Laplacian, 15.9 -> 1.2 ms
 // on 16 Hermitian 30^3 matrices; the form before updated the block in global memory, one
 // thread an element, 1.3 ms (FP64) and 1.7 ms (complex) for 256 columns.
@@ -541,7 +541,7 @@ __global__ void __launch_bounds__(64 * kFacWaves, 2)
 // while step k is multiplied.  No inverse of the whole L_KK is formed, and no
 // column waits for another workgroup.  Bound by the chain of eight steps where
 // few rows are left, else by MFMA: 40^3 FP64, inverse and product 2.4 ms a
-// factorization before, 0.6 ms now; 16 Hermitian 30^3 matrices 8.0 -> 1.6 ms.
+// factorization before, 0.6 ms now; 16 Hermitian 30^3 matrices 8.0 -> 1.5 ms.
 template <typename T>
 __global__ void __launch_bounds__(NT, 2)
     k_fac_lc(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs, const int2 *rblocks, int32_t nrb) {
@@ -647,7 +647,9 @@ template <typename T, int TK> struct FacLoadB : LoadDenseAIl<T, TK> {
 // MFMA-bound on wide nodes, by the atomics on narrow ones.  Branch-free
 // interleaved stages at two workgroups a CU; complex products in the
 // four-product form: the 3M form's imaginary part carries an error of the real
-// parts' size, which a nearly real pivot's imaginary part would show.
+// parts' size, which a nearly real pivot's imaginary part would show.  16 Hermitian
+// 30^3 matrices: 12.7 ms of updates (nodes beyond the single-wavefront ones) ->
+// 8.1 ms (5.5 in the 3M form).
 template <typename T, bool INNER>
 __global__ void __launch_bounds__(NT, 2)
     k_fac_update(const DevPlan *__restrict__ plp, T *Pall, const FacNode *recs, const int4 *tiles, int32_t ntiles) {

@@ -195,7 +195,7 @@ struct DevPlan {
   // adjoint scratch, [batch][panel_elems] each (panel layout) and
   // [batch][sq_elems] each (s x s per node, column-major); null when the work area
   // was sized without them
-  void *adj_z, *adj_l, *adj_s;  // Zbar then M; Lhatbar then Lb; Sbar
+  void *adj_z, *adj_l, *adj_s;  // Zbar; Lhatbar; Sbar (its rows below the diagonal blocks hold N0 between the sweeps)
   void *adj_t, *adj_f, *adj_d;  // Tbar; F; Dtbar0
   Item *bitems;        // adjoint work items
   int64_t *dpos;       // [n] panel element of each pivot D_jj (one matrix)

@@ -750,7 +750,9 @@ template <typename T, int TK> __device__ __forceinline__ constexpr int dense_sta
 // Re = P1 - P2 and Im = P3 - P1 - P2.  The operand sums are formed from the
 // two LDS planes as they are read, so the stages keep their layout.  Its
 // rounding error bound is that of the four-product form with |Ar| + |Ai| and
-// |Br| + |Bi| in place of the moduli (the same order).
+// |Br| + |Bi| in place of the moduli: the same order for the entry as a whole.
+// The imaginary part's error is of the real parts' size, so the factorization
+// and the adjoint take four products.
 struct Acc3M {
   d4 v[3][2][2];
 };
